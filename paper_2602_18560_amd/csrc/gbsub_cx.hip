@@ -35,16 +35,21 @@
 //    amplitude and the source count), so injection and subtraction are
 //    order-independent integer adds and a subtracted template cancels to the
 //    last bit: h always equals the sum of the (rounded) templates of the
-//    sources left.
-//  * Injection is binned: sources are grouped by 1024-bin tile (LDS
-//    histograms, one scan, a scatter with per-block range reservations);
-//    each block accumulates up to CH sources of one tile into an LDS window
-//    of the tile plus the template reach on each side (even and odd bins
-//    apart: the lanes of one atomic add hit pairs of neighbouring words), then
-//    adds the window to h with one global atomic per touched word.  Each
-//    wave takes an equal share of the chunk, 64 sources at a time: their
-//    constants are computed one per lane and broadcast by readlane while
-//    the wave synthesises one template after the other.
+//    candidates left plus the fixed sum of the sources that can never be
+//    candidates.
+//  * Injection.  Most sources of a large catalog are too faint to be
+//    candidates and share their centre bin with many others: the moment path
+//    (k_cx_faint) sums the Taylor coefficients of their samples per centre, in
+//    integers, and transforms once per centre and channel.  The others take
+//    the direct path (k_cx_inject): sources are grouped by 1024-bin tile (LDS
+//    histograms, one scan, a scatter with per-block range reservations); each
+//    block accumulates a chunk of one tile's sources into an LDS window of
+//    the tile plus the template reach on each side (even and odd bins apart:
+//    the lanes of one atomic add hit pairs of neighbouring words), then adds
+//    the window to h with one global atomic per touched word.  Each wave
+//    takes an equal share of the chunk, 64 sources at a time: their constants
+//    are computed one per lane and broadcast by readlane while the wave
+//    synthesises one template after the other.
 //  * The per-channel PSD is the power model's median (or mean) kernel, run
 //    over a two-slot descriptor table (A and E), with the same dirty-tile
 //    stamps; a body is X update, PSD, SNR + subtraction, and a one-block tail.
@@ -64,6 +69,18 @@ constexpr int HALO = NF / 2;                  // template reach on each side of 
 constexpr int CXW = CX_TILE + NF;             // LDS window of an injection block
 constexpr int SRC_PB = 4096;                  // sources per block of the count and scatter passes
 constexpr int CH = 8192;                      // sources per injection block at most
+constexpr int CH_MIN = 32;                    // and at least (a block's four waves take a quarter each)
+constexpr int CH_GRID = 2048;                 // injection blocks that fill the chip
+constexpr uint32_t KEY_NONE = 0xFFFFFFFFu;    // source key: no template on the grid
+constexpr uint32_t KEY_FAINT = 0x80000000u;   // source key: the moment path takes it
+constexpr uint32_t FAINT_MIN_N = 1u << 16;    // smallest catalog with a moment path
+constexpr double FAINT_MAX_D = 0.25 * 4.0 / 3.141592653589793;   // its largest |fdot| T^2 (|b| <= 1/4)
+constexpr int NMOM = 28;                      // moments per centre
+constexpr int FB_MAX = 16384;                 // faint buckets at most
+constexpr int FB_SRC = 16384;                 // sources per block of the faint passes
+constexpr int FB_T = 1024;                    // threads of those blocks
+constexpr int MOM_MIN = 12;                   // fewer faint sources of a centre: one template each
+constexpr int MOM_COOP = 2048;                // more: all waves of the block share the centre
 constexpr int SNR_GRID = 2048;                // blocks of the SNR launch
 constexpr int PLAN_T = 1024;                  // threads of the one-block plan
 
@@ -269,6 +286,26 @@ __device__ __forceinline__ LaneFft lane_fft()
     return L;
 }
 
+// The lane constants in LDS (18 values per lane, one row of doubles each), for
+// kernels that need their registers between transforms.
+constexpr int LFW = sizeof(LaneFft) / sizeof(double);
+
+__device__ __forceinline__ void keep_fft(const LaneFft &L, double (*s)[64])
+{
+    const double *v = reinterpret_cast<const double *>(&L);
+#pragma unroll
+    for (int i = 0; i < LFW; ++i) s[i][lane()] = v[i];
+}
+
+__device__ __forceinline__ LaneFft kept_fft(const double (*s)[64])
+{
+    LaneFft L;
+    double *v = reinterpret_cast<double *>(&L);
+#pragma unroll
+    for (int i = 0; i < LFW; ++i) v[i] = s[i][lane()];
+    return L;
+}
+
 // Per-source constants of a template: index, centre bin, the phase
 // delta x + dh x^2 in turns (dh = d/2), the scale sc = (A/2) (T/128) 2^E of
 // the samples, and the channel rotations exp(i phi_A) = (ca, sa) and
@@ -281,23 +318,17 @@ struct SrcConsts {
     double delta, dh, sc, ca, sa, ce, se;
 };
 
-// The template of one source, by the whole wave: on return each lane holds
-// two values of 2^E U (U itself when sc = (A/2)(T/128)), at the offsets
-// lane_offsets gives.  The phase is the definition's operations in their
-// order (delta x, (d/2) x^2, their sum), so it is the same double as in a
-// plain evaluation.  Decimation in frequency: the first stage (n, n + 64)
+// The 128-point DFT of the samples a (n = ell) and b (n = ell + 64) of each
+// lane, by the whole wave: on return each lane holds two of its values, at
+// the offsets lane_offsets gives.  Decimation in frequency: the first stage (n, n + 64)
 // inside the lane gives the even and odd outputs as two 64-point DFTs a and
 // b (registers P = a, Q = b).  The spans 32 and 16 are row swaps of P with
 // Q, after which every lane holds both elements of one butterfly (of a or
 // of b) and computes both outputs; the spans 8 .. 1 exchange within each
 // register (the partner's value p and the own v give p + sg v, times the
 // twiddle, so the first lane gets the sum and the second the difference).
-__device__ __forceinline__ void wave_template(const SrcConsts &c, const LaneFft &L, const double2 *ex,
-                                              double2 *ue, double2 *uo)
+__device__ __forceinline__ void wave_fft(double2 a, double2 b, const LaneFft &L, double2 *ue, double2 *uo)
 {
-    const double2 e0 = cis_turns(c.delta * L.x0 + c.dh * L.x0q, ex);
-    const double2 e1 = cis_turns(c.delta * L.x1 + c.dh * L.x1q, ex);
-    const double2 a = make_double2(c.sc * e0.x, c.sc * e0.y), b = make_double2(c.sc * e1.x, c.sc * e1.y);
     double2 P = cadd(a, b);
     double2 Q = cmulf(csub(a, b), L.w1);
     // span 32, then 16: full butterflies (twiddle 1 on the sum)
@@ -344,6 +375,18 @@ __device__ __forceinline__ void wave_template(const SrcConsts &c, const LaneFft 
         *ue = make_double2(fma(sg, P.x, p0.x), fma(sg, P.y, p0.y));
         *uo = make_double2(fma(sg, Q.x, p1.x), fma(sg, Q.y, p1.y));
     }
+}
+
+// The template of one source, by the whole wave: 2^E U (U itself when sc =
+// (A/2)(T/128)).  The phase is the definition's operations in their order
+// (delta x, (d/2) x^2, their sum), so it is the same double as in a plain
+// evaluation.
+__device__ __forceinline__ void wave_template(const SrcConsts &c, const LaneFft &L, const double2 *ex,
+                                              double2 *ue, double2 *uo)
+{
+    const double2 e0 = cis_turns(c.delta * L.x0 + c.dh * L.x0q, ex);
+    const double2 e1 = cis_turns(c.delta * L.x1 + c.dh * L.x1q, ex);
+    wave_fft(make_double2(c.sc * e0.x, c.sc * e0.y), make_double2(c.sc * e1.x, c.sc * e1.y), L, ue, uo);
 }
 
 // The value of a channel with rotation (c, s) = exp(i phi_c): exp(i phi_c) v.
@@ -399,7 +442,10 @@ __global__ __launch_bounds__(WG) void k_cx_reset(KArgs a)
     const size_t stride = (size_t)gridDim.x * WG;
     const size_t i0 = (size_t)blockIdx.x * WG + threadIdx.x;
     for (size_t k = i0; k < 4 * (size_t)g.B; k += stride) d.h[k] = 0;
-    for (size_t k = i0; k <= (size_t)d.ntc; k += stride) d.tcnt[k] = 0;
+    for (size_t k = i0; k <= (size_t)d.ntc; k += stride) {
+        d.tcnt[k] = 0;
+        d.fcnt[k] = 0;
+    }
     for (size_t k = i0; k < (size_t)g.nt; k += stride) {
         d.xstamp[k] = 0;
         d.sstamp[k] = 0;
@@ -453,9 +499,31 @@ __global__ __launch_bounds__(WG) void k_cx_isxmax(KArgs a)
     if (lane() == 0) a.d.isx_max[seg] = m;
 }
 
-// Sources per binning tile (LDS histogram per block), the largest amplitude
-// of the valid entries (it sets the fixed-point unit, a function of the
-// catalog's size and amplitudes only), and the validity of every entry.
+// Whether the moment path takes a source (the "faint" sources, see
+// k_cx_faint): centred on the grid, a chirp inside the range of its
+// polynomial, and a lone SNR that cannot reach the candidate cut.  The last
+// by Parseval (sum_j |U_j|^2 = T^2 A^2 / 4): rho_0^2 <= 2 T A^2 max 1/S_instr
+// over the template's (at most two) segments.  With a cut above 1 the bound
+// stays 1, so the data a set of sources gives do not depend on the
+// thresholds.
+__device__ __forceinline__ double lone_bound(const Grid &g, const double *isx_max, double A, int qb)
+{
+    const int g0 = max(qb - HALO, 0) / NF, g1 = min(qb + HALO - 1, g.B - 1) / NF;
+    return 2.0 * g.T * (A * A) * fmax(isx_max[g0], isx_max[g1]) * (1.0 + 1e-9);
+}
+
+__device__ __forceinline__ bool is_faint(const Grid &g, const CxDev &d, float A, int qb, double dd)
+{
+    if (qb < 0 || qb >= g.B || !(fabs(dd) <= FAINT_MAX_D)) return false;
+    return lone_bound(g, d.isx_max, (double)A, qb) < fmin(g.cut2, 1.0);
+}
+
+// One pass over the catalog: validity, the largest amplitude of the valid
+// entries (it sets the fixed-point unit, a function of the catalog's size
+// and amplitudes only), each source's key (its centre bin clamped to the
+// grid and whether the moment path takes it) and the sources per binning
+// tile, those of the moment path apart (LDS histogram per block, the two
+// counts as 16-bit halves of a word).  Eight sources per thread in flight.
 __global__ __launch_bounds__(WG) void k_cx_count(KArgs a)
 {
     __shared__ uint32_t hist[CX_NTC_MAX];
@@ -467,122 +535,368 @@ __global__ __launch_bounds__(WG) void k_cx_count(KArgs a)
     if (threadIdx.x == 0) s_amax = 0;
     __syncthreads();
     const uint32_t b0 = blockIdx.x * (uint32_t)SRC_PB;
+    const bool faint_n = in.n >= FAINT_MIN_N;
     uint32_t amax = 0, bad = 0;
-    for (int r = 0; r < SRC_PB / WG; ++r) {
-        const uint32_t i = b0 + (uint32_t)(r * WG) + threadIdx.x;
-        if (i >= in.n) break;
-        const float A = in.A[i], f = in.F[i], fd = in.FD[i];
-        if (!entry_ok(A, f, fd, in.PA[i], in.PE[i])) {
-            bad = 1;
-            continue;
+    constexpr int U = 8;
+    for (int r0 = 0; r0 < SRC_PB / WG; r0 += U) {
+        float A[U], f[U], fd[U], pa[U], pe[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const uint32_t i = min(b0 + (uint32_t)((r0 + q) * WG) + threadIdx.x, in.n - 1u);
+            A[q] = in.A[i];
+            f[q] = in.F[i];
+            fd[q] = in.FD[i];
+            pa[q] = in.PA[i];
+            pe[q] = in.PE[i];
         }
-        amax = max(amax, __float_as_uint(A));
-        double delta, dd;
-        const int qb = centre_bin(g, f, fd, &delta, &dd);
-        if (qb == INT_MIN) continue;
-        atomicAdd(&hist[bin_tile(g, qb)], 1u);
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const uint32_t i = b0 + (uint32_t)((r0 + q) * WG) + threadIdx.x;
+            if (i >= in.n) continue;
+            uint32_t key = KEY_NONE;
+            if (!entry_ok(A[q], f[q], fd[q], pa[q], pe[q])) {
+                bad = 1;
+            } else {
+                amax = max(amax, __float_as_uint(A[q]));
+                double delta, dd;
+                const int qb = centre_bin(g, f[q], fd[q], &delta, &dd);
+                if (qb != INT_MIN) {
+                    const bool faint = faint_n && is_faint(g, d, A[q], qb, dd);
+                    key = (uint32_t)min(max(qb, 0), g.B - 1);
+                    atomicAdd(&hist[key / CX_TILE], faint ? 0x10000u : 1u);
+                    key |= faint ? KEY_FAINT : 0u;
+                }
+            }
+            d.key[i] = key;
+        }
     }
     if (bad) atomicOr(&d.ctl->bad, 1u);
-    atomicMax(&s_amax, amax);
+    for (int o = 32; o >= 1; o >>= 1) amax = max(amax, (uint32_t)__shfl_xor((int)amax, o, 64));
+    if (lane() == 0) atomicMax(&s_amax, amax);
     __syncthreads();
-    for (int t = threadIdx.x; t < d.ntc; t += WG)
-        if (hist[t]) atomicAdd(&d.tcnt[t], hist[t]);
+    for (int t = threadIdx.x; t < d.ntc; t += WG) {
+        const uint32_t h = hist[t];
+        if (h & 0xFFFFu) atomicAdd(&d.tcnt[t], h & 0xFFFFu);
+        if (h >> 16) atomicAdd(&d.fcnt[t], h >> 16);
+    }
     if (threadIdx.x == 0 && s_amax) atomicMax(&d.ctl->amax_bits, s_amax);
 }
 
-// One block: tile offsets (tcnt becomes its exclusive prefix, tcnt[ntc] the
-// total), scatter cursors, and the injection chunks of each tile (cbase).
+// Exclusive prefix over the block's PLAN_T threads of three counts per
+// thread; *tot gets their totals.  Contains two barriers.
+struct Cnt3 {
+    uint32_t a, b, c;
+};
+
+__device__ __forceinline__ Cnt3 plan_scan(Cnt3 x, Cnt3 *sw, Cnt3 *tot)
+{
+    const int l = lane(), w = threadIdx.x >> 6;
+    Cnt3 i = x;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t ya = (uint32_t)__shfl_up((int)i.a, o, 64), yb = (uint32_t)__shfl_up((int)i.b, o, 64),
+                       yc = (uint32_t)__shfl_up((int)i.c, o, 64);
+        if (l >= o) {
+            i.a += ya;
+            i.b += yb;
+            i.c += yc;
+        }
+    }
+    __syncthreads();
+    if (l == 63) sw[w] = i;
+    __syncthreads();
+    Cnt3 p = {i.a - x.a, i.b - x.b, i.c - x.c}, t = {0, 0, 0};
+    for (int v = 0; v < PLAN_T / 64; ++v) {
+        const Cnt3 y = sw[v];
+        if (v < w) {
+            p.a += y.a;
+            p.b += y.b;
+            p.c += y.c;
+        }
+        t.a += y.a;
+        t.b += y.b;
+        t.c += y.c;
+    }
+    *tot = t;
+    return p;
+}
+
+// One block: the direct sources' tile offsets (tcnt becomes its exclusive
+// prefix, tcnt[ntc] the total), scatter cursors and injection chunks per tile
+// (cbase); and the faint buckets of each tile (fbb, exclusive prefix).
+//
+// Chunks: a tile's sources in blocks of `chunk`, the total over CH_GRID
+// blocks rounded up to a power of two within [CH_MIN, CH].  A wave takes
+// ~1.2 us per template, so a tile of 1000 sources in one chunk kept four
+// waves busy for 300 us with the rest of the chip idle (1e4 sources, T = 1
+// yr); past CH_GRID full chunks the fewer window flushes pay.
+//
+// Buckets: a tile's 1024 centres are cut into a power of two of equal ranges
+// so that a bucket's estimated work, in wave instructions (a centre's
+// moments ~1300, or its few templates ~240 each, and 16 per faint source), is
+// at most the larger of 2^16 and a 3072nd of the catalog's.
+__device__ __forceinline__ uint32_t faint_cost(uint32_t cnt)
+{
+    return min(240u * min(cnt, 1u << 20), 1300u * CX_TILE) / 64u + min(cnt, 1u << 28) / 4u;   // in units of 64
+}
+
 __global__ __launch_bounds__(PLAN_T) void k_cx_plan(KArgs a)
 {
-    __shared__ uint32_t sw[2][PLAN_T / 64];
-    __shared__ uint32_t carry[2];
+    constexpr int RUN = CX_NTC_MAX / PLAN_T;
+    __shared__ Cnt3 sw[PLAN_T / 64];
     const CxDev &d = a.d;
     const int ntc = d.ntc;
-    if (threadIdx.x == 0) carry[0] = carry[1] = 0;
-    __syncthreads();
-    const int l = lane(), w = threadIdx.x >> 6;
-    for (int base = 0; base < ntc; base += PLAN_T) {
-        const int t = base + (int)threadIdx.x;
-        const uint32_t cnt = t < ntc ? d.tcnt[t] : 0u;
-        const uint32_t nch = (cnt + CH - 1) / CH;
-        uint32_t ic = cnt, ih = nch;
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t yc = (uint32_t)__shfl_up((int)ic, o, 64);
-            const uint32_t yh = (uint32_t)__shfl_up((int)ih, o, 64);
-            if (l >= o) {
-                ic += yc;
-                ih += yh;
-            }
+    const int t0 = (int)threadIdx.x * RUN;
+    uint32_t cnt[RUN], fc[RUN];
+    Cnt3 s = {0, 0, 0}, tot;
+#pragma unroll
+    for (int r = 0; r < RUN; ++r) {
+        cnt[r] = t0 + r < ntc ? d.tcnt[t0 + r] : 0u;
+        fc[r] = t0 + r < ntc ? d.fcnt[t0 + r] : 0u;
+        s.a += cnt[r];
+        s.b += fc[r] ? faint_cost(fc[r]) : 0u;
+    }
+    (void)plan_scan(s, sw, &tot);
+    const uint32_t want = (tot.a + CH_GRID - 1) / CH_GRID;
+    uint32_t chunk = CH_MIN;
+    while (chunk < want && chunk < (uint32_t)CH) chunk <<= 1;
+    const uint32_t cap = max(1024u, tot.b / 3072u);
+    uint32_t lb[RUN];
+    s = {0, 0, 0};
+#pragma unroll
+    for (int r = 0; r < RUN; ++r) {
+        s.a += cnt[r];
+        s.b += (cnt[r] + chunk - 1) / chunk;
+        lb[r] = 0;
+        if (fc[r]) {
+            const uint32_t c = faint_cost(fc[r]);
+            while (lb[r] < 10u && (c >> lb[r]) > cap) ++lb[r];
+            s.c += 1u << lb[r];
         }
-        if (l == 63) {
-            sw[0][w] = ic;
-            sw[1][w] = ih;
-        }
-        __syncthreads();
-        uint32_t pc = carry[0], ph = carry[1], tc = 0, th = 0;
-        for (int v = 0; v < PLAN_T / 64; ++v) {
-            pc += v < w ? sw[0][v] : 0u;
-            ph += v < w ? sw[1][v] : 0u;
-            tc += sw[0][v];
-            th += sw[1][v];
-        }
-        if (t < ntc) {
-            d.tcnt[t] = pc + ic - cnt;
-            d.tcur[t] = pc + ic - cnt;
-            d.cbase[t] = ph + ih - nch;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            carry[0] += tc;
-            carry[1] += th;
-        }
-        __syncthreads();
+    }
+    Cnt3 p = plan_scan(s, sw, &tot);
+#pragma unroll
+    for (int r = 0; r < RUN; ++r) {
+        if (t0 + r >= ntc) continue;
+        d.tcnt[t0 + r] = p.a;
+        d.tcur[t0 + r] = p.a;
+        d.cbase[t0 + r] = p.b;
+        d.fbb[t0 + r] = p.c;
+        p.a += cnt[r];
+        p.b += (cnt[r] + chunk - 1) / chunk;
+        p.c += fc[r] ? 1u << lb[r] : 0u;
     }
     if (threadIdx.x == 0) {
-        d.tcnt[ntc] = carry[0];
-        d.cbase[ntc] = carry[1];
+        d.tcnt[ntc] = tot.a;
+        d.cbase[ntc] = tot.b;
+        d.fbb[ntc] = tot.c;
+        d.ctl->n_chunks = chunk;
+        d.ctl->n_events = tot.c;
+        if (tot.c > (uint32_t)FB_MAX) d.ctl->bad |= 2u;    // cannot happen: ntc + 2 x 3072 at most
     }
 }
 
-// Groups the sources by binning tile: per block, an LDS count per tile, one
-// global reservation of each tile's range, then LDS ranks inside it.
-__global__ __launch_bounds__(WG) void k_cx_scatter(KArgs a)
+// Groups the direct sources by binning tile: per block, an LDS count per
+// tile, one global reservation of each tile's range, then LDS cursors in it.
+__global__ __launch_bounds__(FB_T) void k_cx_scatter(KArgs a)
 {
-    __shared__ uint32_t cnt[CX_NTC_MAX];
-    __shared__ uint32_t rank[CX_NTC_MAX];
-    const Grid &g = a.g;
+    __shared__ uint32_t cur[CX_NTC_MAX];
     const CxDev &d = a.d;
     const CxIn &in = a.in;
-    for (int t = threadIdx.x; t < d.ntc; t += WG) {
-        cnt[t] = 0;
-        rank[t] = 0;
+    for (int t = threadIdx.x; t < d.ntc; t += FB_T) cur[t] = 0;
+    __syncthreads();
+    const uint32_t b0 = blockIdx.x * (uint32_t)FB_SRC;
+    int tile[FB_SRC / FB_T];
+#pragma unroll
+    for (int r = 0; r < FB_SRC / FB_T; ++r) {
+        const uint32_t i = b0 + (uint32_t)(r * FB_T) + threadIdx.x;
+        const uint32_t k = d.key[min(i, in.n - 1u)];
+        tile[r] = i >= in.n || (k & KEY_FAINT) ? -1 : (int)(k / CX_TILE);      // KEY_NONE has the bit set
+    }
+#pragma unroll
+    for (int r = 0; r < FB_SRC / FB_T; ++r)
+        if (tile[r] >= 0) atomicAdd(&cur[tile[r]], 1u);
+    __syncthreads();
+    for (int t = threadIdx.x; t < d.ntc; t += FB_T)
+        if (cur[t]) cur[t] = atomicAdd(&d.tcur[t], cur[t]);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < FB_SRC / FB_T; ++r)
+        if (tile[r] >= 0) d.order[atomicAdd(&cur[tile[r]], 1u)] = b0 + (uint32_t)(r * FB_T) + threadIdx.x;
+}
+
+// ---- the faint sources by bucket (catalogs of at least FAINT_MIN_N sources)
+//
+// As the power model's binning: a count pass writes each block's sources per
+// bucket, a column pass turns them into offsets, and after a scan of the
+// totals the scatter pass copies the records (amplitude, frequency,
+// derivative, centre in the tile; phases) to their buckets, so that the
+// moment blocks read contiguous memory instead of gathering five columns of
+// a catalog in random order (64 bytes of HBM per 4-byte value).  A record is
+// one 16-byte and one 8-byte store, and the blocks of one XCD take
+// neighbouring rows, whose slots of a bucket are neighbours: with a store per
+// column and the rows dealt round-robin, a 128-byte line was written in
+// parts by several XCDs' L2s (845 us for 1e7 sources).
+
+// Row of the faint passes taken by this block: blocks go round-robin over
+// the 8 XCDs, so XCD x gets the rows [x per, (x + 1) per).
+__device__ __forceinline__ uint32_t faint_row(uint32_t rows)
+{
+    const uint32_t per = (rows + 7u) / 8u;
+    return (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+}
+
+// Bucket of a faint source and the tile map in LDS: word t holds the first
+// bucket of tile t << 4 | log2(buckets of t).
+__device__ __forceinline__ void load_bucket_map(const CxDev &d, uint32_t *map)
+{
+    for (int t = threadIdx.x; t < d.ntc; t += FB_T) {
+        const uint32_t b = d.fbb[t], m = d.fbb[t + 1] - b;
+        map[t] = (b << 4) | (m > 1u ? 31u - (uint32_t)__clz((int)m) : 0u);
+    }
+}
+
+__device__ __forceinline__ uint32_t bucket_of(const uint32_t *map, uint32_t key)
+{
+    const uint32_t k = key & ~KEY_FAINT, w = map[k / CX_TILE];
+    return (w >> 4) + ((k % CX_TILE) >> (10u - (w & 15u)));
+}
+
+__global__ __launch_bounds__(FB_T) void k_cx_fcount(KArgs a)
+{
+    __shared__ uint32_t map[CX_NTC_MAX];
+    __shared__ uint32_t hist[FB_MAX / 2];           // 16-bit counts
+    const CxDev &d = a.d;
+    const uint32_t nbk = d.ctl->n_events;
+    if (d.ctl->bad) return;
+    load_bucket_map(d, map);
+    for (uint32_t b = threadIdx.x; b < (nbk + 1) / 2; b += FB_T) hist[b] = 0;
+    __syncthreads();
+    const uint32_t b0 = blockIdx.x * (uint32_t)FB_SRC;
+    uint32_t key[FB_SRC / FB_T];
+#pragma unroll
+    for (int r = 0; r < FB_SRC / FB_T; ++r) {
+        const uint32_t i = b0 + (uint32_t)(r * FB_T) + threadIdx.x;
+        key[r] = d.key[min(i, a.in.n - 1u)];
+        if (i >= a.in.n) key[r] = KEY_NONE;
+    }
+#pragma unroll
+    for (int r = 0; r < FB_SRC / FB_T; ++r) {
+        if (key[r] == KEY_NONE || !(key[r] & KEY_FAINT)) continue;
+        const uint32_t b = bucket_of(map, key[r]);
+        atomicAdd(&hist[b >> 1], 1u << (16 * (b & 1u)));
     }
     __syncthreads();
-    const uint32_t b0 = blockIdx.x * (uint32_t)SRC_PB;
-    int key[SRC_PB / WG];
+    for (uint32_t b = threadIdx.x; b < nbk; b += FB_T)
+        d.fmat[(size_t)blockIdx.x * nbk + b] = (hist[b >> 1] >> (16 * (b & 1u))) & 0xFFFFu;
+}
+
+// Column pass, in place: the sources of the blocks before, per bucket, and
+// the bucket totals.  64 buckets per block, one per lane; the waves split
+// the rows.
+__global__ __launch_bounds__(FB_T) void k_cx_fcols(KArgs a)
+{
+    constexpr int NV = FB_T / 64, U = 8;
+    __shared__ uint32_t part[NV][64];
+    const CxDev &d = a.d;
+    const uint32_t nbk = d.ctl->n_events;
+    if (blockIdx.x * 64u >= nbk || d.ctl->bad) return;
+    const int l = lane(), w = threadIdx.x >> 6;
+    const uint32_t b = blockIdx.x * 64u + (uint32_t)l;
+    const bool ok = b < nbk;
+    const uint32_t col = ok ? b : nbk - 1u;
+    const uint32_t rows = (a.in.n + FB_SRC - 1) / FB_SRC, per = (rows + NV - 1) / NV;
+    const uint32_t r0 = min(w * per, rows), r1 = min(r0 + per, rows);
+    uint32_t sum = 0;
+    for (uint32_t r = r0; r < r1; r += U) {
+        uint32_t c[U];
 #pragma unroll
-    for (int r = 0; r < SRC_PB / WG; ++r) {
-        const uint32_t i = b0 + (uint32_t)(r * WG) + threadIdx.x;
-        key[r] = -1;
-        if (i < in.n) {
-            const float A = in.A[i], f = in.F[i], fd = in.FD[i];
-            if (entry_ok(A, f, fd, in.PA[i], in.PE[i])) {
-                double delta, dd;
-                const int qb = centre_bin(g, f, fd, &delta, &dd);
-                if (qb != INT_MIN) key[r] = bin_tile(g, qb);
-            }
+        for (int q = 0; q < U; ++q) c[q] = d.fmat[(size_t)min(r + q, r1 - 1) * nbk + col];
+#pragma unroll
+        for (int q = 0; q < U; ++q) sum += r + q < r1 ? c[q] : 0u;
+    }
+    part[w][l] = sum;
+    __syncthreads();
+    uint32_t run = 0, tot = 0;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const uint32_t x = part[v][l];
+        run += v < w ? x : 0u;
+        tot += x;
+    }
+    if (w == 0 && ok) d.ftot[b] = tot;
+    for (uint32_t r = r0; r < r1; r += U) {
+        uint32_t c[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) c[q] = d.fmat[(size_t)min(r + q, r1 - 1) * nbk + col];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            if (r + q >= r1) continue;
+            if (ok) d.fmat[(size_t)(r + q) * nbk + b] = run;
+            run += c[q];
         }
-        if (key[r] >= 0) atomicAdd(&cnt[key[r]], 1u);
     }
-    __syncthreads();
-    for (int t = threadIdx.x; t < d.ntc; t += WG)
-        if (cnt[t]) cnt[t] = atomicAdd(&d.tcur[t], cnt[t]);
-    __syncthreads();
+}
+
+// Bucket bases: ftot becomes its exclusive prefix, ftot[nbk] the total.
+__global__ __launch_bounds__(PLAN_T) void k_cx_fscan(KArgs a)
+{
+    constexpr int RUN = FB_MAX / PLAN_T;
+    __shared__ Cnt3 sw[PLAN_T / 64];
+    const CxDev &d = a.d;
+    const uint32_t nbk = d.ctl->n_events;
+    if (d.ctl->bad) return;
+    const uint32_t t0 = threadIdx.x * RUN;
+    uint32_t c[RUN];
+    Cnt3 s = {0, 0, 0}, tot;
 #pragma unroll
-    for (int r = 0; r < SRC_PB / WG; ++r) {
-        if (key[r] < 0) continue;
-        const uint32_t i = b0 + (uint32_t)(r * WG) + threadIdx.x;
-        d.order[cnt[key[r]] + atomicAdd(&rank[key[r]], 1u)] = i;
+    for (int r = 0; r < RUN; ++r) {
+        c[r] = t0 + r < nbk ? d.ftot[t0 + r] : 0u;
+        s.a += c[r];
+    }
+    Cnt3 p = plan_scan(s, sw, &tot);
+#pragma unroll
+    for (int r = 0; r < RUN; ++r) {
+        if (t0 + r < nbk) d.ftot[t0 + r] = p.a;
+        p.a += c[r];
+    }
+    if (threadIdx.x == 0) d.ftot[nbk] = tot.a;
+}
+
+__global__ __launch_bounds__(FB_T) void k_cx_fscatter(KArgs a)
+{
+    __shared__ uint32_t map[CX_NTC_MAX];
+    __shared__ uint32_t cur[FB_MAX];
+    const CxDev &d = a.d;
+    const CxIn &in = a.in;
+    const uint32_t nbk = d.ctl->n_events;
+    const uint32_t rows = (in.n + FB_SRC - 1) / FB_SRC, row = faint_row(rows);
+    if (d.ctl->bad || row >= rows) return;
+    load_bucket_map(d, map);
+    for (uint32_t b = threadIdx.x; b < nbk; b += FB_T) cur[b] = d.ftot[b] + d.fmat[(size_t)row * nbk + b];
+    __syncthreads();
+    const uint32_t b0 = row * (uint32_t)FB_SRC;
+    constexpr int U = 4;
+    for (int r0 = 0; r0 < FB_SRC / FB_T; r0 += U) {
+        uint32_t key[U];
+        float A[U], f[U], fd[U], pa[U], pe[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const uint32_t i = b0 + (uint32_t)((r0 + q) * FB_T) + threadIdx.x, ic = min(i, in.n - 1u);
+            key[q] = d.key[ic];
+            A[q] = in.A[ic];
+            f[q] = in.F[ic];
+            fd[q] = in.FD[ic];
+            pa[q] = in.PA[ic];
+            pe[q] = in.PE[ic];
+            if (i >= in.n) key[q] = KEY_NONE;
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            if (key[q] == KEY_NONE || !(key[q] & KEY_FAINT)) continue;
+            const uint32_t p = atomicAdd(&cur[bucket_of(map, key[q])], 1u);
+            d.frec[p] = make_float4(A[q], f[q], fd[q], __uint_as_float((key[q] & ~KEY_FAINT) % CX_TILE));
+            d.fph[p] = make_float2(pa[q], pe[q]);
+        }
     }
 }
 
@@ -634,11 +948,340 @@ __device__ __forceinline__ SrcConsts bcast(const SrcConsts &c, int k)
     return r;
 }
 
-// Injection: h += every template (both channels), and the candidate cut
+// ---- the moment path
+//
+// The templates of all sources with the same centre bin share their bins,
+// and the DFT is linear: their samples are summed first and transformed
+// once per centre and channel.  The sum itself costs less than a sample per
+// source.  Around mid-observation (z = 2x - 1) a source's samples are
+// w exp(i (a z + b z^2)), a = pi (delta + d/2), |a| <= pi/2 (delta + d/2 is
+// the distance of the mid-frequency from its bin), b = pi d/4, |b| <= 1/4 by
+// the choice of the faint sources, w = (A/2)(T/128) exp(i (phi_c + 2 pi
+// (delta/2 + d/8))).  The Taylor coefficients G_k i^k in z follow
+//   G_0 = w, G_1 = a w, G_{k+1} = (a G_k - 2 i b G_{k-1}) / (k + 1),
+// and NMOM = 28 of them give the exponential on |z| <= 1 to 2e-15 at the
+// worst (|a| = pi/2 and |b| = 1/4; 2e-17 for |b| <= 0.14).  So a source costs
+// 28 short steps in one lane, where its template took the whole wave ~240
+// instructions.  The sums over a centre's sources are the samples' polynomial.
+//
+// The coefficients are summed as integers (unit 2^-E7, E7 from the largest
+// amplitude: every coefficient stays below 2^50, and centres with more than
+// 4096 sources take a coarser unit so that no sum leaves 64 bits): the sum
+// does not depend on the order of a centre's sources, which the grouping
+// leaves open.  With catalogs of at least 2^16 sources the unit is finer than
+// h's own rounding of every single template was (2^-E with E <= 45 - ilogb(A
+// T/2); here 2^-48), and h is rounded once per centre.
+//
+// Only sources that can never be candidates are taken, so none is ever
+// subtracted: h stays the same integer whatever subset of the candidates is
+// left.
+
+// Unit of a centre's coefficients.
+__device__ __forceinline__ int moment_exp(uint32_t amax_bits, uint32_t cnt, double T)
+{
+    const double v = (double)__uint_as_float(amax_bits) * (T * 0.5);
+    if (!(v > 0.0)) return 0;
+    return 55 - ilogb(v) - (cnt > 4096u ? 20 - __clz((int)cnt) : 0);
+}
+
+// u64 lane exchanges as for doubles above.
+template <int SPAN> __device__ __forceinline__ uint64_t swap_add(uint64_t p, uint64_t q)
+{
+    double P = __longlong_as_double((long long)p), Q = __longlong_as_double((long long)q);
+    row_swap<SPAN>(&P, &Q);
+    return (uint64_t)__double_as_longlong(P) + (uint64_t)__double_as_longlong(Q);
+}
+
+template <int PAT> __device__ __forceinline__ uint64_t fold_add(uint64_t lo, uint64_t hi, bool up)
+{
+    const uint64_t keep = up ? hi : lo, send = up ? lo : hi;
+    return keep + (uint64_t)__double_as_longlong(partner<PAT>(__longlong_as_double((long long)send)));
+}
+
+// exp(i phi): phases of a few turns through the table (phi/(2 pi) as the
+// rounded product plus its error), others by the library's reduction.
+__device__ __forceinline__ double2 phase_factor(float phi, const double2 *ex)
+{
+    if (__builtin_expect(fabsf(phi) <= 8.0f, 1)) {
+        const double p = (double)phi, t = p * 0.15915494309189535;
+        const double e = fma(p, 0.15915494309189535, -t) - p * 9.839338337591009e-18;
+        return cis_turns(t + e, ex);
+    }
+    double sp, cp;
+    sincos((double)phi, &sp, &cp);
+    return make_double2(cp, sp);
+}
+
+// Integer sums of the coefficients of channel ch over the sources order[o],
+// o = o0 + lane, o0 + lane + step, ... < o1: lane 2k gets Re G_k, lane 2k + 1
+// Im G_k (wrapping 64-bit sums; lanes past 2 NMOM get 0).  A value is rounded
+// to its unit by adding 1.5 2^52 and its bits are added as they are; the
+// constant part of the bits leaves at the end.
+__device__ __forceinline__ uint64_t moment_sums(const KArgs &a, uint32_t o0, uint32_t o1, uint32_t step, int ch,
+                                                int E7, const double2 *ex)
+{
+    const CxDev &d = a.d;
+    const double T = a.g.T, scale = ldexp(T / NF * 0.5, E7);
+    const float *PH = reinterpret_cast<const float *>(d.fph) + ch;
+    uint64_t sr[NMOM], si[NMOM];
+#pragma unroll
+    for (int k = 0; k < NMOM; ++k) sr[k] = si[k] = 0;
+    uint32_t turns = 0;
+    // the next turn's record is loaded while this one's coefficients are
+    // summed, and its place in the order one turn before that
+    const uint32_t last = o1 - 1u, l = (uint32_t)lane();
+    uint32_t p = 0, pn = 0;
+    float4 rec = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    float ph = 0.0f;
+    if (o0 < o1) {
+        p = d.forder[min(o0 + l, last)];
+        pn = d.forder[min(o0 + step + l, last)];
+        rec = d.frec[p];
+        ph = PH[2 * (size_t)p];
+    }
+    for (uint32_t o = o0; o < o1; o += step, ++turns) {
+        const bool in = o + l < o1;
+        const float4 cr = rec;
+        const float cph = ph;
+        rec = d.frec[pn];
+        ph = PH[2 * (size_t)pn];
+        pn = d.forder[min(o + 2u * step + l, last)];
+        double qd, delta, dd;
+        cx_centre((double)cr.y, (double)cr.z, T, &qd, &delta, &dd);
+        const double al = 3.141592653589793 * (delta + 0.5 * dd);
+        const double be2 = 1.5707963267948966 * dd;                       // 2b = pi d / 2
+        // w = (A/2)(T/128) 2^E7 exp(i (phi + 2 pi (delta/2 + d/8)))
+        const double sc = in ? (double)cr.x * scale : 0.0;
+        double2 r = cis_turns(0.5 * delta + 0.125 * dd, ex);
+        r = cmulf(r, phase_factor(cph, ex));
+        r = make_double2(sc * r.x, sc * r.y);
+        double gr = r.x, gi = r.y, hr = 0.0, hi = 0.0;                    // G_k, G_{k-1}
+#pragma unroll
+        for (int k = 0; k < NMOM; ++k) {
+            sr[k] += (uint64_t)__double_as_longlong(gr + 6755399441055744.0);
+            si[k] += (uint64_t)__double_as_longlong(gi + 6755399441055744.0);
+            if (k + 1 < NMOM) {
+                const double ak = al * (1.0 / (k + 1)), bk = be2 * (1.0 / (k + 1));
+                const double nr = fma(ak, gr, bk * hi), ni = fma(ak, gi, -(bk * hr));
+                hr = gr;
+                hi = gi;
+                gr = nr;
+                gi = ni;
+            }
+        }
+    }
+    // lane l ends with the sum of value l: halves of the values change
+    // places with halves of the wave, then of the rows, and so on
+    static_assert(NMOM == 28, "56 values: the folds below");
+    uint64_t v[32];
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+        const int m = j + 32;                                             // values 56 .. 63 are zero
+        v[j] = swap_add<32>(j & 1 ? si[j / 2] : sr[j / 2], m < 2 * NMOM ? (j & 1 ? si[m / 2] : sr[m / 2]) : 0ull);
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) v[j] = swap_add<16>(v[j], v[j + 16]);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = fold_add<8>(v[j], v[j + 8], l & 8);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = fold_add<7>(v[j], v[j + 4], l & 4);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) v[j] = fold_add<2>(v[j], v[j + 2], l & 2);
+    const uint64_t s = fold_add<1>(v[0], v[1], l & 1);
+    return l < 2u * NMOM ? s - (uint64_t)turns * 64ull * 0x4338000000000000ull : 0ull;
+}
+
+// One block per bucket: the bucket's sources are ordered by centre (LDS
+// counts; centres with fewer than MOM_MIN sources last, their sources take
+// one template each), then every (centre, channel) is a wave's task: moment
+// sums, the polynomial at the wave's 128 sample times (Horner, the
+// coefficients broadcast by readlane), one FFT, and the values into the
+// window.  A centre of more than MOM_COOP sources is shared by the block's
+// waves.
+// Bound by VALU issue and the dependent steps of a task (two waves per SIMD:
+// 56 sums of 64 bits per lane).  1e7 sources on the 4-yr grid: 680 us for the
+// 9.4e6 faint ones, plus 380 us of grouping and 300 us for the others'
+// templates, against 6500 us (and 110 us of grouping) with one template per
+// source.  MOM_MIN: a centre's sums cost about 2600 wave instructions for both
+// channels (folds, Horner, FFT, rounding), a template 240.
+__global__ __launch_bounds__(WG, 2) void k_cx_faint(KArgs a)
+{
+    constexpr int NW = WG / 64;
+    __shared__ long long acc[4][2][CXW / 2];
+    __shared__ uint32_t cnt[CX_TILE], beg[CX_TILE];
+    __shared__ double2 ex[NEX];
+    __shared__ double lf[LFW][64];
+    __shared__ unsigned long long msum[2][64];
+    __shared__ uint64_t sw[NW];
+    const Grid &g = a.g;
+    const CxDev &d = a.d;
+    const uint32_t b = blockIdx.x;
+    if (d.ctl->bad || b >= d.ctl->n_events) return;
+    const uint32_t m0 = d.ftot[b], m1 = d.ftot[b + 1];
+    if (m0 == m1) return;
+    int lo = 0, hi = d.ntc - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (d.fbb[mid] <= b) lo = mid; else hi = mid - 1;
+    }
+    const int tile = lo;
+    const int width = CX_TILE / (int)(d.fbb[tile + 1] - d.fbb[tile]);
+    const int c0 = tile * CX_TILE + (int)(b - d.fbb[tile]) * width;       // the bucket's first centre
+    const int nwin = width + NF, w0 = c0 - HALO;
+    for (int k = threadIdx.x; k < 4 * CXW; k += WG) (&acc[0][0][0])[k] = 0;
+    for (int k = threadIdx.x; k < width; k += WG) cnt[k] = 0;
+    if (threadIdx.x < 128) (&msum[0][0])[threadIdx.x] = 0;
+    set_cis_table(ex);
+    if (threadIdx.x < 64) keep_fft(lane_fft(), lf);
+    auto centre = [&](uint32_t p) { return (int)__float_as_uint(d.frec[p].w) & (width - 1); };
+    __syncthreads();
+    for (uint32_t p = m0 + threadIdx.x; p < m1; p += WG) atomicAdd(&cnt[centre(p)], 1u);
+    __syncthreads();
+    // offsets: the centres of at least MOM_MIN sources in order, then the others
+    uint32_t nbig;
+    {
+        constexpr int R = CX_TILE / WG;
+        uint64_t own = 0;
+        for (int r = 0; r < R; ++r) {
+            const int c = (int)threadIdx.x * R + r;
+            const uint64_t x = c < width ? cnt[c] : 0u;
+            own += x >= (uint64_t)MOM_MIN ? x << 32 : x;
+        }
+        uint64_t inc = own;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint64_t y = (uint64_t)__shfl_up((long long)inc, o, 64);
+            if (lane() >= o) inc += y;
+        }
+        if (lane() == 63) sw[threadIdx.x >> 6] = inc;
+        __syncthreads();
+        uint64_t run = inc - own, tot = 0;
+        for (int v = 0; v < NW; ++v) {
+            run += v < (int)(threadIdx.x >> 6) ? sw[v] : 0ull;
+            tot += sw[v];
+        }
+        nbig = (uint32_t)(tot >> 32);
+        for (int r = 0; r < R; ++r) {
+            const int c = (int)threadIdx.x * R + r;
+            if (c >= width) break;
+            const uint64_t x = cnt[c];
+            const bool big = x >= (uint64_t)MOM_MIN;
+            beg[c] = big ? (uint32_t)(run >> 32) : nbig + (uint32_t)run;
+            run += big ? x << 32 : x;
+        }
+        __syncthreads();
+    }
+    for (uint32_t p = m0 + threadIdx.x; p < m1; p += WG)
+        d.forder[m0 + atomicAdd(&beg[centre(p)], 1u)] = p;
+    __syncthreads();                                  // beg: now the end of each centre's range
+
+    const int E = cx_exp(d.ctl->amax_bits, a.in.n, g.T);
+    const uint32_t amax = d.ctl->amax_bits;
+    const int wave = (int)(threadIdx.x >> 6);
+    int je, jo;
+    lane_offsets(&je, &jo);
+    auto put = [&](int bin, int word, long long v) {
+        atomicAdd((unsigned long long *)&acc[word][(bin - w0) & 1][(bin - w0) >> 1], (unsigned long long)v);
+    };
+    // the transform of a centre's sums of channel ch (lane 2k: Re G_k, 2k + 1: Im G_k)
+    auto transform = [&](uint64_t sum, int c, int ch, int E7) {
+        const double v = ldexp((double)(long long)sum, E - E7);
+        const LaneFft L = kept_fft(lf);
+        const double z0 = 2.0 * L.x0 - 1.0, z1 = 2.0 * L.x1 - 1.0;
+        double2 p0 = make_double2(0.0, 0.0), p1 = p0;
+#pragma unroll
+        for (int k = NMOM - 1; k >= 0; --k) {
+            const double mr = rl(v, 2 * k), mi = rl(v, 2 * k + 1);
+            const double cx = k % 4 == 0 ? mr : k % 4 == 1 ? -mi : k % 4 == 2 ? -mr : mi;     // i^k G_k
+            const double cy = k % 4 == 0 ? mi : k % 4 == 1 ? mr : k % 4 == 2 ? -mi : -mr;
+            p0 = make_double2(fma(p0.x, z0, cx), fma(p0.y, z0, cy));
+            p1 = make_double2(fma(p1.x, z1, cx), fma(p1.y, z1, cy));
+        }
+        double2 ue, uo;
+        wave_fft(p0, p1, L, &ue, &uo);
+        put(c0 + c + je, 2 * ch, __double2ll_rn(ue.x));
+        put(c0 + c + je, 2 * ch + 1, __double2ll_rn(ue.y));
+        put(c0 + c + jo, 2 * ch, __double2ll_rn(uo.x));
+        put(c0 + c + jo, 2 * ch + 1, __double2ll_rn(uo.y));
+    };
+    for (int t = wave; t < 2 * width; t += NW) {
+        const int c = t >> 1, ch = t & 1;
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)cnt[c]);
+        if (n < (uint32_t)MOM_MIN || n > (uint32_t)MOM_COOP) continue;
+        const uint32_t e = m0 + (uint32_t)__builtin_amdgcn_readfirstlane((int)beg[c]);
+        const int E7 = moment_exp(amax, n, g.T);
+        transform(moment_sums(a, e - n, e, 64u, ch, E7, ex), c, ch, E7);
+    }
+    if (m1 - m0 > (uint32_t)MOM_COOP) {               // block-uniform
+        for (int c = 0; c < width; ++c) {
+            const uint32_t n = cnt[c];
+            if (n <= (uint32_t)MOM_COOP) continue;
+            const uint32_t e = m0 + beg[c];
+            const int ch = wave & 1, E7 = moment_exp(amax, n, g.T);
+            const uint64_t s = moment_sums(a, e - n + 64u * (uint32_t)(wave >> 1), e, 64u * (NW / 2), ch, E7, ex);
+            atomicAdd(&msum[ch][lane()], (unsigned long long)s);
+            __syncthreads();
+            if (wave < 2) {
+                transform(msum[wave][lane()], c, wave, E7);
+                msum[wave][lane()] = 0;
+            }
+            __syncthreads();
+        }
+    }
+    // the others: one template each
+    const uint32_t s0 = m0 + nbig, share = (m1 - s0 + NW - 1) / NW;
+    const uint32_t v0 = min(s0 + (uint32_t)wave * share, m1), v1 = min(v0 + share, m1);
+    const LaneFft L = kept_fft(lf);
+    for (uint32_t base = v0; base < v1; base += 64u) {
+        const uint32_t p = d.forder[min(base + (uint32_t)lane(), v1 - 1u)];
+        SrcConsts mine{};
+        double dd;
+        const float4 rec = d.frec[p];
+        const float2 ph = d.fph[p];
+        mine.qb = centre_bin(g, rec.y, rec.z, &mine.delta, &dd);
+        mine.dh = dd * 0.5;
+        mine.sc = ldexp(((double)rec.x * 0.5) * (g.T / NF), E);
+        const double2 ra = phase_factor(ph.x, ex), re = phase_factor(ph.y, ex);
+        mine.ca = ra.x;
+        mine.sa = ra.y;
+        mine.ce = re.x;
+        mine.se = re.y;
+        const int n = (int)min(64u, v1 - base);
+        for (int k = 0; k < n; ++k) {
+            const SrcConsts c = bcast(mine, k);
+            double2 ue, uo;
+            wave_template(c, L, ex, &ue, &uo);
+            const double2 ae = rot(ue, c.ca, c.sa), ee = rot(ue, c.ce, c.se);
+            const double2 ao = rot(uo, c.ca, c.sa), eo = rot(uo, c.ce, c.se);
+            put(c.qb + je, 0, fxm(ae.x));
+            put(c.qb + je, 1, fxm(ae.y));
+            put(c.qb + je, 2, fxm(ee.x));
+            put(c.qb + je, 3, fxm(ee.y));
+            put(c.qb + jo, 0, fxm(ao.x));
+            put(c.qb + jo, 1, fxm(ao.y));
+            put(c.qb + jo, 2, fxm(eo.x));
+            put(c.qb + jo, 3, fxm(eo.y));
+        }
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < nwin; k += WG) {
+        const int bin = w0 + k;
+        if (bin < 0 || bin >= g.B) continue;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const long long v = acc[c][k & 1][k >> 1];
+            if (v) atomicAdd((unsigned long long *)&d.h[(size_t)c * g.B + bin], (unsigned long long)v);
+        }
+    }
+}
+
+// Direct injection: h += every template of the sources the moment path does
+// not take (both channels), and the candidate cut
 // rho_0^2 = (8/T) sum_j |U_j|^2 / S_instr >= (kappa rho_th)^2.  One block per
-// chunk of at most CH sources of one binning tile; each wave takes 64
+// chunk of sources of one binning tile (k_cx_plan); each wave takes 64
 // sources at a time, their constants computed one per lane, then one
-// template after the other by the whole wave.
+// template after the other by the whole wave.  The batch's candidates are
+// recorded together: lane k keeps rho_0^2 of source k, one reservation for
+// all (one same-address atomic per batch instead of one per candidate).
 __global__ __launch_bounds__(WG) void k_cx_inject(KArgs a)
 {
     // per channel word, the window's even bins then its odd bins (w0 is
@@ -657,8 +1300,9 @@ __global__ __launch_bounds__(WG) void k_cx_inject(KArgs a)
         if (d.cbase[mid] <= b) lo = mid; else hi = mid - 1;
     }
     const int tile = lo;
-    const uint32_t s0 = d.tcnt[tile] + (b - d.cbase[tile]) * (uint32_t)CH;
-    const uint32_t s1 = min(s0 + (uint32_t)CH, d.tcnt[tile + 1]);
+    const uint32_t chunk = d.ctl->n_chunks;
+    const uint32_t s0 = d.tcnt[tile] + (b - d.cbase[tile]) * chunk;
+    const uint32_t s1 = min(s0 + chunk, d.tcnt[tile + 1]);
     for (int k = threadIdx.x; k < 4 * CXW; k += WG) (&acc[0][0][0])[k] = 0;
     set_cis_table(ex);
     const LaneFft L = lane_fft();
@@ -677,29 +1321,19 @@ __global__ __launch_bounds__(WG) void k_cx_inject(KArgs a)
         const uint32_t s = base + (uint32_t)lane();
         SrcConsts mine = src_consts(g, in, d.order[s < v1 ? s : v0], E, true);
         {
-            // the candidate cut: sum_j |U_j|^2 = T^2 A^2 / 4 (Parseval), so
-            // rho_0^2 <= 2 T A^2 max 1/S_instr over the template's (at most
-            // two) segments; below the cut by that bound, no exact sum
-            const double A = (double)in.A[mine.i];
-            const int g0 = max(mine.qb - HALO, 0) / NF, g1 = min(mine.qb + HALO - 1, g.B - 1) / NF;
-            const double bound = 2.0 * T * (A * A) * fmax(d.isx_max[g0], d.isx_max[g1]);
-            mine.need = bound * (1.0 + 1e-9) >= cut2;
+            // below the candidate cut by the bound: no exact sum
+            mine.need = lone_bound(g, d.isx_max, (double)in.A[mine.i], mine.qb) >= cut2;
         }
+        double myr0 = -1.0;                      // rho_0^2 of this lane's source (none: below the cut)
         // the candidate cut and the template's values into the window
-        auto add = [&](const SrcConsts &c, const double2 &ue, const double2 &uo) {
+        auto add = [&](const SrcConsts &c, int k, const double2 &ue, const double2 &uo) {
             const int be = c.qb + je, bo = c.qb + jo;
             const bool ine = be >= 0 && be < g.B, ino = bo >= 0 && bo < g.B;
             if (c.need) {
                 const double pe = ue.x * ue.x + ue.y * ue.y, po = uo.x * uo.x + uo.y * uo.y;
                 double r = (ine ? pe * d.isx[be] : 0.0) + (ino ? po * d.isx[bo] : 0.0);
                 const double r0 = r0s * wave_sum(r);
-                if (r0 >= cut2 && lane() == 0) {
-                    const uint32_t slot = atomicAdd(&d.ctl->cand_cursor, 1u);
-                    d.c_src[slot] = c.i;
-                    d.c_iter[slot] = -1;
-                    d.c_rho2[slot] = r0;
-                    d.c_qb[slot] = c.qb;
-                }
+                if (lane() == k) myr0 = r0;
             }
             if (ine) {
                 const double2 va = rot(ue, c.ca, c.sa), ve = rot(ue, c.ce, c.se);
@@ -723,7 +1357,21 @@ __global__ __launch_bounds__(WG) void k_cx_inject(KArgs a)
             const SrcConsts c = bcast(mine, k);
             double2 ue, uo;
             wave_template(c, L, ex, &ue, &uo);
-            add(c, ue, uo);
+            add(c, k, ue, uo);
+        }
+        const bool cand = lane() < cnt && mine.need && myr0 >= cut2;
+        const uint64_t m = (uint64_t)__ballot(cand);
+        if (m) {
+            uint32_t slot = 0;
+            if (lane() == 0) slot = atomicAdd(&d.ctl->cand_cursor, (uint32_t)__popcll(m));
+            slot = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot);
+            if (cand) {
+                slot += (uint32_t)__popcll(m & ((1ull << lane()) - 1ull));
+                d.c_src[slot] = mine.i;
+                d.c_iter[slot] = -1;
+                d.c_rho2[slot] = myr0;
+                d.c_qb[slot] = mine.qb;
+            }
         }
     }
     __syncthreads();
@@ -1042,10 +1690,22 @@ uint64_t cx_carve(const Grid &g, uint64_t n, char *base, CxDev *out)
     d.c_rho2 = (double *)take(nn * 8);
     d.c_qb = (int32_t *)take(nn * 4);
     d.rs_hist = (uint32_t *)take(resolved_scratch_words(nn) * 4);
-    d.kA = (uint32_t *)take(nn * 4);
-    d.vA = (int32_t *)take(nn * 4);
-    d.kB = (uint32_t *)take(nn * 4);
-    d.vB = (int32_t *)take(nn * 4);
+    d.kA = (uint32_t *)take(nn * 16);
+    d.vA = (int32_t *)(d.kA + nn);
+    d.kB = d.kA + 2 * nn;
+    d.vB = (int32_t *)(d.kA + 3 * nn);
+    const bool faint = n >= FAINT_MIN_N;
+    d.fcnt = (uint32_t *)take(((uint64_t)d.ntc + 1) * 4);
+    d.fbb = (uint32_t *)take(((uint64_t)d.ntc + 1) * 4);
+    d.ftot = (uint32_t *)take(faint ? (FB_MAX + 1) * 4 : 0);
+    d.fmat = (uint32_t *)take(faint ? ((n + FB_SRC - 1) / FB_SRC) * (uint64_t)FB_MAX * 4 : 0);
+    // binning scratch in memory that is written only later: the candidate
+    // records by the direct injection (after the moment path has ended), the
+    // ids and the resolved-list buffers after the run
+    d.key = d.c_src;
+    d.frec = (float4 *)d.kA;
+    d.fph = (float2 *)d.c_rho2;
+    d.forder = d.c_id;
     if (out) *out = d;
     return off;
 }
@@ -1060,9 +1720,18 @@ hipError_t cx_launch_prep(const Grid &g, const CxDev &d, const CxIn &in, hipStre
     const uint32_t nb = (in.n + SRC_PB - 1) / SRC_PB;
     if (nb) k_cx_count<<<nb, WG, 0, st>>>(a);
     k_cx_plan<<<1, PLAN_T, 0, st>>>(a);
-    if (nb) k_cx_scatter<<<nb, WG, 0, st>>>(a);
-    // chunks: at most one partial chunk per tile beyond n / CH full ones
-    const uint32_t chunks = in.n / CH + (uint32_t)d.ntc;
+    const uint32_t fb = (in.n + FB_SRC - 1) / FB_SRC;
+    if (nb) k_cx_scatter<<<fb, FB_T, 0, st>>>(a);
+    if (in.n >= FAINT_MIN_N) {
+        k_cx_fcount<<<fb, FB_T, 0, st>>>(a);
+        k_cx_fcols<<<FB_MAX / 64, FB_T, 0, st>>>(a);
+        k_cx_fscan<<<1, PLAN_T, 0, st>>>(a);
+        k_cx_fscatter<<<(fb + 7) / 8 * 8, FB_T, 0, st>>>(a);
+        k_cx_faint<<<FB_MAX, WG, 0, st>>>(a);
+    }
+    // chunks: at most one partial chunk per tile beyond the full ones (the
+    // chunk is CH, or at least a CH_GRID'th of the direct sources)
+    const uint32_t chunks = max(in.n / CH, (uint32_t)CH_GRID) + (uint32_t)d.ntc;
     if (in.n) k_cx_inject<<<chunks, WG, 0, st>>>(a);
     return hipGetLastError();
 }

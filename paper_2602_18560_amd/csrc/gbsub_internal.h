@@ -262,6 +262,16 @@ struct CxDev {
     uint32_t *rs_hist;       // resolved-list scratch
     uint32_t *kA, *kB;       // [n] each: resolved-list keys
     int32_t *vA, *vB;        // [n] each: resolved-list values
+    // binning of the injection (catalogs of 2^16 sources or more: the faint
+    // sources by bucket, a range of centres inside a tile)
+    uint32_t *key;           // [n] centre bin, and whether the moment path takes the source
+    uint32_t *fcnt;          // [ntc+1] faint sources per binning tile
+    uint32_t *fbb;           // [ntc+1] first faint bucket of each tile
+    uint32_t *ftot;          // [buckets+1] faint sources per bucket, then their exclusive prefix
+    uint32_t *fmat;          // [blocks][buckets] faint sources per (block, bucket), then the blocks before
+    float4 *frec;            // [n] the faint sources' records by bucket: A, f, fdot, centre inside the tile
+    float2 *fph;             // [n] their phases
+    uint32_t *forder;        // [n] their records by centre inside each bucket
     int32_t ntc;             // binning tiles
     int32_t pad;
 };
