@@ -191,8 +191,8 @@ gbsub_status gbsub_spectrum(const gbsub_ctx *ctx, uint32_t kind, double *out, ui
  * appendix "Subtraction algorithm" takes out of the data, step 9, with the
  * loop body of each): ids[j] (uint32) in ascending id order, and iter_of[j]
  * (int32, may be NULL) = the loop body t in which ids[j] was subtracted.
- * Built on the device (compaction of the candidate records, radix sort by
- * id) in the run's workspace; the run's spectra are untouched.  Host pointers if out_on_device == 0,
+ * Built on the device (compaction of the candidate records, sort by id) in
+ * the run's workspace; the run's spectra are untouched.  Host pointers if out_on_device == 0,
  * device pointers otherwise.  *n (host) receives the count; TRUNCATED if
  * cap is smaller.  STATE if no run has completed. */
 gbsub_status gbsub_resolved(const gbsub_ctx *ctx, uint32_t *ids, int32_t *iter_of, uint64_t cap,

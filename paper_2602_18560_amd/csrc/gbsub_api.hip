@@ -36,6 +36,7 @@ struct gbsub_ctx {
     void *ws;
     gbsub_summary summ;
     uint32_t n_cand;
+    uint64_t res_n;    // its sources (the resolved list's capacity)
     // the S_instr tables in `tables_ws` were computed for this grid
     void *tables_ws;
     Ctl *host_ctl;     // pinned
@@ -325,6 +326,35 @@ gbsub_summary summary_of(const Grid &g, const Ctl &h)
     return s;
 }
 
+// Whether p is memory of device `dev` that its kernels can write.
+bool on_device(const void *p, int dev)
+{
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == dev;
+}
+
+// The resolved list of a run to the caller's arrays: written by the last
+// kernel where they are memory of the run's device, else through sc_ids and
+// sc_bodies (m entries each, in the workspace).  `list`: as launch_resolved.
+gbsub_status write_resolved(int dev, const int32_t *iter, const uint32_t *id, uint32_t nc, uint32_t m, uint32_t *hist,
+                            uint64_t *list, uint64_t n_max, uint32_t *sc_ids, int32_t *sc_bodies, uint32_t *ids,
+                            int32_t *bodies, bool out_on_device)
+{
+    if (hipSetDevice(dev) != hipSuccess) return GBSUB_E_DEVICE;
+    const bool direct = out_on_device && on_device(ids, dev) && (!bodies || on_device(bodies, dev));
+    hipError_t e = launch_resolved(iter, id, nc, m, hist, list, n_max, direct ? ids : sc_ids,
+                                   direct || !bodies ? bodies : sc_bodies, nullptr);
+    if (direct) return dev_err(e == hipSuccess ? hipStreamSynchronize(nullptr) : e);
+    const hipMemcpyKind kd = out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
+    if (e == hipSuccess) e = hipMemcpy(ids, sc_ids, (size_t)m * 4, kd);
+    if (e == hipSuccess && bodies) e = hipMemcpy(bodies, sc_bodies, (size_t)m * 4, kd);
+    return dev_err(e);
+}
+
 }  // namespace
 
 // Workspace of gbsub_run_static, for callers that cannot allocate device
@@ -417,6 +447,7 @@ gbsub_status gbsub_create(const gbsub_config *cfg, gbsub_ctx **out)
     c->batch_slot = -1;
     c->cx_have_result = false;
     c->cx_n = 0;
+    c->res_n = 0;
     c->host_cx_slots = nullptr;
     c->profiling = 0;
     c->ev_used = 0;
@@ -591,6 +622,7 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
     c->dev = d;
     c->ws = ws;
     c->n_cand = h.n_cand;
+    c->res_n = cat->n;
     c->have_result = true;
     return GBSUB_OK;
 }
@@ -702,19 +734,13 @@ gbsub_status gbsub_resolved(const gbsub_ctx *c, uint32_t *ids, int32_t *iter_of,
     if (cap < m) return GBSUB_E_TRUNCATED;
     if (m == 0) return GBSUB_OK;
     if (!ids) return GBSUB_E_INVALID;
-    if (hipSetDevice(c->device) != hipSuccess) return GBSUB_E_DEVICE;
-    // compaction and sort on the device, in the workspace's event buffer
-    // (free once the binning is done: 16 bytes per source, m <= sources)
+    // after the binning the event buffers are free: the list and its scratch
+    // in the values, the output of a host copy in the keys
     const Dev &d = c->dev;
-    uint32_t *kA = reinterpret_cast<uint32_t *>(d.ev_val);
-    int32_t *vA = reinterpret_cast<int32_t *>(kA + m);
-    uint32_t *kB = reinterpret_cast<uint32_t *>(vA + m);
-    int32_t *vB = reinterpret_cast<int32_t *>(kB + m);
-    hipError_t e = launch_resolved(d.c_iter, d.c_id, c->n_cand, (uint32_t)m, d.rs_hist, kA, vA, kB, vB, nullptr);
-    const hipMemcpyKind kd = out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    if (e == hipSuccess) e = hipMemcpy(ids, kA, m * 4, kd);
-    if (e == hipSuccess && iter_of) e = hipMemcpy(iter_of, vA, m * 4, kd);
-    return dev_err(e);
+    uint32_t *out_ids = d.ev_key;
+    return write_resolved(c->device, d.c_iter, d.c_id, c->n_cand, (uint32_t)m, d.rs_hist,
+                          reinterpret_cast<uint64_t *>(d.ev_val), c->res_n, out_ids,
+                          reinterpret_cast<int32_t *>(out_ids + m), ids, iter_of, out_on_device != 0);
 }
 
 gbsub_status gbsub_candidates(const gbsub_ctx *c, uint32_t *ids, int32_t *iter_of, double *rho2,
@@ -934,14 +960,11 @@ gbsub_status gbsub_cx_resolved(const gbsub_ctx *c, uint32_t *ids, int32_t *iter_
     if (cap < m) return GBSUB_E_TRUNCATED;
     if (m == 0) return GBSUB_OK;
     if (!ids) return GBSUB_E_INVALID;
-    if (hipSetDevice(c->device) != hipSuccess) return GBSUB_E_DEVICE;
+    // the output of a host copy in the injection order and the candidates'
+    // centre bins, free after the run
     const CxDev &d = c->cx;
-    hipError_t e = launch_resolved(d.c_iter, d.c_id, (uint32_t)c->cx_summ.n_candidates, (uint32_t)m, d.rs_hist, d.kA,
-                                   d.vA, d.kB, d.vB, nullptr);
-    const hipMemcpyKind kd = out_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    if (e == hipSuccess) e = hipMemcpy(ids, d.kA, m * 4, kd);
-    if (e == hipSuccess && iter_of) e = hipMemcpy(iter_of, d.vA, m * 4, kd);
-    return dev_err(e);
+    return write_resolved(c->device, d.c_iter, d.c_id, (uint32_t)c->cx_summ.n_candidates, (uint32_t)m, d.rs_hist,
+                          d.rlist, c->cx_n, d.order, d.c_qb, ids, iter_of, out_on_device != 0);
 }
 
 gbsub_status gbsub_cx_candidates(const gbsub_ctx *c, uint32_t *ids, int32_t *iter_of, double *rho2, uint64_t cap,
@@ -1301,6 +1324,7 @@ gbsub_status gbsub_batch_retire(gbsub_batch *b, uint32_t k, void *stream, gbsub_
     c->dev = sl.d;
     c->ws = const_cast<void *>(wsk);
     c->n_cand = h.n_cand;
+    c->res_n = sl.n;
     c->have_result = true;
     return GBSUB_OK;
 }

@@ -474,6 +474,7 @@ __global__ __launch_bounds__(WG) void k_cx_reset(KArgs a)
         c->xupd = 0;
         c->tail_due = 0;
         c->n_new_body = 0;
+        c->res_cursor = 0;
     }
 }
 
@@ -1604,9 +1605,8 @@ __global__ __launch_bounds__(WG) void k_cx_tail(KArgs a)
 __global__ __launch_bounds__(WG) void k_cx_ids(KArgs a)
 {
     const CxDev &d = a.d;
-    const uint32_t nc = d.ctl->cand_cursor;
-    for (uint32_t j = blockIdx.x * WG + threadIdx.x; j < nc; j += gridDim.x * WG)
-        d.c_id[j] = a.in.ids[d.c_src[j]];
+    list_resolved(d.ctl->cand_cursor, d.c_iter, d.c_id, d.rlist, &d.ctl->res_cursor,
+                  [&](uint32_t j) { return a.in.ids[d.c_src[j]]; });
 }
 
 __global__ __launch_bounds__(WG) void k_cx_hout(KArgs a, int ch, double *out)
@@ -1690,10 +1690,7 @@ uint64_t cx_carve(const Grid &g, uint64_t n, char *base, CxDev *out)
     d.c_rho2 = (double *)take(nn * 8);
     d.c_qb = (int32_t *)take(nn * 4);
     d.rs_hist = (uint32_t *)take(resolved_scratch_words(nn) * 4);
-    d.kA = (uint32_t *)take(nn * 16);
-    d.vA = (int32_t *)(d.kA + nn);
-    d.kB = d.kA + 2 * nn;
-    d.vB = (int32_t *)(d.kA + 3 * nn);
+    d.rlist = (uint64_t *)take(nn * 16);
     const bool faint = n >= FAINT_MIN_N;
     d.fcnt = (uint32_t *)take(((uint64_t)d.ntc + 1) * 4);
     d.fbb = (uint32_t *)take(((uint64_t)d.ntc + 1) * 4);
@@ -1703,7 +1700,7 @@ uint64_t cx_carve(const Grid &g, uint64_t n, char *base, CxDev *out)
     // records by the direct injection (after the moment path has ended), the
     // ids and the resolved-list buffers after the run
     d.key = d.c_src;
-    d.frec = (float4 *)d.kA;
+    d.frec = (float4 *)d.rlist;
     d.fph = (float2 *)d.c_rho2;
     d.forder = d.c_id;
     if (out) *out = d;

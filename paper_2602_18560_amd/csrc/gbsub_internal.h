@@ -74,6 +74,8 @@ struct Ctl {
     uint32_t tail_due;       // k_snr has run; its partials await the tail
     uint32_t n_new_body;     // complex-template model: sources subtracted by the running body
     uint32_t n_sdl;          // tiles listed in sdl for the next median launch
+    uint32_t res_cursor;     // entries of the resolved list handed out (list_resolved)
+    uint32_t pad;
 };
 
 // Per-block partial results of k_snr (combined by the tail: the last block
@@ -158,7 +160,8 @@ struct Dev {
     uint32_t *chunk_base;    // [nt+1]
     uint32_t *slot_base;     // [nt]   partial-sum slots of tiles with several blocks
     uint32_t *ev_key;        // [2n]   bin | (1<<31 for difference events)
-    int64_t *ev_val;         // [2n]   signed fixed-point power
+    int64_t *ev_val;         // [2n]   signed fixed-point power (after the run: the resolved list
+                             //        of list_resolved, then its sort's scratch)
     I128 *partial;           // [slots][2][tile] partial sums of the hot tiles
     uint64_t *cbits;         // [ceil(n/64)] candidate flags of the sources (count pass)
     uint32_t *rs_hist;       // [resolved_scratch_words(n)] block counts of the resolved-list kernels
@@ -218,13 +221,14 @@ hipError_t launch_snr(const Slot *ds, const Dims &dm, hipStream_t st, hipEvent_t
                       hipEvent_t eb = nullptr);
 hipError_t launch_outputs(const Slot *ds, const Dims &dm, hipStream_t st);
 
-// Output kernels (gbsub_output.hip).  The resolved list: the (id, loop body)
-// pairs of the m candidates with iter >= 0 among nc, compacted and sorted by
-// id into kA / vA (kB / vB: the same sizes, scratch); `hist` holds
-// resolved_scratch_words(n) words for catalogs of up to n sources.
+// Output kernels (gbsub_output.hip).  The resolved list: the m candidates
+// with iter >= 0 among nc, by id, into the device arrays ids and (if not
+// null) bodies.  `list` holds 2 n_max words: list_resolved's m entries, then
+// scratch; `hist` holds resolved_scratch_words(n) words for catalogs of up to
+// n sources.
 uint64_t resolved_scratch_words(uint64_t n_max);
 hipError_t launch_resolved(const int32_t *iter, const uint32_t *id, uint32_t nc, uint32_t m, uint32_t *hist,
-                           uint32_t *kA, int32_t *vA, uint32_t *kB, int32_t *vB, hipStream_t st);
+                           uint64_t *list, uint64_t n_max, uint32_t *ids, int32_t *bodies, hipStream_t st);
 // out[k] = S[k] - sx[k] for k < B.
 hipError_t launch_sgal(const double *S, const double *sx, int B, double *out, hipStream_t st);
 // out[i] = the control block of slot i of the device table, i < n (one launch).
@@ -260,8 +264,7 @@ struct CxDev {
     double *c_rho2;          // [n] rho^2 at the last evaluation
     int32_t *c_qb;           // [n] its template's centre bin (the SNR pass's dirty-tile test)
     uint32_t *rs_hist;       // resolved-list scratch
-    uint32_t *kA, *kB;       // [n] each: resolved-list keys
-    int32_t *vA, *vB;        // [n] each: resolved-list values
+    uint64_t *rlist;         // [2n] the resolved list (list_resolved), then its sort's scratch
     // binning of the injection (catalogs of 2^16 sources or more: the faint
     // sources by bucket, a range of centres inside a tile)
     uint32_t *key;           // [n] centre bin, and whether the moment path takes the source

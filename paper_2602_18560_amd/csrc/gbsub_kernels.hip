@@ -425,6 +425,7 @@ __global__ __launch_bounds__(WG) void k_reset(const Slot *S)
         c->n_sdl = (uint32_t)g.nt;
         c->xupd = 0;
         c->tail_due = 0;
+        c->res_cursor = 0;
     }
     for (int i = blockIdx.x * WG + threadIdx.x; i < g.nt; i += gridDim.x * WG) {
         d.xstamp[i] = 0;          // body 0 converts and filters every tile
@@ -2413,16 +2414,16 @@ __global__ __launch_bounds__(SNR_BLOCKS) void k_snr_tail(const Slot *S)
 
 // ------------------------------------------------------------------ outputs
 
-// ids of the candidates (the catalog is not retained after the run).
+// ids of the candidates (the catalog is not retained after the run) and the
+// resolved list, unsorted.
 __global__ __launch_bounds__(WG) void k_cand_ids(const Slot *S)
 {
     const Slot &sl = S[blockIdx.y];
     if (!sl.active) return;
     const Dev d = sl.d;
     const uint32_t *ids = sl.ids;
-    const uint32_t nc = d.ctl->n_cand;
-    for (uint32_t j = blockIdx.x * WG + threadIdx.x; j < nc; j += gridDim.x * WG)
-        d.c_id[j] = ids[d.c_src[j]];
+    list_resolved(d.ctl->n_cand, d.c_iter, d.c_id, reinterpret_cast<uint64_t *>(d.ev_val), &d.ctl->res_cursor,
+                  [&](uint32_t j) { return ids[d.c_src[j]]; });
 }
 
 // ------------------------------------------------------------------ launchers
