@@ -82,9 +82,9 @@ struct Ctl {
 // of the next k_xupdate, or k_snr_tail in the naive FP32 mode).
 struct SnrPart {
     uint32_t n_new;          // sources subtracted
+    uint32_t near;           // evaluations within 1e-6 of the threshold
+    uint32_t evals;          // candidate evaluations
     uint32_t pad;
-    uint64_t near;           // evaluations within 1e-6 of the threshold
-    uint64_t evals;          // candidate evaluations
     double minm;             // min |rho/rho_th - 1|
 };
 

@@ -2117,15 +2117,14 @@ DEVI void subtract_track_comp(const Grid &g, const Dev &d, int glo, int ghi, flo
 // stamp t (every stamp is at most t + 1).  Tracks over more than SKIP_TILES
 // tiles count as changed without looking.
 constexpr int SKIP_TILES = 4;
-DEVI bool track_refiltered(const uint32_t *stamp, const Grid &g, int lo, int hi, uint32_t t)
+DEVI bool track_refiltered(const uint32_t *stamp, const Grid &g, int lo, int hi, uint32_t first, uint32_t last,
+                           uint32_t t)          // first, last: the stamps of the end tiles
 {
     const int a = div_p2(lo, g.tile), b = div_p2(hi, g.tile);
     if (b - a >= SKIP_TILES) return true;
-    bool r = false;
-    for (int tl = a; tl <= b; ++tl) {
-        const uint32_t s = stamp[tl];
-        r |= s == t || s == t + 1;
-    }
+    auto is = [&](uint32_t s) { return s == t || s == t + 1; };
+    bool r = is(first) || is(last);
+    for (int tl = a + 1; tl < b; ++tl) r |= is(stamp[tl]);
     return r;
 }
 
@@ -2142,7 +2141,7 @@ DEVI bool track_refiltered(const uint32_t *stamp, const Grid &g, int lo, int hi,
 __global__ __launch_bounds__(WG) void k_snr(const Slot *S)
 {
     constexpr int NW = WG / 64;
-    __shared__ uint64_t s_red[3][NW];     // new, near, evals
+    __shared__ uint32_t s_red[3][NW];     // new, near, evals
     __shared__ double s_min[NW];
     const Slot &sl = S[blockIdx.y];
     if (!sl.active) return;
@@ -2156,112 +2155,134 @@ __global__ __launch_bounds__(WG) void k_snr(const Slot *S)
     const bool comp = g.prec == PREC_COMP;
     const FF *psum_ff = reinterpret_cast<const FF *>(d.is_psum);
     const int lane = lane_id();
-    uint32_t my_new = 0;
-    uint64_t near = 0, evals = 0;
+    uint32_t my_new = 0, near = 0, evals = 0;         // at most one each per candidate
     double minm = INFINITY;
     // the wave walks its candidates together (uniform trip count), so that
     // all its lanes can sum the part sums under a wide track
     const uint32_t stride = gridDim.x * WG;
-    for (uint32_t jb = blockIdx.x * WG + (threadIdx.x & ~63u); jb < nc; jb += stride) {
-        const uint32_t j = jb + (uint32_t)lane;
-        const bool live = j < nc && d.c_iter[j] < 0;
-        int glo = 0, ghi = 0;
-        bool eval = false;
-        double r2 = 0.0;
-        if (live) {
-            glo = d.c_glo[j];
-            ghi = d.c_ghi[j];
-            eval = t == 0 || track_refiltered(d.sstamp, g, glo, ghi, (uint32_t)t);
-            if (!eval) r2 = d.c_rho2[j];
+    // SU candidates per thread at a time: their records, then the stamps under
+    // their tracks, then the evaluations.  In late bodies nearly every
+    // candidate stops at the stamps, and the launch is the latency of these
+    // two rounds of loads: 11.1 us a body on the 1e7 catalog, 11.9 with the
+    // loads one after the other
+    constexpr int SU = 2;
+    for (uint32_t jb0 = blockIdx.x * WG + (threadIdx.x & ~63u); jb0 < nc; jb0 += SU * stride) {
+        int it_[SU], lo_[SU], hi_[SU];
+        double r2_[SU];
+        uint32_t sa_[SU], sb_[SU];
+#pragma unroll
+        for (int u = 0; u < SU; ++u) {
+            const uint32_t j = min(jb0 + (uint32_t)u * stride + (uint32_t)lane, nc - 1u);
+            it_[u] = d.c_iter[j];
+            lo_[u] = d.c_glo[j];
+            hi_[u] = d.c_ghi[j];
+            r2_[u] = d.c_rho2[j];
         }
-        // sum of the part sums of 1/S over the parts strictly before the
-        // track's last part: a loop for tracks over a few parts, all lanes
-        // of the wave together for wider ones, one track at a time
-        const int plo = div_p2(glo, g.part), phi = div_p2(ghi, g.part);
-        const bool need = eval && ghi - glo + 1 > NARROW && phi > plo;
-        const bool wide = need && phi - plo > COOP_PARTS;
-        double mid = 0.0;
-        FF midc = ff_of(0.0f);
-        if (need && !wide) {
-            if (naive) {
-                float m = 0.0f;
-                for (int pp = plo; pp < phi; ++pp) m += (float)d.is_psum[pp];
-                mid = (double)m;
-            } else if (comp) {
-                for (int pp = plo; pp < phi; ++pp) midc = ff_add(midc, psum_ff[pp]);
-            } else {
-                for (int pp = plo; pp < phi; ++pp) mid += d.is_psum[pp];
-            }
+#pragma unroll
+        for (int u = 0; u < SU; ++u) {
+            const bool on = it_[u] < 0;
+            sa_[u] = on ? d.sstamp[div_p2(lo_[u], g.tile)] : 0u;
+            sb_[u] = on ? d.sstamp[div_p2(hi_[u], g.tile)] : 0u;
         }
-        for (uint64_t wm = (uint64_t)__ballot(wide); wm; wm &= wm - 1) {
-            const int L = __builtin_ctzll(wm);
-            const int a = __builtin_amdgcn_readlane(plo, L), b = __builtin_amdgcn_readlane(phi, L);
-            double sum = 0.0;
-            FF sumc = ff_of(0.0f);
-            if (naive) {
-                float m = 0.0f;
-                for (int pp = a + lane; pp < b; pp += 64) m += (float)d.is_psum[pp];
-                for (int o = 32; o >= 1; o >>= 1) m += __shfl_xor(m, o, 64);
-                sum = (double)m;
-            } else if (comp) {
-                FF m = ff_of(0.0f);
-                for (int pp = a + lane; pp < b; pp += 64) m = ff_add(m, psum_ff[pp]);
-                for (int o = 32; o >= 1; o >>= 1) {
-                    FF y;
-                    y.hi = __shfl_xor(m.hi, o, 64);
-                    y.lo = __shfl_xor(m.lo, o, 64);
-                    m = ff_add(m, y);
-                }
-                sumc = m;
-            } else {
-                double m = 0.0;
-                for (int pp = a + lane; pp < b; pp += 64) m += d.is_psum[pp];
-                sum = wave_sum(m);
-            }
-            if (lane == L) {
-                mid = sum;
-                midc = sumc;
-            }
-        }
-        if (eval) {
-            ++evals;
-            const double q = d.c_q[j];
-            r2 = g.prec == PREC_FP64 ? (4.0 * q) * track_inv_sum(d.S, d.is_pre, glo, ghi, g.part, mid)
-                                     : snr2_f32(g, d, q, glo, ghi, mid, midc);
-            d.c_rho2[j] = r2;
-        }
-        if (!live) continue;
-        const double rel = fabs(sqrt(r2) / g.rth - 1.0);
-        minm = fmin(minm, rel);
-        near += rel <= 1e-6;
-        if (r2 > g.rth2) {
-            d.c_iter[j] = t;
-            ++my_new;
-            const int64_t v = (int64_t)d.c_qfx[j];
-            if (v) {
-                const float vf = (float)ldexp((double)v, fx_exp(d.ctl->amax_bits, g.T) +
-                                                             f32_scale(d.ctl->amax_bits, g.T));
-                if (comp) {
-                    subtract_track_comp(g, d, glo, ghi, vf);
+#pragma unroll
+        for (int u = 0; u < SU; ++u) {
+            const uint32_t j = jb0 + (uint32_t)u * stride + (uint32_t)lane;
+            const bool live = j < nc && it_[u] < 0;
+            if (!__ballot(live)) continue;
+            const int glo = live ? lo_[u] : 0, ghi = live ? hi_[u] : 0;
+            const bool eval = live && (t == 0 || track_refiltered(d.sstamp, g, glo, ghi, sa_[u], sb_[u], (uint32_t)t));
+            double r2 = r2_[u];
+            // sum of the part sums of 1/S over the parts strictly before the
+            // track's last part: a loop for tracks over a few parts, all lanes
+            // of the wave together for wider ones, one track at a time
+            const int plo = div_p2(glo, g.part), phi = div_p2(ghi, g.part);
+            const bool need = eval && ghi - glo + 1 > NARROW && phi > plo;
+            const bool wide = need && phi - plo > COOP_PARTS;
+            double mid = 0.0;
+            FF midc = ff_of(0.0f);
+            if (need && !wide) {
+                if (naive) {
+                    float m = 0.0f;
+                    for (int pp = plo; pp < phi; ++pp) m += (float)d.is_psum[pp];
+                    mid = (double)m;
+                } else if (comp) {
+                    for (int pp = plo; pp < phi; ++pp) midc = ff_add(midc, psum_ff[pp]);
                 } else {
-                    subtract_track(g, d, glo, ghi, v);
-                    if (naive) subtract_track_f32(g, d, glo, ghi, vf);
+                    for (int pp = plo; pp < phi; ++pp) mid += d.is_psum[pp];
                 }
             }
-            stamp_tiles(d.xstamp, g, glo, ghi, nxt);
-            int sa, sb;
-            window_reach(g, glo, ghi, &sa, &sb);
-            stamp_tiles(d.sstamp, g, sa, sb, nxt);
+            for (uint64_t wm = (uint64_t)__ballot(wide); wm; wm &= wm - 1) {
+                const int L = __builtin_ctzll(wm);
+                const int a = __builtin_amdgcn_readlane(plo, L), b = __builtin_amdgcn_readlane(phi, L);
+                double sum = 0.0;
+                FF sumc = ff_of(0.0f);
+                if (naive) {
+                    float m = 0.0f;
+                    for (int pp = a + lane; pp < b; pp += 64) m += (float)d.is_psum[pp];
+                    for (int o = 32; o >= 1; o >>= 1) m += __shfl_xor(m, o, 64);
+                    sum = (double)m;
+                } else if (comp) {
+                    FF m = ff_of(0.0f);
+                    for (int pp = a + lane; pp < b; pp += 64) m = ff_add(m, psum_ff[pp]);
+                    for (int o = 32; o >= 1; o >>= 1) {
+                        FF y;
+                        y.hi = __shfl_xor(m.hi, o, 64);
+                        y.lo = __shfl_xor(m.lo, o, 64);
+                        m = ff_add(m, y);
+                    }
+                    sumc = m;
+                } else {
+                    double m = 0.0;
+                    for (int pp = a + lane; pp < b; pp += 64) m += d.is_psum[pp];
+                    sum = wave_sum(m);
+                }
+                if (lane == L) {
+                    mid = sum;
+                    midc = sumc;
+                }
+            }
+            if (eval) {
+                ++evals;
+                const double q = d.c_q[j];
+                r2 = g.prec == PREC_FP64 ? (4.0 * q) * track_inv_sum(d.S, d.is_pre, glo, ghi, g.part, mid)
+                                         : snr2_f32(g, d, q, glo, ghi, mid, midc);
+                d.c_rho2[j] = r2;
+            }
+            if (!live) continue;
+            // a stored rho^2 has been in the margin's minimum since its
+            // evaluation; it counts as near again in every body
+            if (eval || fabs(r2 - g.rth2) <= 1e-5 * g.rth2) {
+                const double rel = fabs(sqrt(r2) / g.rth - 1.0);
+                minm = fmin(minm, rel);
+                near += rel <= 1e-6;
+            }
+            if (r2 > g.rth2) {
+                d.c_iter[j] = t;
+                ++my_new;
+                const int64_t v = (int64_t)d.c_qfx[j];
+                if (v) {
+                    const float vf = (float)ldexp((double)v, fx_exp(d.ctl->amax_bits, g.T) +
+                                                                 f32_scale(d.ctl->amax_bits, g.T));
+                    if (comp) {
+                        subtract_track_comp(g, d, glo, ghi, vf);
+                    } else {
+                        subtract_track(g, d, glo, ghi, v);
+                        if (naive) subtract_track_f32(g, d, glo, ghi, vf);
+                    }
+                }
+                stamp_tiles(d.xstamp, g, glo, ghi, nxt);
+                int sa, sb;
+                window_reach(g, glo, ghi, &sa, &sb);
+                stamp_tiles(d.sstamp, g, sa, sb, nxt);
+            }
         }
     }
-    for (int s = 32; s >= 1; s >>= 1) {
-        my_new += (uint32_t)__shfl_xor((int)my_new, s, 64);
-        near += (uint64_t)__shfl_xor((long long)near, s, 64);
-        evals += (uint64_t)__shfl_xor((long long)evals, s, 64);
-        minm = fmin(minm, __shfl_xor(minm, s, 64));
-    }
+    my_new = wave_scan_u32(my_new);
+    near = wave_scan_u32(near);
+    evals = wave_scan_u32(evals);
+    for (int s = 32; s >= 1; s >>= 1) minm = fmin(minm, __shfl_xor(minm, s, 64));
     const int w = threadIdx.x >> 6;
-    if (lane_id() == 0) {
+    if (lane == 63) {
         s_red[0][w] = my_new;
         s_red[1][w] = near;
         s_red[2][w] = evals;
@@ -2278,10 +2299,10 @@ __global__ __launch_bounds__(WG) void k_snr(const Slot *S)
             s_min[0] = fmin(s_min[0], s_min[v]);
         }
         SnrPart p;
-        p.n_new = (uint32_t)s_red[0][0];
-        p.pad = 0;
+        p.n_new = s_red[0][0];
         p.near = s_red[1][0];
         p.evals = s_red[2][0];
+        p.pad = 0;
         p.minm = s_min[0];
         d.b_part[blockIdx.x] = p;
     }
@@ -2295,112 +2316,113 @@ __global__ __launch_bounds__(WG) void k_snr(const Slot *S)
 template <int NT> DEVI void snr_tail(const Slot &sl)
 {
     constexpr int NW = NT / 64;
-    __shared__ uint64_t s_red[5][NW];     // new, near, evals, ux, us
-    __shared__ uint32_t s_nds[NW];
-    __shared__ uint32_t s_wl[NW];
+    constexpr int NR = 4;                 // new, near, evals, X tiles
+    constexpr int NP = SNR_BLOCKS / NT;
+    __shared__ uint32_t s_red[NR][NW];
+    __shared__ uint32_t s_wl[2][NW];
     __shared__ double s_min[NW];
     const Grid g = sl.g;
     const Dev d = sl.d;
     Ctl *c = d.ctl;
-    if (!c->tail_due || c->done || c->bad) return;
+    const Ctl k = *c;                     // every field read once, ahead of the stores
+    if (!k.tail_due || k.done || k.bad) return;
     if (g.prec == PREC_NAIVE) block_scan_array<float, NT>(d.Dtf, d.Dcf, g.nt);
-    const uint32_t nxt = c->iter + 1;
-    uint64_t nw = 0, near = 0, evals = 0, ux = 0, us = 0;
-    uint32_t nds = 0;
-    double minm = INFINITY;
-    for (int i = threadIdx.x; i < SNR_BLOCKS; i += NT) {
-        const SnrPart p = d.b_part[i];
-        nw += p.n_new;
-        near += p.near;
-        evals += p.evals;
-        minm = fmin(minm, p.minm);
-    }
+    const uint32_t nxt = k.iter + 1;
+    const uint32_t lx = d.xstamp[g.nt - 1], ls = d.sstamp[g.nt - 1];
+    const int w = threadIdx.x >> 6;
+    SnrPart p[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) p[i] = d.b_part[threadIdx.x + i * NT];
     // stamped-tile counts, and the list of the tiles to filter in the next
-    // body in tile order (per round of NT tiles: a ballot and a prefix over
-    // the waves)
-    uint32_t listed = 0;                  // block-uniform
-    for (int base = 0; base < g.nt; base += NT) {
-        const int tl = base + (int)threadIdx.x;
-        bool sd = false;
-        if (tl < g.nt) {
-            const uint64_t width = (uint64_t)min(g.tile, g.B - tl * g.tile);
-            if (d.xstamp[tl] == nxt) ux += width;
-            sd = d.sstamp[tl] == nxt;
-            if (sd) {
-                us += width;
-                ++nds;
-            }
+    // body in tile order: rounds of TW tiles per thread, all stamps of a round
+    // loaded together.  One tile per thread and round, with two barriers each,
+    // were 8 rounds of load latency for 1843 tiles and 15 for 3686: the launch
+    // took 10.8 and 14 us a body instead of 9.9 and 11.3
+    constexpr int TW = 2048 / NT;
+    uint32_t nx = 0, listed = 0;          // listed is block-uniform
+    for (int base = 0, rd = 0; base < g.nt; base += NT * TW, rd ^= 1) {
+        const int t0 = base + (int)threadIdx.x * TW;
+        uint32_t xs[TW], ss[TW];
+#pragma unroll
+        for (int q = 0; q < TW; ++q) {
+            const int tl = min(t0 + q, g.nt - 1);
+            xs[q] = d.xstamp[tl];
+            ss[q] = d.sstamp[tl];
         }
-        const uint64_t m = (uint64_t)__ballot(sd);
-        if (lane_id() == 0) s_wl[threadIdx.x >> 6] = (uint32_t)__popcll(m);
+        uint32_t mask = 0;
+#pragma unroll
+        for (int q = 0; q < TW; ++q) {
+            if (t0 + q >= g.nt) continue;
+            nx += xs[q] == nxt;
+            mask |= (ss[q] == nxt ? 1u : 0u) << q;
+        }
+        const uint32_t own = (uint32_t)__popc(mask), inc = wave_scan_u32(own);
+        if (lane_id() == 63) s_wl[rd][w] = inc;
         __syncthreads();
-        uint32_t pre = 0, tot = 0;
+        uint32_t at = listed + inc - own;
 #pragma unroll
         for (int v = 0; v < NW; ++v) {
-            const uint32_t x = s_wl[v];
-            pre += v < (int)(threadIdx.x >> 6) ? x : 0u;
-            tot += x;
+            const uint32_t x = s_wl[rd][v];
+            at += v < w ? x : 0u;
+            listed += x;
         }
-        if (sd) d.sdl[listed + pre + (uint32_t)__popcll(m & ((1ull << lane_id()) - 1ull))] = (uint32_t)tl;
-        listed += tot;
-        __syncthreads();
+        for (; mask; mask &= mask - 1) d.sdl[at++] = (uint32_t)(t0 + __builtin_ctz(mask));
     }
-    for (int s = 32; s >= 1; s >>= 1) {
-        nw += (uint64_t)__shfl_xor((long long)nw, s, 64);
-        near += (uint64_t)__shfl_xor((long long)near, s, 64);
-        evals += (uint64_t)__shfl_xor((long long)evals, s, 64);
-        ux += (uint64_t)__shfl_xor((long long)ux, s, 64);
-        us += (uint64_t)__shfl_xor((long long)us, s, 64);
-        nds += (uint32_t)__shfl_xor((int)nds, s, 64);
-        minm = fmin(minm, __shfl_xor(minm, s, 64));
+    uint32_t red[NR] = {0, 0, 0, nx};
+    double minm = INFINITY;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        red[0] += p[i].n_new;
+        red[1] += p[i].near;
+        red[2] += p[i].evals;
+        minm = fmin(minm, p[i].minm);
     }
-    const int w = threadIdx.x >> 6;
-    if (lane_id() == 0) {
-        s_red[0][w] = nw;
-        s_red[1][w] = near;
-        s_red[2][w] = evals;
-        s_red[3][w] = ux;
-        s_red[4][w] = us;
-        s_nds[w] = nds;
-        s_min[w] = minm;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const uint32_t x = wave_scan_u32(red[r]);
+        if (lane_id() == 63) s_red[r][w] = x;
     }
+    for (int s = 32; s >= 1; s >>= 1) minm = fmin(minm, __shfl_xor(minm, s, 64));
+    if (lane_id() == 0) s_min[w] = minm;
     __syncthreads();
     if (threadIdx.x != 0) return;
     for (int v = 1; v < NW; ++v) {
-        for (int r = 0; r < 5; ++r) s_red[r][0] += s_red[r][v];
-        s_nds[0] += s_nds[v];
+        for (int r = 0; r < NR; ++r) s_red[r][0] += s_red[r][v];
         s_min[0] = fmin(s_min[0], s_min[v]);
     }
-    const int t = (int)c->iter;
-    const uint32_t n_new = (uint32_t)s_red[0][0];
+    // bins of the stamped tiles: the last tile may be short
+    const uint32_t pad = (uint32_t)(g.nt * g.tile - g.B);
+    const uint64_t ux = (uint64_t)s_red[3][0] * (uint32_t)g.tile - (lx == nxt ? pad : 0u);
+    const uint64_t us = (uint64_t)listed * (uint32_t)g.tile - (ls == nxt ? pad : 0u);
+    const uint32_t n_new = s_red[0][0];
     c->tail_due = 0;
-    c->med_split = s_nds[0] <= g.split_tiles;
-    c->n_sdl = s_nds[0];
-    if (t < NEW_CAP) d.n_new[t] = n_new;
-    c->n_resolved += n_new;
-    c->n_near += s_red[1][0];
-    c->units_snr += s_red[2][0];
-    if (s_min[0] < __longlong_as_double((long long)c->min_margin))
+    c->med_split = listed <= g.split_tiles;
+    c->n_sdl = listed;
+    if (k.iter < (uint32_t)NEW_CAP) d.n_new[k.iter] = n_new;
+    c->n_resolved = k.n_resolved + n_new;
+    c->n_near = k.n_near + s_red[1][0];
+    c->units_snr = k.units_snr + s_red[2][0];
+    if (s_min[0] < __longlong_as_double((long long)k.min_margin))
         c->min_margin = (uint64_t)__double_as_longlong(s_min[0]);
-    const uint32_t mi = g.max_iter ? g.max_iter : c->n_cand + 1;
+    const uint32_t mi = g.max_iter ? g.max_iter : k.n_cand + 1;
     uint32_t done = 0;
     if (n_new == 0) {
         done = 1;
-        c->n_iter = (uint32_t)t + 1;
-    } else if ((uint32_t)t + 1 >= mi) {
+        c->n_iter = nxt;
+    } else if (nxt >= mi) {
         done = 1;                    // the loop did not settle within max_iter bodies
         c->status = 6;
-        c->n_iter = (uint32_t)t + 1;
+        c->n_iter = nxt;
     } else {
-        c->iter = (uint32_t)t + 1;
-        c->units_x += s_red[3][0];
-        c->units_med += s_red[4][0];
+        c->iter = nxt;
+        c->units_x = k.units_x + ux;
+        c->units_med = k.units_med + us;
     }
     c->done = done;
     // progress for the host that paces the launches: bodies finished and the
     // settled flag in one word, so that the host never sees one without the other
     if (sl.prog)
-        __hip_atomic_store(sl.prog, ((uint32_t)t + 1) << 1 | done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(sl.prog, nxt << 1 | done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The tail as a kernel of its own, ahead of k_xupdate: the naive FP32 mode
