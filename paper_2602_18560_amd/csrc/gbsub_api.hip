@@ -274,6 +274,7 @@ Dims dims_of(const Slot &sl)
     dm.maxnt = sl.g.nt;
     dm.maxtile = sl.g.tile;
     dm.maxparts = sl.g.nparts;
+    dm.maxlist = list_entries(sl.g);
     dm.est_mask = 1u << sl.g.est;
     dm.naive = sl.g.prec == PREC_NAIVE;
     dm.prep_blocks = (uint32_t)((sl.n + PREP_SRC - 1) / PREP_SRC);
@@ -287,6 +288,7 @@ void widen(Dims &a, const Dims &b)
     a.maxnt = std::max(a.maxnt, b.maxnt);
     a.maxtile = std::max(a.maxtile, b.maxtile);
     a.maxparts = std::max(a.maxparts, b.maxparts);
+    a.maxlist = std::max(a.maxlist, b.maxlist);
     a.est_mask |= b.est_mask;
     a.naive |= b.naive;
     a.prep_blocks = std::max(a.prep_blocks, b.prep_blocks);
@@ -1069,7 +1071,7 @@ namespace {
 bool same_dims(const Dims &a, const Dims &b)
 {
     return a.ns == b.ns && a.maxB == b.maxB && a.maxnt == b.maxnt && a.maxtile == b.maxtile &&
-           a.maxparts == b.maxparts && a.est_mask == b.est_mask && a.naive == b.naive;
+           a.maxparts == b.maxparts && a.maxlist == b.maxlist && a.est_mask == b.est_mask && a.naive == b.naive;
 }
 
 void drop_graph(gbsub_batch *b)

@@ -1747,6 +1747,7 @@ hipError_t cx_launch_psd(const Grid &g, const CxDev &d, hipStream_t st, hipEvent
     dm.maxnt = g.nt;
     dm.maxtile = g.tile;
     dm.maxparts = g.nparts;
+    dm.maxlist = list_entries(g);
     dm.est_mask = 1u << g.est;
     return launch_median(d.slots, dm, st, ea, eb);
 }

@@ -20,13 +20,12 @@ constexpr int CS_WG = 1024;        // threads of a column-pass block (64 tiles, 
 constexpr int ACC_EV = 65536;      // binning events per accumulation block
 constexpr int RED_BINS = 256;      // bins per reduction block of the hot buckets
 constexpr int NEW_CAP = 1 << 16;   // per-iteration counters kept (iterations beyond: not recorded)
-constexpr int KEYBITS = 20;        // bits of the per-tile order key of the median sort
+constexpr int KEYBITS = 18;        // bits of the per-tile order key of the median sort
 constexpr int POSBITS = 12;        // sort word = key << 12 | position (MMAX <= 4096)
 enum Prec { PREC_FP64 = 0, PREC_COMP = 1, PREC_NAIVE = 2 };   // Grid::prec (= gbsub_config precision)
 constexpr int COARSE_MAX = 256;    // coarse-graining bins at most
 constexpr int PART_MAX = 512;      // outputs of a median block in split mode (prefix-of-1/S granule)
 constexpr int SPLIT_BLOCKS = 512;  // split the median into parts while dirty tiles x parts fit this
-constexpr int MED_GRID = 2048;     // blocks of a median launch (per slot); they stride over the dirty list
 
 // Signed 128-bit fixed-point accumulator (two's complement: hi*2^64 + lo).
 // Every power is accumulated as an exact integer multiple of 2^L, so sums
@@ -201,10 +200,17 @@ struct Slot {
 struct Dims {
     int ns;                  // slots (gridDim.y)
     int maxB, maxnt, maxtile, maxparts;
+    int maxlist;             // entries of a listed median launch: every tile, or the split budget's parts
     uint32_t est_mask;       // bit e: some slot uses estimator e
     uint32_t naive;          // some slot runs in naive FP32
     uint32_t prep_blocks, accum_blocks;
 };
+
+inline int list_entries(const Grid &g)
+{
+    const int parts = (int64_t)g.split_blocks < (int64_t)g.nparts ? (int)g.split_blocks : g.nparts;
+    return g.nt > parts ? g.nt : parts;
+}
 
 // Kernel launchers (gbsub_kernels.hip); all enqueue on `st` and return the
 // launch status.  `ds` is the device array of `dm.ns` slot descriptors.

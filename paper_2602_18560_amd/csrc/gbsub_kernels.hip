@@ -1252,48 +1252,54 @@ __global__ __launch_bounds__(WG) void k_xupdate(const Slot *S)
 //
 // One block per tile of `tile` outputs.  The union of the tile's windows
 // (tile + W - 1 bins) is loaded once into LDS and sorted there: a stable LSD
-// radix sort on a per-tile 20-bit order key (the fp64 bit pattern minus the
+// radix sort on a per-tile 16-bit order key (the fp64 bit pattern minus the
 // tile minimum, shifted), then an exact repair that orders equal keys by
-// the full fp64 value.  The sorted index (rank) of every union position
-// then goes into a wavelet matrix: one stable partition of the rank
-// sequence per rank bit, most significant first, down to buckets of 32
-// consecutive ranks, with the bit words and a zero count per 64 positions
-// kept in LDS.  The median of a window is the h-th smallest rank among its
-// W positions: descending the levels (two rank queries per level) gives its
-// bucket and its index there, and the bucket's 32 sorted elements are
-// tested against the window.  Each of the 512 threads answers its
-// R = tile/512 (at most 4) windows independently.  Selection is exact: no
-// arithmetic touches X.
+// the full fp64 value.  The sorted order is cut into buckets of 32 or 64
+// consecutive ranks, and a bit matrix in LDS holds, for every bucket b and
+// 64-position word, which positions have a rank up to the end of bucket b,
+// with the count of such positions before the word.  The median of a window
+// is the h-th smallest rank among its W positions: a binary search over the
+// buckets (two counts per step) gives its bucket and its index there, and
+// the bucket's sorted elements are tested against the window.  Each of the
+// 512 threads answers its R = tile/512 (at most 4) windows independently.
+// Selection is exact: no arithmetic touches X.
+//
+// The kernel is bound by the latency of its LDS phases (two blocks per CU in
+// a full-grid launch, one block's own chain in late bodies), so each phase is
+// built for few dependent steps and barriers: two 9-bit radix passes ranked by
+// ballots instead of five 4-bit ones with scanned counters, ties ordered by
+// counting inside their run instead of odd-even rounds, and one atomic OR per
+// element with two short scans instead of a stable partition per rank bit (a
+// wavelet matrix).  1e7 catalog, W = 1001: 26.4 us a launch instead of 36.5,
+// 17 instead of 25 in the late bodies, of which load 1.4, sort 4.5, ties 1-4,
+// matrix 2.2, selection 2.3, outputs 1.2 and the launch itself 4.5.  8-bit
+// passes (16-bit keys) sort in 4.1 us, but leave more ties than they save.
 
 constexpr int MWG = 512;                    // threads of a median block
 constexpr int RMAX = TILE_MAX / MWG;        // outputs per thread, at most
 constexpr int MCH = MMAX / MWG;             // union elements per thread in the sort
-constexpr int REPAIR_ROUNDS = 16;           // tie-repair rounds after which the sort is refined
-constexpr int WLB = 12;                     // wavelet levels, at most: ranks < MMAX <= 2^12
-constexpr int WWD = MMAX / 64 + 1;          // 64-position words per level (+1: the end position)
-
-// One 64-position word of a wavelet level: its bits and the zeros before it.
-struct alignas(16) WWord {
-    uint64_t bits;
-    uint32_t zpre;
-    uint32_t pad;
-};
+constexpr int DGB = 9;                      // bits of a radix digit
+constexpr int NDG = 1 << DGB;               // digits: one per thread in the scan
+static_assert(NDG == MWG && KEYBITS == 2 * DGB, "the sort's scan and its two passes");
+constexpr int RUN_MAX = 64;                 // longest run of equal keys that the repair orders by counting
+constexpr int NBK = MMAX / 64;              // rank buckets, at most
+constexpr int NWD = MMAX / 64 + 1;          // 64-position words (+1: the end position)
 
 struct MedianSmem {
     double xv[MMAX];                       // X over the union, position order
     uint32_t kp[2][MMAX];                  // sort words: key << POSBITS | position
-    uint16_t rank[MMAX];                   // sorted index of each position
     union {
-        uint16_t off[16 * MWG];             // radix: per-thread digit offsets
-        struct {
-            WWord w[WLB][WWD];             // bits of the positions, level by level
-            uint32_t zt[WLB];              // zeros of the level
-            uint32_t zc[MCH * (MWG / 64)]; // zeros per (element chunk, wave)
-        } wm;                              // wavelet matrix of the ranks
+        uint32_t hist[2][MWG / 64][NDG / 2]; // radix: per-wave digit counts, then offsets, 16 bits each
+                                            // (two buffers, for the passes in turn)
+        struct {                            // rows of nw | 1 words
+            uint64_t bits[NBK * (NWD | 1)]; // positions with a rank up to the end of the bucket
+            uint16_t cnt[NBK * (NWD | 1)];  // such positions before the word
+        } bm;
         double stage[TILE_MAX];            // outputs, for coalesced stores
     } u;
-    uint32_t wsc[(MWG / 64 + 1) * 8];       // cross-wave scan exchange of the radix sort
-    uint64_t red[2 * (MWG / 64)];
+    uint32_t wsc[MWG / 64];                 // cross-wave exchange of the radix sort's scan
+    uint32_t red[2][MWG / 64];              // smallest and largest X of each wave (high words)
+    uint64_t fix[MMAX / 64];                // elements of the runs that the repair orders
     double dsh[MWG / 64];
     int flag;
 };
@@ -1311,92 +1317,107 @@ DEVI uint32_t wave_scan_u32(uint32_t v)
     return v;
 }
 
-// Block-wide exclusive scan of NW words per thread (fields must not
-// overflow); tot[] receives the block totals.  The per-wave totals are
-// combined by NW threads (one word each), so a thread keeps only its own
-// words in registers.  Contains two barriers; `wsc` holds (MWG/64 + 1) * NW
-// words and may be rewritten only after a further barrier.
-template <int NW>
-DEVI void block_scan_words(const uint32_t (&w)[NW], uint32_t (&ex)[NW], uint32_t (&tot)[NW],
-                           uint32_t *wsc)
+// Smallest (largest) word of the wave, in lane 63.
+DEVI uint32_t wave_min_u32(uint32_t v)
 {
-    constexpr int NV = MWG / 64;
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
-    uint32_t inc[NW];
-#pragma unroll
-    for (int j = 0; j < NW; ++j) inc[j] = wave_scan_u32(w[j]);
-    if (lane == 63) {
-#pragma unroll
-        for (int j = 0; j < NW; ++j) wsc[wave * NW + j] = inc[j];
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < NW) {
-        const int j = threadIdx.x;
-        uint32_t run = 0;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            const uint32_t x = wsc[v * NW + j];
-            wsc[v * NW + j] = run;
-            run += x;
-        }
-        wsc[NV * NW + j] = run;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < NW; ++j) {
-        ex[j] = wsc[wave * NW + j] + inc[j] - w[j];
-        tot[j] = wsc[NV * NW + j];
-    }
+    auto low = [&](int x) { v = min(v, (uint32_t)x); };
+    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x111, 0xF, 0xF, false));
+    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x112, 0xF, 0xF, false));
+    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x114, 0xF, 0xF, false));
+    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x118, 0xF, 0xF, false));
+    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xA, 0xF, false));
+    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xC, 0xF, false));
+    return v;
 }
+DEVI uint32_t wave_max_u32(uint32_t v) { return ~wave_min_u32(~v); }
 
-// Stable LSD radix sort of the M words in sm.kp[0] by bits [POSBITS,
-// POSBITS + 4*passes), 4 bits per pass; returns the buffer holding the
-// result.  Thread chunks are contiguous in the current order; within-chunk
-// ranks are kept in registers.
+// Stable LSD radix sort of the M words in sm.kp[0] by bits [POSBITS, POSBITS +
+// DGB*passes), DGB bits per pass; returns the buffer holding the result.  A
+// wave owns a contiguous range of the current order, 64 words at a time: a
+// word's rank among the wave's equal digits is the wave's count so far plus
+// the lower lanes with its digit (a ballot per bit).  The lowest lane of each
+// digit adds the digit's count (the adds of all words are in flight together)
+// and hands the count before it to the others.  The counts, scanned over
+// (digit, wave), become the offsets.  The caller's stores to kp[0] need no
+// barrier of their own.
 DEVI int radix_sort_tile(MedianSmem &sm, int M, int passes)
 {
-    const int tid = threadIdx.x;
+    constexpr int NV = MWG / 64;
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const int CH = (M + MWG - 1) / MWG;
-    const int beg = tid * CH;
+    const int seg = wave * CH * 64 + lane;
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int q = 0; q < NV * NDG / 2 / MWG; ++q) (&sm.u.hist[0][0][0])[q * MWG + tid] = 0;
+    __syncthreads();
     int in = 0;
     for (int ps = 0; ps < passes; ++ps) {
-        const int sh = POSBITS + 4 * ps;
+        const int sh = POSBITS + DGB * ps;
         const uint32_t *kin = sm.kp[in];
         uint32_t *kout = sm.kp[in ^ 1];
-        uint32_t e[MCH];
-        uint32_t lr[MCH];
-        uint64_t c = 0;
+        uint32_t *hist = sm.u.hist[ps & 1][wave];
+        uint32_t e[MCH], lr[MCH], old[MCH];
+        int first[MCH];
 #pragma unroll
-        for (int i = 0; i < MCH; ++i) e[i] = (i < CH && beg + i < M) ? kin[beg + i] : 0u;
+        for (int c = 0; c < MCH; ++c)
+            if (c < CH) e[c] = kin[min(seg + c * 64, M - 1)];
 #pragma unroll
-        for (int i = 0; i < MCH; ++i) {
-            if (i < CH && beg + i < M) {
-                const uint32_t dg = (e[i] >> sh) & 15u;
-                lr[i] = (uint32_t)(c >> (4 * dg)) & 15u;
-                c += 1ull << (4 * dg);
+        for (int c = 0; c < MCH; ++c) {
+            if (c >= CH) continue;
+            const bool ok = seg + c * 64 < M;
+            const uint32_t dg = (e[c] >> sh) & (NDG - 1u);
+            const uint64_t in = (uint64_t)__ballot(ok);
+            uint32_t plo = (uint32_t)in, phi = (uint32_t)(in >> 32);
+#pragma unroll
+            for (int bit = 0; bit < DGB; ++bit) {
+                const uint32_t sg = (uint32_t)((int32_t)(dg << (31 - bit)) >> 31);     // the bit in every bit
+                const uint64_t m = (uint64_t)__ballot(sg != 0);
+                plo &= ~((uint32_t)m ^ sg);
+                phi &= ~((uint32_t)(m >> 32) ^ sg);
+            }
+            const uint64_t peers = (uint64_t)phi << 32 | plo;
+            lr[c] = (uint32_t)__popcll(peers & below);
+            first[c] = __ffsll((unsigned long long)peers) - 1;
+            old[c] = 0;
+            if (ok && lr[c] == 0)
+                old[c] = atomicAdd(&hist[dg >> 1], (uint32_t)__popcll(peers) << (16 * (dg & 1u)));
+        }
+#pragma unroll
+        for (int c = 0; c < MCH; ++c) {
+            if (c >= CH) continue;
+            const uint32_t dg = (e[c] >> sh) & (NDG - 1u);
+            lr[c] += ((uint32_t)__shfl((int)old[c], first[c] & 63, 64) >> (16 * (dg & 1u))) & 0xFFFFu;
+        }
+        __syncthreads();
+        // exclusive scan over (digit, wave), thread = digit
+        uint16_t(*h)[NDG] = reinterpret_cast<uint16_t(*)[NDG]>(&sm.u.hist[ps & 1][0][0]);
+        {
+            uint32_t c[NV], s = 0;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                c[v] = h[v][tid];
+                s += c[v];
+            }
+            const uint32_t inc = wave_scan_u32(s);
+            if (lane == 63) sm.wsc[wave] = inc;
+            if (ps + 1 < passes) {
+#pragma unroll
+                for (int q = 0; q < NV * NDG / 2 / MWG; ++q) (&sm.u.hist[(ps & 1) ^ 1][0][0])[q * MWG + tid] = 0;
+            }
+            __syncthreads();
+            uint32_t run = inc - s;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) run += v < wave ? sm.wsc[v] : 0u;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                h[v][tid] = (uint16_t)run;
+                run += c[v];
             }
         }
-        uint32_t w[8], ex[8], tot[8];
+        __syncthreads();
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            w[j] = (uint32_t)((c >> (8 * j)) & 15u) | ((uint32_t)((c >> (8 * j + 4)) & 15u) << 16);
-        block_scan_words<8>(w, ex, tot, sm.wsc);
-        uint32_t run = 0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            sm.u.off[(2 * j) * MWG + tid] = (uint16_t)(run + (ex[j] & 0xFFFFu));
-            run += tot[j] & 0xFFFFu;
-            sm.u.off[(2 * j + 1) * MWG + tid] = (uint16_t)(run + (ex[j] >> 16));
-            run += tot[j] >> 16;
-        }
-        // offsets are private to the thread: no barrier before reading them
-#pragma unroll
-        for (int i = 0; i < MCH; ++i) {
-            if (i < CH && beg + i < M) {
-                const uint32_t dg = (e[i] >> sh) & 15u;
-                kout[sm.u.off[dg * MWG + tid] + lr[i]] = e[i];
-            }
-        }
+        for (int c = 0; c < MCH; ++c)
+            if (c < CH && seg + c * 64 < M) kout[h[wave][(e[c] >> sh) & (NDG - 1u)] + lr[c]] = e[c];
         __syncthreads();
         in ^= 1;
     }
@@ -1496,121 +1517,183 @@ DEVI void median_work(MedianSmem &sm, const Slot *slp, int blk, int span)
     const int u1 = whole ? B - 1 : win_start(t1 - 1, B, W, h) + W - 1;
     const int M = u1 - u0 + 1;
 
-    // ---- load the union (all loads in flight together); tile min / max
-    double xr[MCH];
+    // ---- load the union and the outputs' S_instr (all loads in flight
+    // together); tile min / max
+    double xr[MCH], sxr[RMAX];
+#pragma unroll
+    for (int r = 0; r < RMAX; ++r) sxr[r] = d.sx[min(t0 + tid + r * MWG, t1 - 1)];
 #pragma unroll
     for (int i = 0; i < MCH; ++i) {
         const int p = tid + i * MWG;
         xr[i] = p < M ? d.X[u0 + p] : 0.0;
     }
-    uint64_t mn = ~0ull, mx = 0;
+    // bounds of the positive values, from the high words of the fp64 patterns
+    uint32_t mn32 = ~0u, mx32 = 0;
 #pragma unroll
     for (int i = 0; i < MCH; ++i) {
         const int p = tid + i * MWG;
         if (p < M) {
             sm.xv[p] = xr[i];
             const uint64_t b = (uint64_t)__double_as_longlong(xr[i]);
-            mn = (b != 0 && b < mn) ? b : mn;          // smallest positive value
-            mx = b > mx ? b : mx;
+            const uint32_t hi = (uint32_t)(b >> 32);
+            mn32 = b != 0 ? min(mn32, hi) : mn32;
+            mx32 = max(mx32, hi);
         }
     }
-    for (int s = 32; s >= 1; s >>= 1) {
-        const uint64_t a = (uint64_t)__shfl_xor((long long)mn, s, 64);
-        const uint64_t b = (uint64_t)__shfl_xor((long long)mx, s, 64);
-        mn = a < mn ? a : mn;
-        mx = b > mx ? b : mx;
+    mn32 = wave_min_u32(mn32);
+    mx32 = wave_max_u32(mx32);
+    if (lane_id() == 63) {
+        sm.red[0][tid >> 6] = mn32;
+        sm.red[1][tid >> 6] = mx32;
     }
-    if (lane_id() == 0) {
-        sm.red[tid >> 6] = mn;
-        sm.red[(MWG / 64) + (tid >> 6)] = mx;
-    }
+    if (tid < MMAX / 64) sm.fix[tid] = 0;
+    if (tid == 0) sm.flag = 0;
     __syncthreads();
-    mn = sm.red[0];
-    mx = sm.red[MWG / 64];
-    for (int w = 1; w < MWG / 64; ++w) {
-        mn = sm.red[w] < mn ? sm.red[w] : mn;
-        mx = sm.red[MWG / 64 + w] > mx ? sm.red[MWG / 64 + w] : mx;
+#pragma unroll
+    for (int w = 0; w < MWG / 64; ++w) {
+        mn32 = min(w == 0 ? ~0u : mn32, sm.red[0][w]);
+        mx32 = max(w == 0 ? 0u : mx32, sm.red[1][w]);
     }
-    // order key: 0 for an empty bin, 1 + (bits - smallest positive bits) >> shift
+    // order key: 0 for an empty bin, 1 + (bits - lower bound) >> shift
     // otherwise (X >= 0, so the fp64 bit patterns are in value order); empty
     // bins do not stretch the key range of the occupied ones
+    const uint64_t mn = (uint64_t)mn32 << 32, mx = (uint64_t)mx32 << 32 | 0xFFFFFFFFull;
     const uint64_t vspan = mx > mn ? mx - mn : 0;
     const int span_bits = vspan ? 64 - __clzll(vspan) : 0;
-    const int shift = span_bits > KEYBITS - 1 ? span_bits - (KEYBITS - 1) : 0;
-    const uint32_t kmax = mx ? 1u + (uint32_t)(vspan >> shift) : 0u;
-    const int passes = ((kmax ? 32 - __clz(kmax) : 0) + 3) / 4;
+    const int shift = span_bits > KEYBITS ? span_bits - KEYBITS : 0;
+    constexpr uint64_t KMAX = (1ull << KEYBITS) - 1ull;
+    auto key_of = [&](uint64_t b) -> uint32_t {       // the two largest keys share the last value
+        const uint64_t k = 1ull + ((b - mn) >> shift);
+        return b ? (uint32_t)(k < KMAX ? k : KMAX) : 0u;
+    };
 #pragma unroll
     for (int i = 0; i < MCH; ++i) {
         const int p = tid + i * MWG;
-        if (p < M) {
-            const uint64_t b = (uint64_t)__double_as_longlong(xr[i]);
-            const uint32_t key = b ? 1u + (uint32_t)((b - mn) >> shift) : 0u;
-            sm.kp[0][p] = (key << POSBITS) | (uint32_t)p;
-        }
+        if (p < M) sm.kp[0][p] = (key_of((uint64_t)__double_as_longlong(xr[i])) << POSBITS) | (uint32_t)p;
     }
-    __syncthreads();
 
     // ---- sort
-    int rb = radix_sort_tile(sm, M, passes);
-    uint32_t *sw = sm.kp[rb];
+    uint32_t *sw = sm.kp[radix_sort_tile(sm, M, 2)];
 
-    // ---- repair key ties: order equal keys by (fp64 value, position), by
-    // odd-even transposition inside runs of equal keys.  A run needs about
-    // as many rounds as its elements must travel; an outlier can stretch
-    // the key range until long runs of distinct values share a key, so past
-    // REPAIR_ROUNDS rounds the tile is sorted again by the KEYBITS bits below
-    // the key and then stably by the key, which leaves only short runs.
-    if (shift > 0) {
-        bool refined = false;
-        for (int round = 0;; ++round) {
-            if (round == REPAIR_ROUNDS && !refined) {
-                refined = true;
-                const int sh2 = shift > KEYBITS ? shift - KEYBITS : 0;
-                const uint64_t lmask = (1ull << (shift - sh2)) - 1ull;
-                for (int p = tid; p < M; p += MWG) {
-                    const uint64_t bp = (uint64_t)__double_as_longlong(sm.xv[p]);
-                    const uint32_t lk = bp ? (uint32_t)(((bp - mn) >> sh2) & lmask) : 0u;
-                    sm.kp[0][p] = (lk << POSBITS) | (uint32_t)p;
+    // ---- repair key ties: order equal keys by (fp64 value, position).  A
+    // neighbouring pair out of order marks its run of equal keys; the
+    // elements of a marked run then find their places by counting.  (Long
+    // runs are common where wide tracks leave plateaus of equal values, but
+    // those are in order.)  A marked run of more than RUN_MAX elements
+    // (an outlier can stretch the key range that far) has the tile sorted
+    // again by all its bits, KEYBITS at a time from the lowest.
+    {
+        constexpr int U = 4;                           // words looked at together
+        auto bits_of = [&](uint32_t w) { return (uint64_t)__double_as_longlong(sm.xv[w & 0xFFFu]); };
+        uint32_t mine[MCH];
+        int todo = 0;
+#pragma unroll
+        for (int j = 0; j < MCH; ++j) {
+            const int i = tid + j * MWG;
+            mine[j] = sw[min(i, M - 1)];
+            const uint32_t nx = sw[min(i + 1, M - 1)];
+            if (i + 1 < M && ((mine[j] ^ nx) >> POSBITS) == 0 && bits_of(mine[j]) > bits_of(nx)) todo |= 1 << j;
+        }
+        for (int j = 0; todo >> j; ++j) {
+            if (!((todo >> j) & 1)) continue;
+            const int i = tid + j * MWG;
+            const uint32_t key = sw[i] >> POSBITS;
+            int l = i, r = i + 1;                      // the run's ends, U words ahead at a time
+            for (bool on = true; on && r - l < RUN_MAX;) {
+                uint32_t w[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) w[u] = sw[max(l - 1 - u, 0)];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    on = on && l > 0 && (w[u] >> POSBITS) == key;
+                    l -= on;
                 }
-                __syncthreads();
-                const int r2 = radix_sort_tile(sm, M, (shift - sh2 + 3) / 4);
-                for (int i = tid; i < M; i += MWG) {       // the key again, in the low-key order
-                    const uint32_t p = sm.kp[r2][i] & 0xFFFu;
-                    const uint64_t bp = (uint64_t)__double_as_longlong(sm.xv[p]);
-                    const uint32_t key = bp ? 1u + (uint32_t)((bp - mn) >> shift) : 0u;
-                    sm.kp[0][i] = (key << POSBITS) | p;
-                }
-                __syncthreads();
-                rb = radix_sort_tile(sm, M, passes);
-                sw = sm.kp[rb];
             }
-            if (tid == 0) sm.flag = 0;
-            __syncthreads();
-            int swapped = 0;
-            for (int par = 0; par < 2; ++par) {
-                for (int i = par + 2 * tid; i + 1 < M; i += 2 * MWG) {
-                    const uint32_t a = sw[i], b = sw[i + 1];
-                    if ((a >> POSBITS) != (b >> POSBITS)) continue;
-                    const uint32_t pa = a & 0xFFFu, pb = b & 0xFFFu;
-                    const uint64_t ba = (uint64_t)__double_as_longlong(sm.xv[pa]);
-                    const uint64_t bb = (uint64_t)__double_as_longlong(sm.xv[pb]);
-                    if (ba > bb || (ba == bb && pa > pb)) {
-                        sw[i] = b;
-                        sw[i + 1] = a;
-                        swapped = 1;
+            for (bool on = true; on && r - l < RUN_MAX;) {
+                uint32_t w[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) w[u] = sw[min(r + 1 + u, M - 1)];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    on = on && r + 1 < M && (w[u] >> POSBITS) == key;
+                    r += on;
+                }
+            }
+            atomicOr(&sm.flag, r - l >= RUN_MAX ? 2 : 1);
+            if (r - l >= RUN_MAX) break;
+            const uint64_t ones = (2ull << (r - l)) - 1ull;
+            atomicOr((unsigned long long *)&sm.fix[l >> 6], ones << (l & 63));
+            if ((l >> 6) != (r >> 6)) atomicOr((unsigned long long *)&sm.fix[r >> 6], ones >> (64 - (l & 63)));
+        }
+        __syncthreads();
+        const int flag = sm.flag;
+        if (flag == 1) {                               // places by counting
+            int at[MCH];
+#pragma unroll
+            for (int j = 0; j < MCH; ++j) {
+                const int i = tid + j * MWG;
+                at[j] = -1;
+                if (i >= M || !((sm.fix[i >> 6] >> (i & 63)) & 1ull)) continue;
+                const uint32_t key = mine[j] >> POSBITS;
+                const uint64_t b = bits_of(mine[j]);
+                int n = i;
+                for (int l = i - 1, on = 1; on; l -= U) {
+                    uint32_t w[U];
+                    uint64_t x[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        w[u] = sw[max(l - u, 0)];
+                        x[u] = bits_of(w[u]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        on = on && l - u >= 0 && (w[u] >> POSBITS) == key;
+                        n -= on && x[u] > b;
                     }
                 }
-                __syncthreads();
+                for (int r = i + 1, on = 1; on; r += U) {
+                    uint32_t w[U];
+                    uint64_t x[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        w[u] = sw[min(r + u, M - 1)];
+                        x[u] = bits_of(w[u]);
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        on = on && r + u < M && (w[u] >> POSBITS) == key;
+                        n += on && x[u] < b;
+                    }
+                }
+                at[j] = n;
             }
-            if (swapped) sm.flag = 1;
             __syncthreads();
-            const int any = sm.flag;
+#pragma unroll
+            for (int j = 0; j < MCH; ++j)
+                if (at[j] >= 0) sw[at[j]] = mine[j];
             __syncthreads();
-            if (!any) break;
+        } else if (flag) {
+            for (int p = tid; p < M; p += MWG) sw[p] = (uint32_t)p;
+            for (int lev = (shift + KEYBITS - 1) / KEYBITS; lev >= 0; --lev) {
+                __syncthreads();
+                const int top = lev ? shift - KEYBITS * (lev - 1) : 0, lo = top > KEYBITS ? top - KEYBITS : 0;
+                uint32_t w[MCH];
+#pragma unroll
+                for (int i = 0; i < MCH; ++i) {
+                    const uint32_t q = sw[min(tid + i * MWG, M - 1)] & 0xFFFu;
+                    const uint64_t bp = (uint64_t)__double_as_longlong(sm.xv[q]);
+                    const uint64_t v = lev ? ((bp - mn) >> lo) & ((1ull << (top - lo)) - 1ull)
+                                           : 1ull + ((bp - mn) >> shift);      // KEYBITS + 1 bits
+                    w[i] = ((bp ? (uint32_t)v : 0u) << POSBITS) | q;
+                }
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < MCH; ++i)
+                    if (tid + i * MWG < M) sm.kp[0][tid + i * MWG] = w[i];
+                sw = sm.kp[radix_sort_tile(sm, M, lev ? 2 : 3)];
+            }
         }
     }
-    for (int i = tid; i < M; i += MWG) sm.rank[sw[i] & 0xFFFu] = (uint16_t)i;
-    __syncthreads();
 
     const int R = (span + MWG - 1) / MWG;
     const int kb = t0 + tid * R;
@@ -1621,122 +1704,106 @@ DEVI void median_work(MedianSmem &sm, const Slot *slp, int blk, int span)
 #pragma unroll
         for (int r = 0; r < RMAX; ++r) med[r] = m;
     } else {
-        // ---- wavelet matrix of the rank sequence, levels LB-1 .. WB (the
-        // rank bits above the 32-rank buckets).  Element i of a level is
-        // handled by thread i % MWG (chunk j = i / MWG), so a wave's ballot
-        // is one 64-position word.
+        // ---- bit matrix of the sorted order: buckets of 2^WB ranks (32 in
+        // split mode, whose unions are short enough)
         constexpr int NV = MWG / 64;
-        constexpr int WB = 5;                           // bucket: 2^WB consecutive ranks
         const int lane = lane_id();
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const int NJ = (M + MWG - 1) / MWG;
-        const int LB = M > 1 ? 32 - __clz((uint32_t)(M - 1)) : 1;
-        const uint64_t below = (1ull << lane) - 1ull;
-        uint16_t *src = sm.rank;
-        uint16_t *dst = reinterpret_cast<uint16_t *>(sm.kp[rb ^ 1]);   // free after the sort
-        uint64_t in[MCH];
+        const int WB = M <= 32 * NBK ? 5 : 6;
+        const int nb = (M + (1 << WB) - 1) >> WB;
+        const int nw = (M >> 6) + 1;                   // with the word of the end position
+        const int rw = nw | 1;                         // odd rows: a column's words spread over the banks
+        uint64_t *const bits = sm.u.bm.bits;
+        uint16_t *const cnt = sm.u.bm.cnt;
+        for (int i = tid; i < nb * rw; i += MWG) bits[i] = 0;
+        __syncthreads();
 #pragma unroll
-        for (int j = 0; j < MCH; ++j) in[j] = __ballot(j < NJ && j * MWG + tid < M);
-        for (int lvl = LB - 1; lvl >= WB; --lvl) {
-            uint32_t v[MCH];
-            uint64_t one[MCH];
-#pragma unroll
-            for (int j = 0; j < MCH; ++j) {
-                const int i = j * MWG + tid;
-                const bool ok = j < NJ && i < M;
-                v[j] = ok ? (uint32_t)src[i] : 0u;
-                one[j] = __ballot(ok && ((v[j] >> lvl) & 1u));
-                if (lane == 0 && j < NJ) sm.u.wm.zc[j * NV + wave] = (uint32_t)__popcll(in[j] & ~one[j]);
-            }
-            __syncthreads();
-            // exclusive prefix of the zero counts in element order
-            const uint32_t zv = lane < NJ * NV ? sm.u.wm.zc[lane] : 0u;
-            const uint32_t zinc = wave_scan_u32(zv);
-            const uint32_t zex = zinc - zv;
-            const uint32_t ztot = (uint32_t)__builtin_amdgcn_readlane((int)zinc, NJ * NV - 1);
-#pragma unroll
-            for (int j = 0; j < MCH; ++j) {
-                const uint32_t zw = (uint32_t)__builtin_amdgcn_readlane((int)zex, min(j, NJ - 1) * NV + wave);
-                const int i = j * MWG + tid;
-                if (j < NJ && i < M) {
-                    const uint32_t zb = zw + (uint32_t)__popcll(in[j] & ~one[j] & below);
-                    const bool bit = (v[j] >> lvl) & 1u;
-                    dst[bit ? ztot + (uint32_t)i - zb : zb] = (uint16_t)v[j];
-                    if (lane == 0) {
-                        WWord e;
-                        e.bits = one[j];
-                        e.zpre = zw;
-                        e.pad = 0;
-                        sm.u.wm.w[lvl][i >> 6] = e;
-                    }
-                }
-            }
-            if (tid == 0) {
-                sm.u.wm.zt[lvl] = ztot;
-                if ((M & 63) == 0) {
-                    WWord e;
-                    e.bits = 0;
-                    e.zpre = ztot;
-                    e.pad = 0;
-                    sm.u.wm.w[lvl][M >> 6] = e;
-                }
-            }
-            __syncthreads();
-            uint16_t *tmp = src;
-            src = dst;
-            dst = tmp;
+        for (int j = 0; j < MCH; ++j) {
+            const int i = j * MWG + tid;
+            if (i >= M) continue;
+            const uint32_t q = sw[i] & 0xFFFu;
+            atomicOr((unsigned long long *)&bits[(i >> WB) * rw + (int)(q >> 6)], 1ull << (q & 63u));
         }
+        __syncthreads();
+        // each word's bits over the buckets (lane = bucket): the rows are
+        // disjoint, so the sums of the halves are their ORs
+        constexpr int NC = (NWD + NV - 1) / NV;        // columns per wave, at most
+        {
+            uint64_t v[NC];
+#pragma unroll
+            for (int q = 0; q < NC; ++q)
+                v[q] = wave + q * NV < nw && lane < nb ? bits[lane * rw + wave + q * NV] : 0ull;
+#pragma unroll
+            for (int q = 0; q < NC; ++q) {
+                const int w = wave + q * NV;
+                if (w >= nw) continue;
+                const uint64_t c = (uint64_t)wave_scan_u32((uint32_t)(v[q] >> 32)) << 32 | wave_scan_u32((uint32_t)v[q]);
+                if (lane < nb) {
+                    bits[lane * rw + w] = c;
+                    cnt[lane * rw + w] = (uint16_t)__popcll(c);
+                }
+            }
+        }
+        __syncthreads();
+        {
+            constexpr int NR = (NBK + NV - 1) / NV;    // rows per wave, at most (lane = word)
+            uint32_t c[NR];
+#pragma unroll
+            for (int q = 0; q < NR; ++q)
+                c[q] = wave + q * NV < nb && lane < nw ? cnt[(wave + q * NV) * rw + lane] : 0u;
+#pragma unroll
+            for (int q = 0; q < NR; ++q) {
+                const uint32_t inc = wave_scan_u32(c[q]);
+                if (wave + q * NV < nb && lane < nw) cnt[(wave + q * NV) * rw + lane] = (uint16_t)(inc - c[q]);
+            }
+        }
+        __syncthreads();
 
         // ---- median of each window: the h-th smallest rank (0-based) among
         // positions [a, a + W) of the union.  A thread's first window: the
-        // levels give its bucket and its index among the window's elements
-        // in the bucket; the bucket's 32 sorted elements are then tested
+        // matrix gives its bucket and its index among the window's elements
+        // in the bucket; the bucket's sorted elements are then tested
         // against the window.  Each next window of the thread is the
         // previous one moved by one position (or the same one, at a grid
         // edge): one element leaves, one enters, and the median stays or
         // becomes the nearest element above or below it in sorted order
         // whose position lies in the new window, found by walking the
-        // sorted words (at most SLIDE_MAX steps, else the levels again).
+        // sorted words (at most SLIDE_MAX steps, else the matrix again).
         // The sorted order is (fp64 value, position) in lexicographic
         // order, so comparisons with the median need no ranks.
-        auto rank0 = [&](int lvl, int x) -> int {      // zeros among positions < x
-            const WWord e = sm.u.wm.w[lvl][x >> 6];
-            const uint64_t m = ~e.bits & ((1ull << (x & 63)) - 1ull);
-            return (int)e.zpre + __popcll(m);
-        };
         auto query = [&](int a) -> int {               // sorted index of the median of [a, a + W)
-            int lo = a, hi = a + W, kk = h, base = 0;
-            for (int lvl = LB - 1; lvl >= WB; --lvl) {
-                const int Z = (int)sm.u.wm.zt[lvl];
-                const int zl = rank0(lvl, lo), zh = rank0(lvl, hi);
-                const int zeros = zh - zl;
-                if (kk < zeros) {
-                    lo = zl;
-                    hi = zh;
+            const int wa = a >> 6, we = (a + W) >> 6;
+            const uint64_t ma = (1ull << (a & 63)) - 1ull, me = (1ull << ((a + W) & 63)) - 1ull;
+            auto upto = [&](int b) -> int {            // the window's elements up to the end of bucket b
+                const int r = b * rw;
+                return (int)cnt[r + we] + __popcll(bits[r + we] & me) - (int)cnt[r + wa] - __popcll(bits[r + wa] & ma);
+            };
+            int lo = 0, hi = nb - 1, kk = h;           // the first bucket with more than h up to its end
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1, c = upto(mid);
+                if (c > h) {
+                    hi = mid;
                 } else {
-                    kk -= zeros;
-                    lo = Z + lo - zl;
-                    hi = Z + hi - zh;
-                    base |= 1 << lvl;
+                    lo = mid + 1;
+                    kk = h - c;
                 }
             }
-            // base: first rank of the bucket (MMAX is a multiple of 32)
-            uint32_t mask = 0;
-#pragma unroll
-            for (int i0 = 0; i0 < 32; i0 += 4) {
+            const int base = lo << WB;                 // 2^WB words: inside kp (MMAX is a multiple of 64)
+            uint64_t mask = 0;
+            for (int i0 = 0; i0 < (1 << WB); i0 += 4) {
                 const uint4 q4 = *reinterpret_cast<const uint4 *>(&sw[base + i0]);
                 const uint32_t qq[4] = {q4.x, q4.y, q4.z, q4.w};
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     const bool act = base + i0 + c < M && (qq[c] & 0xFFFu) - (uint32_t)a < (uint32_t)W;
-                    mask |= (uint32_t)act << (i0 + c);
+                    mask |= (uint64_t)act << (i0 + c);
                 }
             }
             // position of the (kk+1)-th set bit
             int pos = 0;
 #pragma unroll
-            for (int wdt = 16; wdt >= 1; wdt >>= 1) {
-                const int c = __popc(mask & ((1u << wdt) - 1u));
+            for (int wdt = 32; wdt >= 1; wdt >>= 1) {
+                const int c = __popcll(mask & ((1ull << wdt) - 1ull));
                 if (kk >= c) {
                     kk -= c;
                     mask >>= wdt;
@@ -1751,7 +1818,7 @@ DEVI void median_work(MedianSmem &sm, const Slot *slp, int blk, int span)
             const uint64_t bq = (uint64_t)__double_as_longlong(sm.xv[q]);
             return bp < bq || (bp == bq && p < q);
         };
-        constexpr int SLIDE_MAX = 32;
+        constexpr int SLIDE_MAX = 16, SLIDE_U = 4;
         int qm[RMAX];
         int ap = kb < ke ? win_start(min(kb, ke - 1), B, W, h) - u0 : 0;
         qm[0] = query(ap);
@@ -1776,12 +1843,13 @@ DEVI void median_work(MedianSmem &sm, const Slot *slp, int blk, int span)
                     // that entered, or the one below or above that took the
                     // median's place), so the walk stays inside [0, M)
                     int c = m, found = -1;
-                    for (int st = 0; st < SLIDE_MAX; ++st) {
-                        c += dir;
-                        if ((sw[c] & 0xFFFu) - (uint32_t)a < (uint32_t)W) {
-                            found = c;
-                            break;
-                        }
+                    for (int st = 0; st < SLIDE_MAX && found < 0; st += SLIDE_U, c += SLIDE_U * dir) {
+                        uint32_t w[SLIDE_U];           // past the ends: repeated, never taken
+#pragma unroll
+                        for (int u = 0; u < SLIDE_U; ++u) w[u] = sw[min(max(c + (u + 1) * dir, 0), M - 1)];
+#pragma unroll
+                        for (int u = SLIDE_U - 1; u >= 0; --u)
+                            if ((w[u] & 0xFFFu) - (uint32_t)a < (uint32_t)W) found = c + (u + 1) * dir;
                     }
                     m = found >= 0 ? found : query(a);
                 }
@@ -1793,9 +1861,31 @@ DEVI void median_work(MedianSmem &sm, const Slot *slp, int blk, int span)
         for (int r = 0; r < RMAX; ++r) med[r] = (kb + r < ke && r < R) ? sm.xv[sw[qm[r]] & 0xFFFu] : 0.0;
     }
 
-    // ---- S = C med + S_instr; in-tile prefix of 1/S and the tile sum.  The
-    // outputs pass through LDS so that global loads and stores are coalesced.
-    __syncthreads();                       // the wavelet matrix is dead: reuse it
+    // ---- S = C med + S_instr; in-part prefix of 1/S and the part sums.  With
+    // one output per thread, from registers
+    if (R == 1 && g.prec == PREC_FP64) {
+        const int lane = lane_id(), wave = tid >> 6;
+        const bool on = kb < ke;
+        const double Sk = g.C * med[0] + sxr[0], inv = on ? 1.0 / Sk : 0.0;
+        if (on) d.S[kb] = Sk;
+        const double inc = wave_incl_scan(inv);
+        double exw = __shfl_up(inc, 1, 64);
+        if (lane == 0) exw = 0.0;
+        if (lane == 63) sm.dsh[wave] = inc;
+        __syncthreads();
+        double pre = 0.0, tot = 0.0;                   // span is one part here
+#pragma unroll
+        for (int w = 0; w < MWG / 64; ++w) {
+            const double x = sm.dsh[w];
+            if (w < wave) pre += x;
+            if (w < span / 64) tot += x;
+        }
+        if (on) d.is_pre[kb] = (pre + exw) + inv;
+        if (tid == 0) d.is_psum[div_p2(t0, g.part)] = tot;
+        return;
+    }
+    // the outputs pass through LDS so that global loads and stores are coalesced
+    __syncthreads();                       // the bit matrix is dead: reuse it
     double *st = sm.u.stage;
     const int sc = g.prec == PREC_FP64 ? 0 : f32_scale(d.ctl->amax_bits, g.T);
     const int n = t1 - t0;
@@ -1803,13 +1893,16 @@ DEVI void median_work(MedianSmem &sm, const Slot *slp, int blk, int span)
     for (int r = 0; r < RMAX; ++r)
         if (kb + r < ke) st[kb + r - t0] = med[r];
     __syncthreads();
-    for (int i = tid; i < n; i += MWG) {
+#pragma unroll
+    for (int r = 0; r < RMAX; ++r) {
+        const int i = tid + r * MWG;
+        if (i >= n) continue;
         double Sk, inv;
         if (g.prec == PREC_FP64) {
-            Sk = g.C * st[i] + d.sx[t0 + i];
+            Sk = g.C * st[i] + sxr[r];
             inv = 1.0 / Sk;
         } else {                           // S and 1/S in fp32, scaled by 2^sc
-            const float sf = (float)g.C * (float)ldexp(st[i], sc) + (float)ldexp(d.sx[t0 + i], sc);
+            const float sf = (float)g.C * (float)ldexp(st[i], sc) + (float)ldexp(sxr[r], sc);
             Sk = ldexp((double)sf, -sc);
             inv = (double)(1.0f / sf);
         }
@@ -1848,14 +1941,15 @@ __global__ __launch_bounds__(MWG, 2) void k_median(const Slot *S)
     median_work(sm, &sl, blk, span);
 }
 
-// Not inlined: the listed launch loops over the tiles, and the loop must
-// not change the registers the work gets.
-__device__ __noinline__ void median_entry(MedianSmem &sm, const Slot *slp, int blk, int span)
-{
-    median_work(sm, slp, blk, span);
-}
-
-__global__ __launch_bounds__(MWG, 4) void k_median_listed(const Slot *S)
+// The launch of several slots (batches, the template model's two channels):
+// the dirty tiles come listed in tile order by the previous body's tail
+// (every tile for the first body) and each block takes an entry, so the
+// working blocks are dispatched first and a slot's clean tiles cost few
+// blocks: the grid holds the longest list a body can have, Dims::maxlist.
+// (A grid of 2048 blocks striding over the list had to call the work as a
+// function, with spilled registers: 42.7 instead of 39.3 us a launch of the
+// template model's 1e7 run.)
+__global__ __launch_bounds__(MWG, 2) void k_median_listed(const Slot *S)
 {
     __shared__ MedianSmem sm;
     const Slot &sl = S[blockIdx.y];
@@ -1863,21 +1957,13 @@ __global__ __launch_bounds__(MWG, 4) void k_median_listed(const Slot *S)
     const Grid g = sl.g;
     const Dev d = sl.d;
     if (d.ctl->done || d.ctl->bad) return;
-    // The launch of several slots (batches, the template model's two
-    // channels): the dirty tiles come listed in tile order by the previous
-    // body's tail (every tile for the first body), and a grid of at most
-    // MED_GRID blocks per slot strides over the list, so the working blocks
-    // are dispatched first and a slot's clean tiles cost no blocks.
     const bool split = d.ctl->med_split != 0;
     const int span = split ? g.part : g.tile;
-    const uint32_t n_ent = d.ctl->n_sdl * (split ? (uint32_t)g.np : 1u);
-    for (uint32_t e = blockIdx.x; e < n_ent; e += gridDim.x) {
-        const int tile = (int)d.sdl[split ? e / (uint32_t)g.np : e];
-        const int blk = split ? tile * g.np + (int)(e % (uint32_t)g.np) : tile;
-        if (blk * span >= g.B) continue;
-        median_entry(sm, &sl, blk, span);
-        __syncthreads();                   // LDS is reused by the next entry
-    }
+    const int e = blockIdx.x;
+    if (e >= (int)d.ctl->n_sdl * (split ? g.np : 1)) return;
+    const int tile = (int)d.sdl[split ? e / g.np : e];
+    const int blk = split ? tile * g.np + e % g.np : tile;
+    if (blk * span < g.B) median_work(sm, &sl, blk, span);
 }
 
 // ------------------------------------------------------------------ running mean
@@ -1968,13 +2054,7 @@ __global__ __launch_bounds__(MWG) void k_mean(const Slot *S)
     mean_work(sm, &sl, blk, span);
 }
 
-// Not inlined: the listed launch loops over the tiles, and the loop must
-// not change the registers the work gets.
-__device__ __noinline__ void mean_entry(MeanSmem &sm, const Slot *slp, int blk, int span)
-{
-    mean_work(sm, slp, blk, span);
-}
-
+// The launch of several slots, as k_median_listed.
 __global__ __launch_bounds__(MWG) void k_mean_listed(const Slot *S)
 {
     __shared__ MeanSmem sm;
@@ -1983,21 +2063,13 @@ __global__ __launch_bounds__(MWG) void k_mean_listed(const Slot *S)
     const Grid g = sl.g;
     const Dev d = sl.d;
     if (d.ctl->done || d.ctl->bad) return;
-    // The launch of several slots (batches, the template model's two
-    // channels): the dirty tiles come listed in tile order by the previous
-    // body's tail (every tile for the first body), and a grid of at most
-    // MED_GRID blocks per slot strides over the list, so the working blocks
-    // are dispatched first and a slot's clean tiles cost no blocks.
     const bool split = d.ctl->med_split != 0;
     const int span = split ? g.part : g.tile;
-    const uint32_t n_ent = d.ctl->n_sdl * (split ? (uint32_t)g.np : 1u);
-    for (uint32_t e = blockIdx.x; e < n_ent; e += gridDim.x) {
-        const int tile = (int)d.sdl[split ? e / (uint32_t)g.np : e];
-        const int blk = split ? tile * g.np + (int)(e % (uint32_t)g.np) : tile;
-        if (blk * span >= g.B) continue;
-        mean_entry(sm, &sl, blk, span);
-        __syncthreads();                   // LDS is reused by the next entry
-    }
+    const int e = blockIdx.x;
+    if (e >= (int)d.ctl->n_sdl * (split ? g.np : 1)) return;
+    const int tile = (int)d.sdl[split ? e / g.np : e];
+    const int blk = split ? tile * g.np + e % g.np : tile;
+    if (blk * span < g.B) mean_work(sm, &sl, blk, span);
 }
 
 // ------------------------------------------------------------------ SNR, decisions, subtraction
@@ -2500,10 +2572,9 @@ hipError_t launch_median(const Slot *ds, const Dims &dm, hipStream_t st, hipEven
 {
     const bool med = dm.est_mask & 1u, mean = dm.est_mask & 2u;
     hipError_t e = hipSuccess;
-    // one slot: a block per part; several: the listed launch (its blocks stride
-    // over each slot's dirty tiles)
+    // one slot: a block per part; several: the listed launch
     const bool listed = dm.ns > 1;
-    const unsigned gx = (unsigned)(listed ? min(dm.maxparts, MED_GRID) : dm.maxparts);
+    const unsigned gx = (unsigned)(listed ? dm.maxlist : dm.maxparts);
     const void *km = listed ? (const void *)k_median_listed : (const void *)k_median;
     const void *kn = listed ? (const void *)k_mean_listed : (const void *)k_mean;
     if (med) e = go(km, dim3(gx, dm.ns), dim3(MWG), st, ea, mean ? nullptr : eb, ds);
