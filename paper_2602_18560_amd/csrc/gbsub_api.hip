@@ -41,8 +41,8 @@ struct gbsub_ctx {
     void *tables_ws;
     Ctl *host_ctl;     // pinned
     Slot *host_slot;   // pinned staging of the one-slot table
-    uint32_t *host_prog;   // pinned, device-mapped: bodies finished << 1 | settled, written by the tail
-    uint32_t *dev_prog;    // the same word as the kernels address it
+    uint64_t *host_prog;   // pinned, device-mapped: the tail's progress word (Slot::prog)
+    uint64_t *dev_prog;    // the same word as the kernels address it
     int batch_slot;    // slot held in a batch, -1 if none
     // results of the last complex-template run
     bool cx_have_result;
@@ -511,8 +511,11 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
     const Dims dm = dims_of(*c->host_slot);
     // every kernel of an earlier run has ended (each return below follows a
     // synchronization once loop bodies are in flight)
-    volatile uint32_t *prog = c->host_prog;
+    volatile uint64_t *prog = c->host_prog;
     *prog = 0;
+    // bodies of two launches (k_median_next) from the first one whose dirty
+    // tiles fit the split budget
+    bool two = g.prec == PREC_FP64 && (uint32_t)g.nt <= g.split_tiles;
 
     c->ev_used = 0;
     c->recs.clear();
@@ -523,7 +526,7 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
     }
     if (e == hipSuccess) e = c->timed(K_RESET, -1, st, [&] { return launch_reset(ds, dm, st); });
     if (e == hipSuccess) e = c->timed(K_PREP, -1, st, [&] { return launch_prep(ds, dm, st); });
-    if (e == hipSuccess)
+    if (e == hipSuccess && !two)
         e = c->timed_ext(K_XUPDATE, -1, [&](hipEvent_t a, hipEvent_t b) { return launch_xupdate(ds, dm, st, a, b); });
     if (e != hipSuccess) {
         c->tables_ws = nullptr;
@@ -535,7 +538,9 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
     // waits for the host and at most AHEAD bodies run past the settled one
     // (their kernels exit at once).  The device enforces max_iter.  A body is
     // median, SNR, then the X update of the next body, whose last block
-    // takes this body's stop decision.  Whenever the stream runs dry without
+    // takes this body's stop decision; once few tiles are dirty (by the latest
+    // word), the X update and that decision are part of the next body's
+    // median launch.  Whenever the stream runs dry without
     // a settled flag in sight, the control block in device memory decides.
     constexpr uint64_t AHEAD = 2;
     const uint64_t guard = (uint64_t)cat->n + 2 + (c->cfg.max_iter ? c->cfg.max_iter : 0);
@@ -545,11 +550,11 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
     };
     auto body = [&](int64_t ti) {
         hipError_t r = c->timed_ext(K_MEDIAN, ti, [&](hipEvent_t a, hipEvent_t b) {
-            return launch_median(ds, dm, st, a, b);
+            return two ? launch_next(ds, dm, st, a, b) : launch_median(ds, dm, st, a, b);
         });
         if (r == hipSuccess)
             r = c->timed_ext(K_SNR, ti, [&](hipEvent_t a, hipEvent_t b) { return launch_snr(ds, dm, st, a, b); });
-        if (r == hipSuccess)
+        if (r == hipSuccess && !two)
             r = c->timed_ext(K_XUPDATE, ti, [&](hipEvent_t a, hipEvent_t b) {
                 return launch_xupdate(ds, dm, st, a, b);
             });
@@ -559,10 +564,11 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
     uint32_t seen_prev = 0;
     auto quiet_since = std::chrono::steady_clock::now();
     for (;;) {
-        const uint32_t w = *prog;
+        const uint64_t w = *prog;
         if (w & 1u) break;
-        const uint32_t seen = w >> 1;
+        const uint32_t seen = (uint32_t)w >> 1;
         if (t < (uint64_t)seen + AHEAD) {
+            two = two || (g.prec == PREC_FP64 && seen > 0 && (uint32_t)(w >> 32) <= g.split_tiles);
             if (t > guard) return fail(GBSUB_E_DEVICE);   // the loop must settle within n + 1 bodies
             if (body((int64_t)t) != hipSuccess) return fail(GBSUB_E_DEVICE);
             ++t;
@@ -829,8 +835,9 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
         sl.active = 1;
         c->host_cx_slots[ch] = sl;
     }
-    CxIn in{cat->A, cat->f, cat->fdot, cat->phi_a, cat->phi_e, cat->id, (uint32_t)cat->n, c->dev_prog};
-    volatile uint32_t *prog = c->host_prog;
+    CxIn in{cat->A, cat->f, cat->fdot, cat->phi_a, cat->phi_e, cat->id, (uint32_t)cat->n,
+            reinterpret_cast<uint32_t *>(c->dev_prog)};
+    volatile uint32_t *prog = reinterpret_cast<uint32_t *>(c->host_prog);
     *prog = 0;
     auto fail = [&](gbsub_status s) {
         (void)hipStreamSynchronize(st);

@@ -193,7 +193,8 @@ struct Slot {
     uint64_t n;
     uint32_t active;
     uint32_t pad;
-    uint32_t *prog;          // host-mapped word of a single run: bodies finished << 1 | settled (null in batches)
+    uint64_t *prog;          // host-mapped word of a single run: dirty tiles of the next body << 32 |
+                             // bodies finished << 1 | settled (null in batches)
 };
 
 // Launch extents: the largest per-slot block counts of a set of slots.
@@ -223,6 +224,9 @@ hipError_t launch_xupdate(const Slot *ds, const Dims &dm, hipStream_t st, hipEve
                           hipEvent_t eb = nullptr);
 hipError_t launch_median(const Slot *ds, const Dims &dm, hipStream_t st, hipEvent_t ea = nullptr,
                          hipEvent_t eb = nullptr);
+// X update, PSD and the previous body's tail in one launch (one FP64 slot).
+hipError_t launch_next(const Slot *ds, const Dims &dm, hipStream_t st, hipEvent_t ea = nullptr,
+                       hipEvent_t eb = nullptr);
 hipError_t launch_snr(const Slot *ds, const Dims &dm, hipStream_t st, hipEvent_t ea = nullptr,
                       hipEvent_t eb = nullptr);
 hipError_t launch_outputs(const Slot *ds, const Dims &dm, hipStream_t st);

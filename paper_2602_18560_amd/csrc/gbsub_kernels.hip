@@ -1503,7 +1503,104 @@ DEVI void part_prefix_ff(double *dsh, double *st, const Grid &g, const Dev &d, i
     }
 }
 
-// The work of one tile (or part) of a PSD launch.
+// Inclusive scan of 128-bit sums across the 64 lanes of a wave: x plus the sum
+// that the DPP pattern C moves in (rows outside R get zero).
+template <int C, int R> DEVI uint64_t dpp_u64(uint64_t v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, C, R, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), C, R, 0xF, false);
+    return (uint64_t)hi << 32 | lo;
+}
+
+template <int C, int R> DEVI I128 dpp_add(I128 x)
+{
+    I128 y;
+    y.lo = dpp_u64<C, R>(x.lo);
+    y.hi = (int64_t)dpp_u64<C, R>((uint64_t)x.hi);
+    return i128_add(x, y);
+}
+
+DEVI I128 wave_scan_i128(I128 x)
+{
+    x = dpp_add<0x111, 0xF>(x);                        // row_shr:1, 2, 4, 8
+    x = dpp_add<0x112, 0xF>(x);
+    x = dpp_add<0x114, 0xF>(x);
+    x = dpp_add<0x118, 0xF>(x);
+    x = dpp_add<0x142, 0xA>(x);                        // row_bcast:15, 31
+    return dpp_add<0x143, 0xC>(x);
+}
+
+// X over the union [u0, u1] of the windows of one part straight from the
+// accumulators, X = 2^L (Xn + prefix(D)), for the launches that convert and
+// filter at once: xr[i] = X of bin u0 + threadIdx.x + i MWG.  The sums are
+// exact integers, so one prefix from the first tile's carry serves every
+// tile of the union, and a converted bin equals what k_xupdate stores.  D
+// goes through `st`, LDS of FST entries that may overlap anything else (the
+// last barrier is past its last read): read in bin order, summed in runs of
+// consecutive bins.  A part's range from its first tile's start is at most
+// tile - 1 + part + W - 1 <= MMAX - 1 + PART_MAX bins.
+constexpr int FCH = (MMAX - 1 + PART_MAX + MWG - 1) / MWG;   // bins per thread, at most (odd)
+constexpr int FST = MMAX + PART_MAX;
+DEVI void fresh_union(const Grid &g, const Dev &d, int u0, int u1, I128 *st, double (&xr)[MCH])
+{
+    __shared__ I128 sh[MWG / 64];
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    const int tl = div_p2(u0, g.tile), first = tl * g.tile, len = u1 + 1 - first;
+    const int CH = ((len + MWG - 1) / MWG) | 1;             // odd: a run's reads spread over the banks
+    I128 v[FCH], xn[MCH];
+#pragma unroll
+    for (int i = 0; i < FCH; ++i)
+        if (i * MWG < len) v[i] = d.D[first + min(tid + i * MWG, len - 1)];
+#pragma unroll
+    for (int i = 0; i < MCH; ++i)
+        if (u0 + i * MWG <= u1) xn[i] = d.Xn[min(u0 + tid + i * MWG, u1)];
+    const I128 carry = i128_add(d.Dcarry[tl], split_sum_value(d.Dadj[tl]));
+    const int L = fx_exp(d.ctl->amax_bits, g.T);
+#pragma unroll
+    for (int i = 0; i < FCH; ++i)
+        if (tid + i * MWG < len) st[tid + i * MWG] = v[i];
+    __syncthreads();
+    const int k0 = tid * CH;
+    I128 s = zero_t<I128>();
+#pragma unroll
+    for (int i = 0; i < FCH; ++i) {
+        v[i] = zero_t<I128>();
+        if (i < CH && k0 + i < len) v[i] = st[k0 + i];
+        s = i128_add(s, v[i]);
+    }
+    const I128 inc = wave_scan_i128(s);
+    if (lane == 63) sh[wave] = inc;
+    __syncthreads();
+    // exclusive: the waves before, and inc - s
+    I128 run = carry;
+#pragma unroll
+    for (int w = 0; w < MWG / 64; ++w) {
+        const I128 x = sh[w];
+        if (w < wave) run = i128_add(run, x);
+    }
+    run = i128_add(run, inc);
+    I128 neg;
+    neg.lo = ~s.lo + 1;
+    neg.hi = (int64_t)(~(uint64_t)s.hi + (neg.lo == 0));
+    run = i128_add(run, neg);
+#pragma unroll
+    for (int i = 0; i < FCH; ++i) {
+        run = i128_add(run, v[i]);
+        if (i < CH && k0 + i < len) st[k0 + i] = run;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < MCH; ++i) {
+        const int k = u0 + tid + i * MWG;
+        if (k <= u1) xr[i] = ldexp(i128_to_double(i128_add(st[k - first], xn[i])), L);
+    }
+    __syncthreads();
+}
+
+// The work of one tile (or part) of a PSD launch.  FRESH: X comes from
+// the accumulators (fresh_union); the block stores the bins of its own outputs
+// where their tile's X has changed.
+template <bool FRESH>
 DEVI void median_work(MedianSmem &sm, const Slot *slp, int blk, int span)
 {
     const Grid g = slp->g;
@@ -1518,16 +1615,27 @@ DEVI void median_work(MedianSmem &sm, const Slot *slp, int blk, int span)
     const int M = u1 - u0 + 1;
 
     // ---- load the union and the outputs' S_instr (all loads in flight
-    // together); tile min / max
+    // together); bounds of the positive values, from the high words of the
+    // fp64 patterns
     double xr[MCH], sxr[RMAX];
 #pragma unroll
     for (int r = 0; r < RMAX; ++r) sxr[r] = d.sx[min(t0 + tid + r * MWG, t1 - 1)];
+    if constexpr (FRESH) {
+        static_assert(FST * sizeof(I128) <= sizeof(MedianSmem), "fresh_union's LDS");
+        const bool store = d.xstamp[div_p2(t0, g.tile)] == d.ctl->xupd;
+        fresh_union(g, d, u0, u1, reinterpret_cast<I128 *>(&sm), xr);
 #pragma unroll
-    for (int i = 0; i < MCH; ++i) {
-        const int p = tid + i * MWG;
-        xr[i] = p < M ? d.X[u0 + p] : 0.0;
+        for (int i = 0; i < MCH; ++i) {
+            const int k = u0 + tid + i * MWG;
+            if (store && k >= t0 && k < t1) d.X[k] = xr[i];
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < MCH; ++i) {
+            const int p = tid + i * MWG;
+            xr[i] = p < M ? d.X[u0 + p] : 0.0;
+        }
     }
-    // bounds of the positive values, from the high words of the fp64 patterns
     uint32_t mn32 = ~0u, mx32 = 0;
 #pragma unroll
     for (int i = 0; i < MCH; ++i) {
@@ -1938,7 +2046,38 @@ __global__ __launch_bounds__(MWG, 2) void k_median(const Slot *S)
     const int blk = blockIdx.x;
     const int tile = split ? blk / g.np : blk;
     if (tile >= g.nt || blk * span >= g.B || d.sstamp[tile] != d.ctl->iter) return;
-    median_work(sm, &sl, blk, span);
+    median_work<false>(sm, &sl, blk, span);
+}
+
+// A body's X update, PSD and the previous body's tail in one launch (one
+// slot, FP64, few dirty tiles): block 0 is the tail of the k_snr before it,
+// the others take a part each, convert its union from the accumulators and
+// filter it.  They touch disjoint data: the blocks read the accumulators, the
+// stamps and the control fields set before the launch (xupd, the stamp of this
+// body, among them) and write X, S and the prefixes of their own parts; the
+// tail reads the partials and stamps and writes the counters, flags and list.
+// Past the settled body no tile carries the stamp.  An empty launch costs
+// 4.5 us and k_xupdate's late ones 9.5; the conversion adds 3 us to a part's
+// chain, so a late body of the 1e7 catalog takes 29 us instead of 35 (median
+// 17, SNR 8.5, X update 9.5), and one of the running mean 19 instead of 26.  A
+// part reads 32 bytes of accumulators per bin, from its first tile's start,
+// where the two launches read 8 of X; taken while the dirty tiles fit the
+// split budget (at most one wave of part-sized blocks on the chip), where the
+// launch is latency, not traffic.
+template <int NT> DEVI void snr_tail(const Slot &sl);
+__global__ __launch_bounds__(MWG, 4) void k_median_next(const Slot *S)
+{
+    __shared__ MedianSmem sm;
+    const Slot &sl = *S;
+    if (blockIdx.x == 0) {
+        snr_tail<MWG>(sl);
+        return;
+    }
+    const Grid g = sl.g;
+    const Dev d = sl.d;
+    const int blk = blockIdx.x - 1;
+    if (d.ctl->bad || d.sstamp[blk / g.np] != d.ctl->xupd) return;
+    median_work<true>(sm, &sl, blk, g.part);
 }
 
 // The launch of several slots (batches, the template model's two channels):
@@ -1963,7 +2102,7 @@ __global__ __launch_bounds__(MWG, 2) void k_median_listed(const Slot *S)
     if (e >= (int)d.ctl->n_sdl * (split ? g.np : 1)) return;
     const int tile = (int)d.sdl[split ? e / g.np : e];
     const int blk = split ? tile * g.np + e % g.np : tile;
-    if (blk * span < g.B) median_work(sm, &sl, blk, span);
+    if (blk * span < g.B) median_work<false>(sm, &sl, blk, span);
 }
 
 // ------------------------------------------------------------------ running mean
@@ -1980,7 +2119,8 @@ struct MeanSmem {
 };
 
 // The work of one tile (or part) of a PSD launch.
-DEVI void mean_work(MeanSmem &sm, const Slot *slp, int blk, int span)
+template <bool FRESH>
+DEVI void mean_work(MeanSmem &sm, const Slot *slp, int blk, int span, I128 *st = nullptr)
 {
     const Grid g = slp->g;
     const Dev d = slp->d;
@@ -1993,7 +2133,20 @@ DEVI void mean_work(MeanSmem &sm, const Slot *slp, int blk, int span)
     const int u1 = whole ? B - 1 : win_start(t1 - 1, B, W, h) + W - 1;
     const int M = u1 - u0 + 1;
 
-    for (int p = tid; p < M; p += MWG) sm.v[p] = d.X[u0 + p] + d.sx[u0 + p];
+    if constexpr (FRESH) {
+        const bool store = d.xstamp[div_p2(t0, g.tile)] == d.ctl->xupd;
+        double xr[MCH];
+        fresh_union(g, d, u0, u1, st, xr);
+#pragma unroll
+        for (int i = 0; i < MCH; ++i) {
+            const int p = tid + i * MWG;
+            if (p >= M) continue;
+            sm.v[p] = xr[i] + d.sx[u0 + p];
+            if (store && u0 + p >= t0 && u0 + p < t1) d.X[u0 + p] = xr[i];
+        }
+    } else {
+        for (int p = tid; p < M; p += MWG) sm.v[p] = d.X[u0 + p] + d.sx[u0 + p];
+    }
     __syncthreads();
     // inclusive prefix over the union: thread-contiguous runs
     const int ch = (M + MWG - 1) / MWG;
@@ -2051,7 +2204,26 @@ __global__ __launch_bounds__(MWG) void k_mean(const Slot *S)
     const int blk = blockIdx.x;
     const int tile = split ? blk / g.np : blk;
     if (tile >= g.nt || blk * span >= g.B || d.sstamp[tile] != d.ctl->iter) return;
-    mean_work(sm, &sl, blk, span);
+    mean_work<false>(sm, &sl, blk, span);
+}
+
+// As k_median_next.
+__global__ __launch_bounds__(MWG) void k_mean_next(const Slot *S)
+{
+    __shared__ union {
+        MeanSmem mean;
+        I128 st[FST];
+    } sm;
+    const Slot &sl = *S;
+    if (blockIdx.x == 0) {
+        snr_tail<MWG>(sl);
+        return;
+    }
+    const Grid g = sl.g;
+    const Dev d = sl.d;
+    const int blk = blockIdx.x - 1;
+    if (d.ctl->bad || d.sstamp[blk / g.np] != d.ctl->xupd) return;
+    mean_work<true>(sm.mean, &sl, blk, g.part, sm.st);
 }
 
 // The launch of several slots, as k_median_listed.
@@ -2069,7 +2241,7 @@ __global__ __launch_bounds__(MWG) void k_mean_listed(const Slot *S)
     if (e >= (int)d.ctl->n_sdl * (split ? g.np : 1)) return;
     const int tile = (int)d.sdl[split ? e / g.np : e];
     const int blk = split ? tile * g.np + e % g.np : tile;
-    if (blk * span < g.B) mean_work(sm, &sl, blk, span);
+    if (blk * span < g.B) mean_work<false>(sm, &sl, blk, span);
 }
 
 // ------------------------------------------------------------------ SNR, decisions, subtraction
@@ -2491,10 +2663,12 @@ template <int NT> DEVI void snr_tail(const Slot &sl)
         c->units_med = k.units_med + us;
     }
     c->done = done;
-    // progress for the host that paces the launches: bodies finished and the
-    // settled flag in one word, so that the host never sees one without the other
+    // progress for the host that paces the launches: the next body's dirty
+    // tiles, the bodies finished and the settled flag in one word, so that the
+    // host never sees one without the others
     if (sl.prog)
-        __hip_atomic_store(sl.prog, nxt << 1 | done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(sl.prog, (uint64_t)listed << 32 | nxt << 1 | done, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The tail as a kernel of its own, ahead of k_xupdate: the naive FP32 mode
@@ -2580,6 +2754,12 @@ hipError_t launch_median(const Slot *ds, const Dims &dm, hipStream_t st, hipEven
     if (med) e = go(km, dim3(gx, dm.ns), dim3(MWG), st, ea, mean ? nullptr : eb, ds);
     if (mean && e == hipSuccess) e = go(kn, dim3(gx, dm.ns), dim3(MWG), st, med ? nullptr : ea, eb, ds);
     return e;
+}
+
+hipError_t launch_next(const Slot *ds, const Dims &dm, hipStream_t st, hipEvent_t ea, hipEvent_t eb)
+{
+    const void *k = dm.est_mask & 2u ? (const void *)k_mean_next : (const void *)k_median_next;
+    return go(k, dim3(dm.maxparts + 1), dim3(MWG), st, ea, eb, ds);
 }
 
 hipError_t launch_snr(const Slot *ds, const Dims &dm, hipStream_t st, hipEvent_t ea, hipEvent_t eb)
