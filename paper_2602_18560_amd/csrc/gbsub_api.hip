@@ -695,19 +695,42 @@ gbsub_status gbsub_coarse(const gbsub_ctx *c, uint32_t kind, double f_lo, double
         !(f_hi > f_lo) || !std::isfinite(f_hi))
         return GBSUB_E_INVALID;
     if (hipSetDevice(c->device) != hipSuccess) return GBSUB_E_DEVICE;
-    CoarseEdges ed;
-    for (uint32_t j = 0; j <= n_out; ++j) ed.e[j] = f_lo * std::pow(f_hi / f_lo, (double)j / (double)n_out);
-    ed.e[n_out] = f_hi;
     const Grid &g = c->g;
-    hipError_t e = launch_coarse(c->dev.S, c->dev.sx, c->dev.X, (int)kind, g.k0, g.B, g.T, ed, (int)n_out,
-                                 c->dev.coarse, nullptr);
-    std::vector<double> h(3 * (size_t)n_out);
-    if (e == hipSuccess) e = hipMemcpy(h.data(), c->dev.coarse, h.size() * 8, hipMemcpyDeviceToHost);
+    // edges e_j in fp64; a bin starts at the first sample with f_i >= e_j (the
+    // last one ends past f_i = e_n), near e_j T - k0
+    CoarseEdges ed;
+    for (uint32_t j = 0; j <= n_out; ++j) {
+        const double x = j == n_out ? f_hi : f_lo * std::pow(f_hi / f_lo, (double)j / (double)n_out);
+        auto past = [&](int i) {
+            const double f = (double)(g.k0 + i) / g.T;
+            return j == n_out ? f > x : f >= x;
+        };
+        const double at = x * g.T - (double)g.k0;
+        int i = at > 0.0 ? (at < (double)g.B ? (int)at : g.B) : 0;
+        while (i > 0 && past(i - 1)) --i;
+        while (i < g.B && !past(i)) ++i;
+        ed.i[j] = i;
+    }
+    // long grids: each bin in several shares, whose sums go to the in-part 1/S
+    // prefixes, dead once a run has settled (COARSE_BIN samples per bin, so the
+    // shares' three sums each fit)
+    const int ns = (int64_t)n_out * COARSE_BIN <= (int64_t)g.B ? std::max(1, COARSE_GRID / (int)n_out) : 1;
+    double *sums = ns > 1 ? c->dev.is_pre : c->dev.coarse;
+    hipError_t e = launch_coarse(c->dev.S, c->dev.sx, c->dev.X, (int)kind, g.k0, g.B, g.T, ed, (int)n_out, ns, sums,
+                                 nullptr);
+    std::vector<double> h(3 * (size_t)n_out * ns);
+    if (e == hipSuccess) e = hipMemcpy(h.data(), sums, h.size() * 8, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return GBSUB_E_DEVICE;
     for (uint32_t k = 0; k < n_out; ++k) {
-        const double cnt = h[3 * k + 2];
-        const double fm = cnt > 0 ? h[3 * k] / cnt : 0.0;
-        const double sm = cnt > 0 ? h[3 * k + 1] / cnt : 0.0;
+        double f = 0.0, v = 0.0, cnt = 0.0;
+        for (int q = 0; q < ns; ++q) {
+            const double *o = &h[3 * ((size_t)k * ns + q)];
+            f += o[0];
+            v += o[1];
+            cnt += o[2];
+        }
+        const double fm = cnt > 0 ? f / cnt : 0.0;
+        const double sm = cnt > 0 ? v / cnt : 0.0;
         f_out[k] = fm;
         s_out[k] = sm;
         if (hc_out) hc_out[k] = std::sqrt(fm * sm);

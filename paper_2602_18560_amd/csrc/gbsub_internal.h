@@ -24,6 +24,8 @@ constexpr int KEYBITS = 18;        // bits of the per-tile order key of the medi
 constexpr int POSBITS = 12;        // sort word = key << 12 | position (MMAX <= 4096)
 enum Prec { PREC_FP64 = 0, PREC_COMP = 1, PREC_NAIVE = 2 };   // Grid::prec (= gbsub_config precision)
 constexpr int COARSE_MAX = 256;    // coarse-graining bins at most
+constexpr int COARSE_GRID = 1024;  // blocks of a coarse-graining launch: shares of the bins, about
+constexpr int COARSE_BIN = 1024;   // grid samples per coarse-graining bin from which the bins are shared
 constexpr int PART_MAX = 512;      // outputs of a median block in split mode (prefix-of-1/S granule)
 constexpr int SPLIT_BLOCKS = 512;  // split the median into parts while dirty tiles x parts fit this
 
@@ -314,7 +316,8 @@ hipError_t cx_launch_h(const Grid &g, const CxDev &d, uint32_t n, int ch, double
 hipError_t cx_launch_templates(const Grid &g, const float *A, const float *F, const float *FD, uint32_t n,
                                int64_t *q, double *U, hipStream_t st);
 
-struct CoarseEdges { double e[COARSE_MAX + 1]; };
+// First grid sample of each coarse-graining bin; the last entry ends the last bin.
+struct CoarseEdges { int32_t i[COARSE_MAX + 1]; };
 
 // Population hyperparameters of a generator launch (gbsub_population).
 struct PopParams {
@@ -324,9 +327,9 @@ struct PopParams {
 // columns A, F, FD and (if non-null) the ids (gbsub_population.hip).
 hipError_t launch_generate(const PopParams &pp, uint64_t seed, uint64_t first, uint64_t n, float *A, float *F,
                            float *FD, uint32_t *id, hipStream_t st);
-// Sums of f_i and of the chosen spectrum over each logarithmic bin
-// [e_k, e_{k+1}) (the last bin closed) into out[3k .. 3k+2] = (sum f, sum v, count).
+// Sums of f_i and of the chosen spectrum over each bin of `ed`, in ns shares:
+// out[3 (k ns + s) ..] = (sum f, sum v, count) of share s of bin k.
 hipError_t launch_coarse(const double *S, const double *sx, const double *X, int kind, int64_t k0, int B,
-                         double T, const CoarseEdges &ed, int n_out, double *out, hipStream_t st);
+                         double T, const CoarseEdges &ed, int n_out, int ns, double *out, hipStream_t st);
 
 }  // namespace gbs
