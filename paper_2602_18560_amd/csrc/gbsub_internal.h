@@ -17,6 +17,7 @@ constexpr int COOP_PARTS = 8;      // tracks over more parts: the part sums are 
 constexpr int PREP_SRC = 4096;     // sources per block of the prep passes (count and scatter)
 constexpr int SEG_BINS = 128;      // bins per segment of the 1/S_instr bounds of the candidate test
 constexpr int CS_WG = 1024;        // threads of a column-pass block (64 tiles, 16 waves over the blocks)
+constexpr int ACC_T = 512;         // threads of an accumulation block
 constexpr int ACC_EV = 65536;      // binning events per accumulation block
 constexpr int RED_BINS = 256;      // bins per reduction block of the hot buckets
 constexpr int NEW_CAP = 1 << 16;   // per-iteration counters kept (iterations beyond: not recorded)

@@ -897,16 +897,16 @@ DEVI I128 split_total(const SplitAcc &a, int k)
 // the chunk's partial-sum slot of a hot tile.
 DEVI void accum_comp(const Grid &g, const Dev &d, int b, uint32_t ci, uint32_t e0, uint32_t e1, FF *xc, FF *dc)
 {
-    __shared__ FF shf[WG / 64];
+    __shared__ FF shf[ACC_T / 64];
     const int k0 = b * g.tile;
     const int L = fx_exp(d.ctl->amax_bits, g.T);
     const int sc = f32_scale(d.ctl->amax_bits, g.T);
-    for (int k = threadIdx.x; k < g.tile; k += WG) {
+    for (int k = threadIdx.x; k < g.tile; k += ACC_T) {
         xc[k] = ff_of(0.0f);
         dc[k] = ff_of(0.0f);
     }
     __syncthreads();
-    for (uint32_t e = e0 + threadIdx.x; e < e1; e += WG) {
+    for (uint32_t e = e0 + threadIdx.x; e < e1; e += ACC_T) {
         const uint32_t key = d.ev_key[e];
         const float v = (float)ldexp((double)d.ev_val[e], L + sc);
         const int k = (int)(key & 0x7FFFFFFFu) - k0;
@@ -916,7 +916,7 @@ DEVI void accum_comp(const Grid &g, const Dev &d, int b, uint32_t ci, uint32_t e
     const int nbin = min(g.tile, g.B - k0);
     if (d.nch[b] == 1) {
         FF s = ff_of(0.0f);
-        for (int k = threadIdx.x; k < g.tile; k += WG) {
+        for (int k = threadIdx.x; k < g.tile; k += ACC_T) {
             if (k < nbin) {
                 const FF x = ff_norm(xc[k].hi, xc[k].lo), y = ff_norm(dc[k].hi, dc[k].lo);
                 d.Xc[k0 + k] = x;
@@ -925,21 +925,21 @@ DEVI void accum_comp(const Grid &g, const Dev &d, int b, uint32_t ci, uint32_t e
             }
         }
         FF tot;
-        block_excl_scan(s, shf, &tot);
+        block_excl_scan<FF, ACC_T>(s, shf, &tot);
         if (threadIdx.x == 0) d.Dtc[b] = tot;
     } else {
         FF *slot = reinterpret_cast<FF *>(d.partial + (size_t)(d.slot_base[b] + ci) * 2 * g.tile);
-        for (int k = threadIdx.x; k < g.tile; k += WG) {
+        for (int k = threadIdx.x; k < g.tile; k += ACC_T) {
             slot[k] = ff_norm(xc[k].hi, xc[k].lo);
             slot[g.tile + k] = ff_norm(dc[k].hi, dc[k].lo);
         }
     }
 }
 
-__global__ __launch_bounds__(WG) void k_accum(const Slot *S)
+__global__ __launch_bounds__(ACC_T) void k_accum(const Slot *S)
 {
     __shared__ SplitAcc xn, dd;
-    __shared__ I128 sh[WG / 64];
+    __shared__ I128 sh[ACC_T / 64];
     const Slot &sl = S[blockIdx.y];
     if (!sl.active) return;
     const Grid g = sl.g;
@@ -962,24 +962,28 @@ __global__ __launch_bounds__(WG) void k_accum(const Slot *S)
         accum_comp(g, d, b, ci, e0, e1, reinterpret_cast<FF *>(xn.h), reinterpret_cast<FF *>(dd.h));
         return;
     }
-    for (int k = threadIdx.x; k < g.tile; k += WG) {
+    for (int k = threadIdx.x; k < g.tile; k += ACC_T) {
         xn.h[k] = 0; xn.l[k] = 0;
         dd.h[k] = 0; dd.l[k] = 0;
     }
     __syncthreads();
-    // four events per thread in flight
-    for (uint32_t e = e0 + threadIdx.x; e < e1; e += 4 * WG) {
-        uint32_t key[4];
-        int64_t v[4];
+    // AU events per thread in flight.  A hot tile's 65536 events are the whole
+    // launch of a small catalog: 25 us with 512 threads and 8 events each in
+    // flight, 51 with 256 and 4 (1e7 sources 57 and 91); 1024 threads leave one
+    // block per CU, 27 and 69 us
+    constexpr int AU = 8;
+    for (uint32_t e = e0 + threadIdx.x; e < e1; e += AU * ACC_T) {
+        uint32_t key[AU];
+        int64_t v[AU];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const uint32_t ee = e + (uint32_t)(q * WG);
-            key[q] = ee < e1 ? d.ev_key[ee] : 0u;
-            v[q] = ee < e1 ? d.ev_val[ee] : 0;
+        for (int q = 0; q < AU; ++q) {
+            const uint32_t ee = min(e + (uint32_t)(q * ACC_T), e1 - 1u);
+            key[q] = d.ev_key[ee];
+            v[q] = d.ev_val[ee];
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (e + (uint32_t)(q * WG) >= e1) continue;
+        for (int q = 0; q < AU; ++q) {
+            if (e + (uint32_t)(q * ACC_T) >= e1) continue;
             const int k = (int)(key[q] & 0x7FFFFFFFu) - k0;
             split_add((key[q] >> 31) ? dd : xn, k, v[q]);
         }
@@ -988,7 +992,7 @@ __global__ __launch_bounds__(WG) void k_accum(const Slot *S)
     const int nbin = min(g.tile, g.B - k0);
     if (d.nch[b] == 1) {
         I128 s = zero_t<I128>();
-        for (int k = threadIdx.x; k < g.tile; k += WG) {
+        for (int k = threadIdx.x; k < g.tile; k += ACC_T) {
             if (k < nbin) {
                 const I128 dk = split_total(dd, k);
                 d.Xn[k0 + k] = split_total(xn, k);
@@ -997,11 +1001,11 @@ __global__ __launch_bounds__(WG) void k_accum(const Slot *S)
             }
         }
         I128 tot;
-        block_excl_scan(s, sh, &tot);
+        block_excl_scan<I128, ACC_T>(s, sh, &tot);
         if (threadIdx.x == 0) d.Dtile[b] = tot;
     } else {
         I128 *slot = d.partial + (size_t)(d.slot_base[b] + ci) * 2 * g.tile;
-        for (int k = threadIdx.x; k < g.tile; k += WG) {
+        for (int k = threadIdx.x; k < g.tile; k += ACC_T) {
             slot[k] = split_total(xn, k);
             slot[g.tile + k] = split_total(dd, k);
         }
@@ -2720,7 +2724,7 @@ hipError_t launch_prep(const Slot *ds, const Dims &dm, hipStream_t st)
     k_prep_colscan<<<dim3((dm.maxnt + 63) / 64, dm.ns), CS_WG, 0, st>>>(ds);
     k_prep_plan<<<dim3(1, dm.ns), WG, 0, st>>>(ds);
     if (dm.prep_blocks > 0) k_prep_scatter<<<dim3(dm.prep_blocks, dm.ns), WG, 0, st>>>(ds);
-    k_accum<<<dim3(dm.accum_blocks, dm.ns), WG, 0, st>>>(ds);
+    k_accum<<<dim3(dm.accum_blocks, dm.ns), ACC_T, 0, st>>>(ds);
     k_accum_reduce<<<dim3(dm.maxnt * (dm.maxtile / RED_BINS), dm.ns), RED_BINS, 0, st>>>(ds);
     if (dm.naive) k_accum_f32<<<dim3(2048, dm.ns), WG, 0, st>>>(ds);
     k_dscan<<<dim3(1, dm.ns), WG, 0, st>>>(ds);
