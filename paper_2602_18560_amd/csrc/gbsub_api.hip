@@ -26,6 +26,14 @@
 
 using namespace gbs;
 
+// Results that kernels write straight to host memory: a copy after a kernel
+// costs its own launch and a round trip.
+struct HostOut {
+    alignas(64) uint64_t prog;             // the tail's progress word (Slot::prog)
+    alignas(64) Ctl ctl;                   // the control block of a finished run
+    CoarseSum coarse[COARSE_GRID];
+};
+
 struct gbsub_ctx {
     gbsub_config cfg;
     Grid g;
@@ -40,16 +48,14 @@ struct gbsub_ctx {
     // the S_instr tables in `tables_ws` were computed for this grid
     void *tables_ws;
     Ctl *host_ctl;     // pinned
-    Slot *host_slot;   // pinned staging of the one-slot table
-    uint64_t *host_prog;   // pinned, device-mapped: the tail's progress word (Slot::prog)
-    uint64_t *dev_prog;    // the same word as the kernels address it
+    HostOut *host_out;     // pinned, device-mapped, coherent: what kernels write for the host
+    HostOut *dev_out;      // the same memory as the kernels address it
     int batch_slot;    // slot held in a batch, -1 if none
     // results of the last complex-template run
     bool cx_have_result;
     CxDev cx;
     gbsub_summary cx_summ;
     uint32_t cx_n;
-    Slot *host_cx_slots;   // pinned staging of the two channel descriptors
     // profiling: bit k of `profiling` selects kernel family k
     uint32_t profiling;
     struct Rec { int kid; int64_t t; hipEvent_t a, b; };
@@ -181,7 +187,6 @@ uint64_t carve(const Grid &g, uint64_t n, char *base, Dev *d)
     t.c_rho2 = (double *)take(nn * 8);
     t.b_part = (SnrPart *)take((uint64_t)SNR_BLOCKS * sizeof(SnrPart));
     t.n_new = (uint32_t *)take((uint64_t)NEW_CAP * 4);
-    t.coarse = (double *)take(3 * COARSE_MAX * 8);
     t.ctl = (Ctl *)take(sizeof(Ctl));
     if (d) *d = t;
     return off;
@@ -443,26 +448,21 @@ gbsub_status gbsub_create(const gbsub_config *cfg, gbsub_ctx **out)
     c->ws = nullptr;
     c->tables_ws = nullptr;
     c->host_ctl = nullptr;
-    c->host_slot = nullptr;
-    c->host_prog = nullptr;
-    c->dev_prog = nullptr;
+    c->host_out = nullptr;
+    c->dev_out = nullptr;
     c->batch_slot = -1;
     c->cx_have_result = false;
     c->cx_n = 0;
     c->res_n = 0;
-    c->host_cx_slots = nullptr;
     c->profiling = 0;
     c->ev_used = 0;
     c->clear_stats();
     if (hipHostMalloc((void **)&c->host_ctl, sizeof(Ctl), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&c->host_slot, sizeof(Slot), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&c->host_cx_slots, 2 * sizeof(Slot), hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&c->host_prog, 64, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
-        hipHostGetDevicePointer((void **)&c->dev_prog, c->host_prog, 0) != hipSuccess) {
+        hipHostMalloc((void **)&c->host_out, sizeof(HostOut), hipHostMallocMapped | hipHostMallocCoherent) !=
+            hipSuccess ||
+        hipHostGetDevicePointer((void **)&c->dev_out, c->host_out, 0) != hipSuccess) {
         if (c->host_ctl) (void)hipHostFree(c->host_ctl);
-        if (c->host_slot) (void)hipHostFree(c->host_slot);
-        if (c->host_cx_slots) (void)hipHostFree(c->host_cx_slots);
-        if (c->host_prog) (void)hipHostFree(c->host_prog);
+        if (c->host_out) (void)hipHostFree(c->host_out);
         delete c;
         return GBSUB_E_DEVICE;
     }
@@ -479,9 +479,7 @@ void gbsub_destroy(gbsub_ctx *c)
 {
     if (!c) return;
     if (c->host_ctl) (void)hipHostFree(c->host_ctl);
-    if (c->host_slot) (void)hipHostFree(c->host_slot);
-    if (c->host_cx_slots) (void)hipHostFree(c->host_cx_slots);
-    if (c->host_prog) (void)hipHostFree(c->host_prog);
+    if (c->host_out) (void)hipHostFree(c->host_out);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     delete c;
 }
@@ -506,12 +504,13 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
     carve(c->g, cat->n, (char *)ws, &d);
     const Grid &g = c->g;
     Slot *ds = reinterpret_cast<Slot *>(ws);    // one-slot table at the start of the workspace
-    *c->host_slot = make_slot(g, d, cat);
-    c->host_slot->prog = c->dev_prog;
-    const Dims dm = dims_of(*c->host_slot);
+    Slot slot = make_slot(g, d, cat);
+    slot.prog = &c->dev_out->prog;
+    slot.host_ctl = &c->dev_out->ctl;
+    const Dims dm = dims_of(slot);
     // every kernel of an earlier run has ended (each return below follows a
     // synchronization once loop bodies are in flight)
-    volatile uint64_t *prog = c->host_prog;
+    volatile uint64_t *prog = &c->host_out->prog;
     *prog = 0;
     // bodies of two launches (k_median_next) from the first one whose dirty
     // tiles fit the split budget
@@ -519,12 +518,11 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
 
     c->ev_used = 0;
     c->recs.clear();
-    hipError_t e = hipMemcpyAsync(ds, c->host_slot, sizeof(Slot), hipMemcpyHostToDevice, st);
+    hipError_t e = c->timed(K_RESET, -1, st, [&] { return launch_reset(ds, slot, st); });
     if (e == hipSuccess && c->tables_ws != ws) {
         e = c->timed(K_TABLES, -1, st, [&] { return launch_grid_tables(ds, dm, st); });
         if (e == hipSuccess) c->tables_ws = ws;
     }
-    if (e == hipSuccess) e = c->timed(K_RESET, -1, st, [&] { return launch_reset(ds, dm, st); });
     if (e == hipSuccess) e = c->timed(K_PREP, -1, st, [&] { return launch_prep(ds, dm, st); });
     if (e == hipSuccess && !two)
         e = c->timed_ext(K_XUPDATE, -1, [&](hipEvent_t a, hipEvent_t b) { return launch_xupdate(ds, dm, st, a, b); });
@@ -599,11 +597,10 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
         ++t;
     }
     e = c->timed(K_OUTPUT, -1, st, [&] { return launch_outputs(ds, dm, st); });
-    if (e == hipSuccess) e = hipMemcpyAsync(c->host_ctl, d.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(GBSUB_E_DEVICE);
 
-    const Ctl &h = *c->host_ctl;
+    const Ctl &h = c->host_out->ctl;
     const gbsub_status status = h.status == 6 ? GBSUB_E_MAXITER : GBSUB_OK;
     if (c->profiling) {
         const int64_t n_body = (int64_t)h.n_iter;
@@ -711,23 +708,19 @@ gbsub_status gbsub_coarse(const gbsub_ctx *c, uint32_t kind, double f_lo, double
         while (i < g.B && !past(i)) ++i;
         ed.i[j] = i;
     }
-    // long grids: each bin in several shares, whose sums go to the in-part 1/S
-    // prefixes, dead once a run has settled (COARSE_BIN samples per bin, so the
-    // shares' three sums each fit)
-    const int ns = (int64_t)n_out * COARSE_BIN <= (int64_t)g.B ? std::max(1, COARSE_GRID / (int)n_out) : 1;
-    double *sums = ns > 1 ? c->dev.is_pre : c->dev.coarse;
-    hipError_t e = launch_coarse(c->dev.S, c->dev.sx, c->dev.X, (int)kind, g.k0, g.B, g.T, ed, (int)n_out, ns, sums,
-                                 nullptr);
-    std::vector<double> h(3 * (size_t)n_out * ns);
-    if (e == hipSuccess) e = hipMemcpy(h.data(), sums, h.size() * 8, hipMemcpyDeviceToHost);
+    // long grids: each bin in several shares
+    const int ns = (int64_t)n_out * COARSE_BIN <= (int64_t)g.B ? COARSE_GRID / (int)n_out : 1;
+    hipError_t e = launch_coarse(c->dev.S, c->dev.sx, c->dev.X, (int)kind, g.k0, g.B, g.T, ed, (int)n_out, ns,
+                                 c->dev_out->coarse, nullptr);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) return GBSUB_E_DEVICE;
     for (uint32_t k = 0; k < n_out; ++k) {
         double f = 0.0, v = 0.0, cnt = 0.0;
         for (int q = 0; q < ns; ++q) {
-            const double *o = &h[3 * ((size_t)k * ns + q)];
-            f += o[0];
-            v += o[1];
-            cnt += o[2];
+            const CoarseSum &o = c->host_out->coarse[(size_t)k * ns + q];
+            f += o.f;
+            v += o.v;
+            cnt += o.n;
         }
         const double fm = cnt > 0 ? f / cnt : 0.0;
         const double sm = cnt > 0 ? v / cnt : 0.0;
@@ -841,26 +834,9 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
     const Grid &g = c->g;
     CxDev d;
     cx_carve(g, cat->n, (char *)ws, &d);
-    // the A and E channels as two descriptors of the median kernels
-    for (int ch = 0; ch < 2; ++ch) {
-        Slot sl{};
-        sl.g = g;
-        sl.d.sx = d.sx;
-        sl.d.X = d.X + (size_t)ch * g.B;
-        sl.d.S = d.S + (size_t)ch * g.B;
-        sl.d.is_pre = d.is_pre + (size_t)ch * g.B;
-        sl.d.is_psum = d.is_psum + (size_t)ch * g.nparts;
-        sl.d.xstamp = d.xstamp;
-        sl.d.sstamp = d.sstamp;
-        sl.d.sdl = d.sdl;
-        sl.d.ctl = d.ctl;
-        sl.n = cat->n;
-        sl.active = 1;
-        c->host_cx_slots[ch] = sl;
-    }
     CxIn in{cat->A, cat->f, cat->fdot, cat->phi_a, cat->phi_e, cat->id, (uint32_t)cat->n,
-            reinterpret_cast<uint32_t *>(c->dev_prog)};
-    volatile uint32_t *prog = reinterpret_cast<uint32_t *>(c->host_prog);
+            reinterpret_cast<uint32_t *>(&c->dev_out->prog), &c->dev_out->ctl};
+    volatile uint32_t *prog = reinterpret_cast<uint32_t *>(&c->host_out->prog);
     *prog = 0;
     auto fail = [&](gbsub_status s) {
         (void)hipStreamSynchronize(st);
@@ -868,8 +844,7 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
     };
     c->ev_used = 0;
     c->recs.clear();
-    hipError_t e = hipMemcpyAsync(d.slots, c->host_cx_slots, 2 * sizeof(Slot), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = c->timed(K_PREP, -1, st, [&] { return cx_launch_prep(g, d, in, st); });
+    hipError_t e = c->timed(K_PREP, -1, st, [&] { return cx_launch_prep(g, d, in, st); });
     if (e != hipSuccess) return fail(GBSUB_E_DEVICE);
     auto body = [&](int64_t ti) {
         hipError_t r = c->timed(K_XUPDATE, ti, st, [&] { return cx_launch_power(g, d, in, st); });
@@ -917,10 +892,9 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
         ++t;
     }
     e = cx_launch_outputs(g, d, in, st);
-    if (e == hipSuccess) e = hipMemcpyAsync(c->host_ctl, d.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(GBSUB_E_DEVICE);
-    const Ctl &h = *c->host_ctl;
+    const Ctl &h = c->host_out->ctl;
     if (h.bad) return GBSUB_E_INVALID;
     if (c->profiling) {
         for (const auto &r : c->recs) {
@@ -1211,12 +1185,11 @@ gbsub_status gbsub_batch_admit(gbsub_batch *b, gbsub_ctx *c, const gbsub_catalog
     b->host_table[k] = make_slot(c->g, d, cat);
     const Dims one = dims_of(b->host_table[k]);
     Slot *ds = b->table + k;
-    hipError_t e = hipMemcpyAsync(ds, &b->host_table[k], sizeof(Slot), hipMemcpyHostToDevice, st);
+    hipError_t e = launch_reset(ds, b->host_table[k], st);
     if (e == hipSuccess && c->tables_ws != ws) {
         e = launch_grid_tables(ds, one, st);
         if (e == hipSuccess) c->tables_ws = ws;
     }
-    if (e == hipSuccess) e = launch_reset(ds, one, st);
     if (e == hipSuccess) e = launch_prep(ds, one, st);
     if (e == hipSuccess) e = launch_xupdate(ds, one, st);
     if (e != hipSuccess) {
@@ -1336,12 +1309,12 @@ gbsub_status gbsub_batch_retire(gbsub_batch *b, uint32_t k, void *stream, gbsub_
     Slot *ds = b->table + k;
     const uint8_t outcome = b->state[k];
     hipError_t e = hipSuccess;
+    // the control block is as the poll that saw the slot settle read it, and the
+    // table's entry is launched no more
     if (outcome == GBSUB_SLOT_SETTLED) e = launch_outputs(ds, dims_of(sl), st);
-    if (e == hipSuccess) e = hipMemcpyAsync(&b->host_ctls[k], sl.d.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st);
-    b->host_table[k].active = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(ds, &b->host_table[k], sizeof(Slot), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return GBSUB_E_DEVICE;
+    b->host_table[k].active = 0;
     const Ctl &h = b->host_ctls[k];
     const gbsub_summary s = summary_of(sl.g, h);
     if (out) *out = s;

@@ -452,6 +452,22 @@ __global__ __launch_bounds__(WG) void k_cx_reset(KArgs a)
         d.sstamp[k] = 0;
         d.sdl[k] = (uint32_t)k;
     }
+    if (i0 < 2) {                          // the A and E channels as two descriptors of the PSD kernels
+        Slot sl{};
+        sl.g = g;
+        sl.d.sx = d.sx;
+        sl.d.X = d.X + i0 * (size_t)g.B;
+        sl.d.S = d.S + i0 * (size_t)g.B;
+        sl.d.is_pre = d.is_pre + i0 * (size_t)g.B;
+        sl.d.is_psum = d.is_psum + i0 * (size_t)g.nparts;
+        sl.d.xstamp = d.xstamp;
+        sl.d.sstamp = d.sstamp;
+        sl.d.sdl = d.sdl;
+        sl.d.ctl = d.ctl;
+        sl.n = a.in.n;
+        sl.active = 1;
+        d.slots[i0] = sl;
+    }
     if (i0 == 0) {
         Ctl *c = d.ctl;
         c->amax_bits = 0;
@@ -1615,6 +1631,7 @@ __global__ __launch_bounds__(WG) void k_cx_ids(KArgs a)
     const CxDev &d = a.d;
     list_resolved(d.ctl->cand_cursor, d.c_iter, d.c_id, d.rlist, &d.ctl->res_cursor,
                   [&](uint32_t j) { return a.in.ids[d.c_src[j]]; });
+    if (blockIdx.x == gridDim.x - 1) put_host(a.in.host_ctl, d.ctl, threadIdx.x);
 }
 
 __global__ __launch_bounds__(WG) void k_cx_hout(KArgs a, int ch, double *out)

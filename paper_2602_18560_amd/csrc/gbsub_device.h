@@ -63,6 +63,16 @@ DEVI void window_reach(const Grid &g, int lo, int hi, int *a, int *b)
     *b = (whole || hi >= g.B - g.W) ? g.B - 1 : hi + g.h;
 }
 
+// A record to host-mapped memory, in 8-byte words: lane w of the calling threads
+// stores word w (lane: 0, 1, .. at least the record's words).
+template <typename T> DEVI void put_host(T *dst, const T *src, int lane)
+{
+    static_assert(sizeof(T) % 8 == 0, "copied in 8-byte words");
+    if (lane < (int)(sizeof(T) / 8))
+        __hip_atomic_store(reinterpret_cast<uint64_t *>(dst) + lane, reinterpret_cast<const uint64_t *>(src)[lane],
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The ids of candidates 0 .. nc-1 (id_of(j): that of candidate j) into c_id,
 // and the resolved ones (iter >= 0) as words id << 32 | j into `list`, in any
 // order: each block takes a contiguous share of at least LR_MIN candidates,

@@ -179,7 +179,6 @@ struct Dev {
     double *c_rho2;          // rho^2 at the last evaluation
     SnrPart *b_part;         // [SNR_BLOCKS] per-block partials of k_snr
     uint32_t *n_new;         // [NEW_CAP] sources subtracted per loop body
-    double *coarse;          // [3 * COARSE_MAX] coarse-graining sums (f, value, count)
     Ctl *ctl;
     uint32_t max_slots;      // capacity of `partial`
     uint32_t max_chunks;     // grid of the accumulation kernel
@@ -198,6 +197,7 @@ struct Slot {
     uint32_t pad;
     uint64_t *prog;          // host-mapped word of a single run: dirty tiles of the next body << 32 |
                              // bodies finished << 1 | settled (null in batches)
+    Ctl *host_ctl;           // host-mapped copy of the control block, written by k_cand_ids (or null)
 };
 
 // Launch extents: the largest per-slot block counts of a set of slots.
@@ -219,7 +219,8 @@ inline int list_entries(const Grid &g)
 // Kernel launchers (gbsub_kernels.hip); all enqueue on `st` and return the
 // launch status.  `ds` is the device array of `dm.ns` slot descriptors.
 hipError_t launch_grid_tables(const Slot *ds, const Dims &dm, hipStream_t st);
-hipError_t launch_reset(const Slot *ds, const Dims &dm, hipStream_t st);
+// Writes the descriptor to ds (device memory) and clears the slot's run state.
+hipError_t launch_reset(Slot *ds, const Slot &slot, hipStream_t st);
 hipError_t launch_prep(const Slot *ds, const Dims &dm, hipStream_t st);
 // The loop body's launchers take optional events that the dispatch itself
 // stamps with its start and end (nullptr: none).
@@ -301,6 +302,7 @@ struct CxIn {
     const uint32_t *ids;
     uint32_t n;
     uint32_t *prog;
+    Ctl *host_ctl;           // host-mapped copy of the control block, written by k_cx_ids
 };
 hipError_t cx_launch_prep(const Grid &g, const CxDev &d, const CxIn &in, hipStream_t st);
 // A loop body: X update, the PSD of both channels (the median or mean
@@ -317,6 +319,10 @@ hipError_t cx_launch_h(const Grid &g, const CxDev &d, uint32_t n, int ch, double
 hipError_t cx_launch_templates(const Grid &g, const float *A, const float *F, const float *FD, uint32_t n,
                                int64_t *q, double *U, hipStream_t st);
 
+// Sums over the samples of a share of a coarse-graining bin.
+struct CoarseSum {
+    double f, v, n;
+};
 // First grid sample of each coarse-graining bin; the last entry ends the last bin.
 struct CoarseEdges { int32_t i[COARSE_MAX + 1]; };
 
@@ -329,8 +335,8 @@ struct PopParams {
 hipError_t launch_generate(const PopParams &pp, uint64_t seed, uint64_t first, uint64_t n, float *A, float *F,
                            float *FD, uint32_t *id, hipStream_t st);
 // Sums of f_i and of the chosen spectrum over each bin of `ed`, in ns shares:
-// out[3 (k ns + s) ..] = (sum f, sum v, count) of share s of bin k.
+// out[k ns + s] (host-mapped) = the sums of share s of bin k.
 hipError_t launch_coarse(const double *S, const double *sx, const double *X, int kind, int64_t k0, int B,
-                         double T, const CoarseEdges &ed, int n_out, int ns, double *out, hipStream_t st);
+                         double T, const CoarseEdges &ed, int n_out, int ns, CoarseSum *out, hipStream_t st);
 
 }  // namespace gbs

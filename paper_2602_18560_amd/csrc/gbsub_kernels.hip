@@ -397,13 +397,14 @@ __global__ __launch_bounds__(WG) void k_isx_seg(const Slot *S)
 
 // Clears the per-run state of a slot: control block, tile counters, dirty
 // stamps (every tile is dirty for the first loop body, t = 0).
-__global__ __launch_bounds__(WG) void k_reset(const Slot *S)
+// It also writes the slot's descriptor to device memory (a copy from the host
+// ahead of the run cost its own 2 us and the 8 to 10 us until the next kernel).
+__global__ __launch_bounds__(WG) void k_reset(Slot sl, Slot *ds)
 {
-    const Slot &sl = S[blockIdx.y];
-    if (!sl.active) return;
-    const Grid g = sl.g;
-    const Dev d = sl.d;
+    const Grid &g = sl.g;
+    const Dev &d = sl.d;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *ds = sl;
         Ctl *c = d.ctl;
         c->amax_bits = 0;
         c->bad = 0;
@@ -2696,6 +2697,7 @@ __global__ __launch_bounds__(WG) void k_cand_ids(const Slot *S)
     const uint32_t *ids = sl.ids;
     list_resolved(d.ctl->n_cand, d.c_iter, d.c_id, reinterpret_cast<uint64_t *>(d.ev_val), &d.ctl->res_cursor,
                   [&](uint32_t j) { return ids[d.c_src[j]]; });
+    if (sl.host_ctl && blockIdx.x == gridDim.x - 1) put_host(sl.host_ctl, d.ctl, threadIdx.x);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -2710,11 +2712,10 @@ hipError_t launch_grid_tables(const Slot *ds, const Dims &dm, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t launch_reset(const Slot *ds, const Dims &dm, hipStream_t st)
+hipError_t launch_reset(Slot *ds, const Slot &slot, hipStream_t st)
 {
-    const unsigned nb = (unsigned)((dm.maxnt + WG - 1) / WG);
-    k_reset<<<dim3(nb, dm.ns), WG, 0, st>>>(ds);
-    if (dm.naive) k_zero_f32<<<dim3(1024, dm.ns), WG, 0, st>>>(ds);
+    k_reset<<<(slot.g.nt + WG - 1) / WG, WG, 0, st>>>(slot, ds);
+    if (slot.g.prec == PREC_NAIVE) k_zero_f32<<<1024, WG, 0, st>>>(ds);
     return hipGetLastError();
 }
 
@@ -2725,7 +2726,9 @@ hipError_t launch_prep(const Slot *ds, const Dims &dm, hipStream_t st)
     k_prep_plan<<<dim3(1, dm.ns), WG, 0, st>>>(ds);
     if (dm.prep_blocks > 0) k_prep_scatter<<<dim3(dm.prep_blocks, dm.ns), WG, 0, st>>>(ds);
     k_accum<<<dim3(dm.accum_blocks, dm.ns), ACC_T, 0, st>>>(ds);
-    k_accum_reduce<<<dim3(dm.maxnt * (dm.maxtile / RED_BINS), dm.ns), RED_BINS, 0, st>>>(ds);
+    // a tile is hot from more than ACC_EV events on; a block takes PREP_SRC sources of two events at most
+    if ((uint64_t)dm.prep_blocks * PREP_SRC * 2 > (uint64_t)ACC_EV)
+        k_accum_reduce<<<dim3(dm.maxnt * (dm.maxtile / RED_BINS), dm.ns), RED_BINS, 0, st>>>(ds);
     if (dm.naive) k_accum_f32<<<dim3(2048, dm.ns), WG, 0, st>>>(ds);
     k_dscan<<<dim3(1, dm.ns), WG, 0, st>>>(ds);
     return hipGetLastError();
@@ -2788,9 +2791,10 @@ constexpr int CT = 512;
 
 __global__ __launch_bounds__(CT) void k_coarse(const double *S, const double *sx, const double *X, int kind,
                                                int64_t k0, int B, double T, CoarseEdges ed, int n_out, int ns,
-                                               double *out)
+                                               CoarseSum *out)
 {
     __shared__ double sf[CT / 64], sv[CT / 64];
+    __shared__ CoarseSum sum;
     const int kb = blockIdx.x, part = blockIdx.y;
     const int i0 = ed.i[kb], i1 = ed.i[kb + 1];
     const int n = max(i1 - i0, 0), share = (n + ns - 1) / ns;
@@ -2818,19 +2822,19 @@ __global__ __launch_bounds__(CT) void k_coarse(const double *S, const double *sx
         sv[threadIdx.x >> 6] = av;
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    for (int w = 1; w < CT / 64; ++w) {
-        af += sf[w];
-        av += sv[w];
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < CT / 64; ++w) {
+            af += sf[w];
+            av += sv[w];
+        }
+        sum = {af, av, (double)(b1 - b0)};
     }
-    double *o = out + 3 * ((size_t)kb * ns + part);
-    o[0] = af;
-    o[1] = av;
-    o[2] = (double)(b1 - b0);
+    __syncthreads();
+    put_host(out + (size_t)kb * ns + part, &sum, threadIdx.x);
 }
 
 hipError_t launch_coarse(const double *S, const double *sx, const double *X, int kind, int64_t k0, int B,
-                         double T, const CoarseEdges &ed, int n_out, int ns, double *out, hipStream_t st)
+                         double T, const CoarseEdges &ed, int n_out, int ns, CoarseSum *out, hipStream_t st)
 {
     k_coarse<<<dim3(n_out, ns), CT, 0, st>>>(S, sx, X, kind, k0, B, T, ed, n_out, ns, out);
     return hipGetLastError();
