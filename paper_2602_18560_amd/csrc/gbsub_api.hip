@@ -162,9 +162,18 @@ uint64_t carve(const Grid &g, uint64_t n, char *base, Dev *d)
     t.sstamp = (uint32_t *)take(nt * 4);
     t.sdl = (uint32_t *)take(nt * 4);
     t.btot = (uint32_t *)take(nt * 4);
-    const uint64_t npb = (nn + PREP_SRC - 1) / PREP_SRC;
-    t.bhist = (uint32_t *)take(npb * ((nt + 1) / 2) * 4);
-    t.boff = (uint32_t *)take(npb * nt * 4);
+    // Prep blocks: PREP_SRC sources each, or PREP_SRC_MIN where that leaves the
+    // chip idle (1e4 sources were three blocks: count 19 and scatter 13 us, now 9
+    // and 6; 2.3e5 sources 21 and 13, now 11 and 7).  The
+    // (block, tile) matrices and per-block results of the smaller blocks lie
+    // in X, S and the 1/S prefixes, which are written only after the prep, so
+    // no catalog needs more memory for them.
+    const uint64_t rows = (nn + PREP_SRC_MIN - 1) / PREP_SRC_MIN;
+    const bool small = n <= PREP_SMALL && (rows + 1) * nt <= B;
+    t.prep_src = small ? (uint32_t)PREP_SRC_MIN : (uint32_t)PREP_SRC;
+    const uint64_t npb = small ? rows : (nn + PREP_SRC - 1) / PREP_SRC;
+    t.bhist = small ? (uint32_t *)t.X : (uint32_t *)take(npb * ((nt + 1) / 2) * 4);
+    t.boff = small ? (uint32_t *)t.S : (uint32_t *)take(npb * nt * 4);
     t.bbase = (uint32_t *)take((nt + 1) * 4);
     t.nch = (uint32_t *)take(nt * 4);
     t.chunk_base = (uint32_t *)take((nt + 1) * 4);
@@ -174,9 +183,8 @@ uint64_t carve(const Grid &g, uint64_t n, char *base, Dev *d)
     t.partial = (I128 *)take((uint64_t)t.max_slots * 2 * (uint64_t)g.tile * 16);
     t.cbits = (uint64_t *)take(((nn + 63) / 64) * 8);
     t.rs_hist = (uint32_t *)take(resolved_scratch_words(nn) * 4);
-    const uint64_t ncb = npb;
-    t.blk_cand = (uint32_t *)take((ncb + 1) * 4);
-    t.blk_amax = (uint32_t *)take(ncb * 4);
+    t.blk_cand = small ? (uint32_t *)t.is_pre : (uint32_t *)take((npb + 1) * 4);
+    t.blk_amax = small ? t.blk_cand + npb + 1 : (uint32_t *)take(npb * 4);
     t.c_src = (uint32_t *)take(nn * 4);
     t.c_id = (uint32_t *)take(nn * 4);
     t.c_glo = (int32_t *)take(nn * 4);
@@ -282,7 +290,8 @@ Dims dims_of(const Slot &sl)
     dm.maxlist = list_entries(sl.g);
     dm.est_mask = 1u << sl.g.est;
     dm.naive = sl.g.prec == PREC_NAIVE;
-    dm.prep_blocks = (uint32_t)((sl.n + PREP_SRC - 1) / PREP_SRC);
+    dm.prep_blocks = (uint32_t)((sl.n + sl.d.prep_src - 1) / sl.d.prep_src);
+    dm.max_n = sl.n;
     dm.accum_blocks = sl.d.max_chunks;
     return dm;
 }
@@ -297,6 +306,7 @@ void widen(Dims &a, const Dims &b)
     a.est_mask |= b.est_mask;
     a.naive |= b.naive;
     a.prep_blocks = std::max(a.prep_blocks, b.prep_blocks);
+    a.max_n = std::max(a.max_n, b.max_n);
     a.accum_blocks = std::max(a.accum_blocks, b.accum_blocks);
 }
 

@@ -15,6 +15,8 @@ constexpr int NARROW = 16;         // tracks of <= NARROW bins: SNR summed bin b
 constexpr int SNR_BLOCKS = 1024;   // fixed grid of the per-candidate kernels
 constexpr int COOP_PARTS = 8;      // tracks over more parts: the part sums are added by the whole wave
 constexpr int PREP_SRC = 4096;     // sources per block of the prep passes (count and scatter)
+constexpr int PREP_SRC_MIN = 1024; // and of catalogs up to PREP_SMALL sources
+constexpr uint64_t PREP_SMALL = 1u << 20;
 constexpr int SEG_BINS = 128;      // bins per segment of the 1/S_instr bounds of the candidate test
 constexpr int CS_WG = 1024;        // threads of a column-pass block (64 tiles, 16 waves over the blocks)
 constexpr int ACC_T = 512;         // threads of an accumulation block
@@ -182,6 +184,8 @@ struct Dev {
     Ctl *ctl;
     uint32_t max_slots;      // capacity of `partial`
     uint32_t max_chunks;     // grid of the accumulation kernel
+    uint32_t prep_src;       // sources per prep block: PREP_SRC or PREP_SRC_MIN
+    uint32_t pad;
 };
 
 // One catalog of a launch: its grid, workspace, catalog.  Kernels read the
@@ -208,6 +212,7 @@ struct Dims {
     uint32_t est_mask;       // bit e: some slot uses estimator e
     uint32_t naive;          // some slot runs in naive FP32
     uint32_t prep_blocks, accum_blocks;
+    uint64_t max_n;
 };
 
 inline int list_entries(const Grid &g)

@@ -520,9 +520,10 @@ DEVI int tile_of(int bin, int tile) { return div_p2(bin, tile); }
 // counts are 16-bit halves of LDS words (at most 2 PREP_SRC < 2^16 events
 // of a block fall in one tile), which keeps the block's LDS at 16 KB; the
 // packed words are the block's row of bhist.
-DEVI void k_prep_count_body(Grid g, Dev d, const float *A, const float *F, const float *FD, uint64_t n)
+template <int CB>                            // sources per thread in flight
+DEVI void k_prep_count_body(const Grid &g, const Dev &d, const float *A, const float *F, const float *FD, uint64_t n,
+                            uint32_t *hist)
 {
-    __shared__ uint32_t hist[NBK_MAX / 2];
     __shared__ uint32_t scand, samax;
     auto hadd = [&](int b) { atomicAdd(&hist[b >> 1], 1u << (16 * (b & 1))); };
     for (int b = threadIdx.x; b < (g.nt + 1) / 2; b += WG) hist[b] = 0;
@@ -531,12 +532,11 @@ DEVI void k_prep_count_body(Grid g, Dev d, const float *A, const float *F, const
         samax = 0;
     }
     __syncthreads();
-    const uint64_t base = (uint64_t)blockIdx.x * PREP_SRC;
+    const uint64_t base = (uint64_t)blockIdx.x * d.prep_src;
     uint32_t cc = 0, bad = 0, amax = 0;
-    constexpr int CB = 8;
     // CB sources per thread in flight: loads first, then the tracks and
     // the S_instr gathers of the candidate tests
-    for (int r0 = 0; r0 < PREP_SRC / WG; r0 += CB) {
+    for (int r0 = 0; r0 < (int)d.prep_src / WG; r0 += CB) {
         float a[CB], f[CB], fd[CB];
 #pragma unroll
         for (int q = 0; q < CB; ++q) {
@@ -633,12 +633,15 @@ DEVI void k_prep_count_body(Grid g, Dev d, const float *A, const float *F, const
 __global__ __launch_bounds__(WG) void k_prep_count(const Slot *S)
 {
     const Slot &sl = S[blockIdx.y];
-    if (!sl.active || (uint64_t)blockIdx.x * PREP_SRC >= sl.n) return;
+    if (!sl.active || (uint64_t)blockIdx.x * sl.d.prep_src >= sl.n) return;
     const Grid g = sl.g;
     const Dev d = sl.d;
-    const float *A = sl.A, *F = sl.F, *FD = sl.FD;
-    const uint64_t n = sl.n;
-    k_prep_count_body(g, d, A, F, FD, n);
+    static_assert(PREP_SRC % (8 * WG) == 0 && PREP_SRC_MIN % (4 * WG) == 0, "whole batches");
+    __shared__ uint32_t hist[NBK_MAX / 2];
+    if (d.prep_src == PREP_SRC)
+        k_prep_count_body<8>(g, d, sl.A, sl.F, sl.FD, sl.n, hist);
+    else
+        k_prep_count_body<4>(g, d, sl.A, sl.F, sl.FD, sl.n, hist);
 }
 
 
@@ -661,7 +664,7 @@ __global__ __launch_bounds__(CS_WG) void k_prep_colscan(const Slot *S)
     const int tile = blockIdx.x * 64 + lane;
     const bool ok = tile < g.nt;
     const int col = ok ? tile : g.nt - 1;                      // a valid column; results dropped
-    const int nb = (int)((sl.n + PREP_SRC - 1) / PREP_SRC);
+    const int nb = (int)((sl.n + d.prep_src - 1) / d.prep_src);
     const int per = (nb + NV - 1) / NV;
     const int b0 = min(w * per, nb), b1 = min(b0 + per, nb);
     const size_t row = 2 * (size_t)((g.nt + 1) / 2);          // 16-bit counts per bhist row
@@ -712,7 +715,7 @@ __global__ __launch_bounds__(WG) void k_prep_plan(const Slot *S)
     // largest A and the candidates of the count blocks: their exclusive
     // prefix is each scatter block's first candidate slot
     {
-        const int nb = (int)((sl.n + PREP_SRC - 1) / PREP_SRC);
+        const int nb = (int)((sl.n + d.prep_src - 1) / d.prep_src);
         uint32_t am = 0;
         for (int b = threadIdx.x; b < nb; b += WG) am = max(am, d.blk_amax[b]);
         for (int s = 32; s >= 1; s >>= 1) am = max(am, (uint32_t)__shfl_xor((int)am, s, 64));
@@ -765,9 +768,10 @@ __global__ __launch_bounds__(WG) void k_prep_plan(const Slot *S)
 // Scatter pass: the block's events start, inside each tile's segment, at
 // the slot the column pass gave it; it writes the events and the candidate
 // records.
-DEVI void k_prep_scatter_body(Grid g, Dev d, const float *A, const float *F, const float *FD, uint64_t n)
+template <int SB>                            // sources per thread in flight
+DEVI void k_prep_scatter_body(const Grid &g, const Dev &d, const float *A, const float *F, const float *FD, uint64_t n,
+                              uint32_t *cur)
 {
-    __shared__ uint32_t cur[NBK_MAX];
     __shared__ uint32_t scand, cbase;
     for (int b = threadIdx.x; b < g.nt; b += WG) cur[b] = d.bbase[b] + d.boff[(size_t)blockIdx.x * g.nt + b];
     if (threadIdx.x == 0) {
@@ -776,9 +780,8 @@ DEVI void k_prep_scatter_body(Grid g, Dev d, const float *A, const float *F, con
     }
     __syncthreads();
     const int L = fx_exp(d.ctl->amax_bits, g.T);
-    const uint64_t base = (uint64_t)blockIdx.x * PREP_SRC;
-    constexpr int SB = 8;                    // sources per thread in flight
-    for (int r0 = 0; r0 < PREP_SRC / WG; r0 += SB) {
+    const uint64_t base = (uint64_t)blockIdx.x * d.prep_src;
+    for (int r0 = 0; r0 < (int)d.prep_src / WG; r0 += SB) {
         float a[SB], f[SB], fd[SB];
         uint64_t cw[SB];                         // candidate-flag words of the sources
 #pragma unroll
@@ -838,12 +841,14 @@ DEVI void k_prep_scatter_body(Grid g, Dev d, const float *A, const float *F, con
 __global__ __launch_bounds__(WG) void k_prep_scatter(const Slot *S)
 {
     const Slot &sl = S[blockIdx.y];
-    if (!sl.active || (uint64_t)blockIdx.x * PREP_SRC >= sl.n) return;
+    if (!sl.active || (uint64_t)blockIdx.x * sl.d.prep_src >= sl.n) return;
     const Grid g = sl.g;
     const Dev d = sl.d;
-    const float *A = sl.A, *F = sl.F, *FD = sl.FD;
-    const uint64_t n = sl.n;
-    k_prep_scatter_body(g, d, A, F, FD, n);
+    __shared__ uint32_t cur[NBK_MAX];
+    if (d.prep_src == PREP_SRC)
+        k_prep_scatter_body<8>(g, d, sl.A, sl.F, sl.FD, sl.n, cur);
+    else
+        k_prep_scatter_body<4>(g, d, sl.A, sl.F, sl.FD, sl.n, cur);
 }
 
 
@@ -2726,8 +2731,8 @@ hipError_t launch_prep(const Slot *ds, const Dims &dm, hipStream_t st)
     k_prep_plan<<<dim3(1, dm.ns), WG, 0, st>>>(ds);
     if (dm.prep_blocks > 0) k_prep_scatter<<<dim3(dm.prep_blocks, dm.ns), WG, 0, st>>>(ds);
     k_accum<<<dim3(dm.accum_blocks, dm.ns), ACC_T, 0, st>>>(ds);
-    // a tile is hot from more than ACC_EV events on; a block takes PREP_SRC sources of two events at most
-    if ((uint64_t)dm.prep_blocks * PREP_SRC * 2 > (uint64_t)ACC_EV)
+    // a tile is hot from more than ACC_EV events on; a source has two at most
+    if (2 * dm.max_n > (uint64_t)ACC_EV)
         k_accum_reduce<<<dim3(dm.maxnt * (dm.maxtile / RED_BINS), dm.ns), RED_BINS, 0, st>>>(ds);
     if (dm.naive) k_accum_f32<<<dim3(2048, dm.ns), WG, 0, st>>>(ds);
     k_dscan<<<dim3(1, dm.ns), WG, 0, st>>>(ds);
