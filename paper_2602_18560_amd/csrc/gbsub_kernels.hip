@@ -240,6 +240,19 @@ DEVI T block_excl_scan(T x, T *sh, T *total)
     return add_t(pre, ex);
 }
 
+// Inclusive scan of a u32 across the 64 lanes of a wave (DPP row shifts and
+// row broadcasts; every lane must be active).
+DEVI uint32_t wave_scan_u32(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast:15
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast:31
+    return v;
+}
+
 DEVI double wave_sum(double x)
 {
     for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
@@ -1314,19 +1327,6 @@ struct MedianSmem {
     int flag;
 };
 
-// Inclusive scan of a u32 across the 64 lanes of a wave (DPP row shifts and
-// row broadcasts; every lane must be active).
-DEVI uint32_t wave_scan_u32(uint32_t v)
-{
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr:1
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);   // row_shr:2
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);   // row_shr:4
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);   // row_shr:8
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast:15
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast:31
-    return v;
-}
-
 // Smallest (largest) word of the wave, in lane 63.
 DEVI uint32_t wave_min_u32(uint32_t v)
 {
@@ -2263,7 +2263,14 @@ DEVI double track_inv_sum(const double *v, const double *pre, int lo, int hi, in
 {
     if (hi - lo + 1 <= NARROW) {
         double s = 0.0;
-        for (int k = lo; k <= hi; ++k) s += 1.0 / v[k];
+        for (int k = lo; k <= hi; k += 4) {            // four bins' loads at a time, summed in order
+            double x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = v[min(k + u, hi)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (k + u <= hi) s += 1.0 / x[u];
+        }
         return s;
     }
     const double below = mod_p2(lo, part) == 0 ? 0.0 : pre[lo - 1];
@@ -2312,9 +2319,9 @@ DEVI double snr2_f32(const Grid &g, const Dev &d, double qd, int lo, int hi, dou
 }
 
 // Removes a resolved source's power from the exact accumulators: its one
-// bin of Xn, or the two entries of the difference array D plus the carries
-// into the tiles that start inside (glo, ghi + 1] (X = Xn + prefix of D,
-// with the prefix split into a carry per tile and a sum inside the tile).
+// bin of Xn, or the two entries of the difference array D (X = Xn + prefix of
+// D, with the prefix split into a carry per tile and a sum inside the tile;
+// mark_track adds to the carries).
 DEVI void subtract_track(const Grid &g, const Dev &d, int glo, int ghi, int64_t v)
 {
     if (glo == ghi) {
@@ -2323,8 +2330,24 @@ DEVI void subtract_track(const Grid &g, const Dev &d, int glo, int ghi, int64_t 
     }
     atomic_add_i128(&d.D[glo], -v);
     if (ghi + 1 < g.B) atomic_add_i128(&d.D[ghi + 1], v);
-    const int te = min(div_p2(ghi + 1, g.tile), g.nt - 1);
-    for (int tl = div_p2(glo, g.tile) + 1; tl <= te; ++tl) split_sum_add(&d.Dadj[tl], -v);
+}
+
+// What a resolved track changes besides its own bins, by n threads (this one
+// is the i-th): the carries into the tiles that start inside (glo, ghi + 1]
+// (v: its power; not where the carries are float sums), and the stamps of
+// the tiles the next body must convert (the track) and filter (every output
+// whose window holds a bin of the track).
+DEVI void mark_track(const Grid &g, const Dev &d, int glo, int ghi, int64_t v, uint32_t nxt, int i, int n)
+{
+    const int ta = div_p2(glo, g.tile), tb = div_p2(ghi, g.tile);
+    if (v && glo != ghi) {
+        const int te = min(div_p2(ghi + 1, g.tile), g.nt - 1);
+        for (int tl = ta + 1 + i; tl <= te; tl += n) split_sum_add(&d.Dadj[tl], -v);
+    }
+    for (int tl = ta + i; tl <= tb; tl += n) d.xstamp[tl] = nxt;
+    int sa, sb;
+    window_reach(g, glo, ghi, &sa, &sb);
+    for (int tl = div_p2(sa, g.tile) + i; tl <= div_p2(sb, g.tile); tl += n) d.sstamp[tl] = nxt;
 }
 
 // The same subtraction in fp32 (naive FP32 mode), vf = the power as a float:
@@ -2417,8 +2440,7 @@ __global__ __launch_bounds__(WG) void k_snr(const Slot *S)
     // SU candidates per thread at a time: their records, then the stamps under
     // their tracks, then the evaluations.  In late bodies nearly every
     // candidate stops at the stamps, and the launch is the latency of these
-    // two rounds of loads: 11.1 us a body on the 1e7 catalog, 11.9 with the
-    // loads one after the other
+    // two rounds of loads: 10.3 us a body on the 1e7 catalog
     constexpr int SU = 2;
     for (uint32_t jb0 = blockIdx.x * WG + (threadIdx.x & ~63u); jb0 < nc; jb0 += SU * stride) {
         int it_[SU], lo_[SU], hi_[SU];
@@ -2462,7 +2484,12 @@ __global__ __launch_bounds__(WG) void k_snr(const Slot *S)
                 } else if (comp) {
                     for (int pp = plo; pp < phi; ++pp) midc = ff_add(midc, psum_ff[pp]);
                 } else {
-                    for (int pp = plo; pp < phi; ++pp) mid += d.is_psum[pp];
+                    double x[COOP_PARTS];              // at most COOP_PARTS, all loads in flight
+#pragma unroll
+                    for (int q = 0; q < COOP_PARTS; ++q) x[q] = d.is_psum[min(plo + q, phi - 1)];
+#pragma unroll
+                    for (int q = 0; q < COOP_PARTS; ++q)
+                        if (plo + q < phi) mid += x[q];
                 }
             }
             for (uint64_t wm = (uint64_t)__ballot(wide); wm; wm &= wm - 1) {
@@ -2486,8 +2513,18 @@ __global__ __launch_bounds__(WG) void k_snr(const Slot *S)
                     }
                     sumc = m;
                 } else {
+                    // a 1.5M-bin track has 46 rounds of 64 parts: eight
+                    // rounds' loads at a time
+                    constexpr int PU = 8;
                     double m = 0.0;
-                    for (int pp = a + lane; pp < b; pp += 64) m += d.is_psum[pp];
+                    for (int pp = a + lane; pp < b; pp += PU * 64) {
+                        double x[PU];
+#pragma unroll
+                        for (int q = 0; q < PU; ++q) x[q] = d.is_psum[min(pp + q * 64, b - 1)];
+#pragma unroll
+                        for (int q = 0; q < PU; ++q)
+                            if (pp + q * 64 < b) m += x[q];
+                    }
                     sum = wave_sum(m);
                 }
                 if (lane == L) {
@@ -2502,18 +2539,19 @@ __global__ __launch_bounds__(WG) void k_snr(const Slot *S)
                                          : snr2_f32(g, d, q, glo, ghi, mid, midc);
                 d.c_rho2[j] = r2;
             }
-            if (!live) continue;
             // a stored rho^2 has been in the margin's minimum since its
             // evaluation; it counts as near again in every body
-            if (eval || fabs(r2 - g.rth2) <= 1e-5 * g.rth2) {
+            if (eval || (live && fabs(r2 - g.rth2) <= 1e-5 * g.rth2)) {
                 const double rel = fabs(sqrt(r2) / g.rth - 1.0);
                 minm = fmin(minm, rel);
                 near += rel <= 1e-6;
             }
-            if (r2 > g.rth2) {
+            const bool hit = live && r2 > g.rth2;
+            int64_t v = 0;                             // for the exact carries
+            if (hit) {
                 d.c_iter[j] = t;
                 ++my_new;
-                const int64_t v = (int64_t)d.c_qfx[j];
+                v = (int64_t)d.c_qfx[j];
                 if (v) {
                     const float vf = (float)ldexp((double)v, fx_exp(d.ctl->amax_bits, g.T) +
                                                                  f32_scale(d.ctl->amax_bits, g.T));
@@ -2524,10 +2562,18 @@ __global__ __launch_bounds__(WG) void k_snr(const Slot *S)
                         if (naive) subtract_track_f32(g, d, glo, ghi, vf);
                     }
                 }
-                stamp_tiles(d.xstamp, g, glo, ghi, nxt);
-                int sa, sb;
-                window_reach(g, glo, ghi, &sa, &sb);
-                stamp_tiles(d.sstamp, g, sa, sb, nxt);
+                if (comp) v = 0;
+            }
+            // the tiles of a wide track (up to 735) by the whole wave: with one
+            // thread each the first body took 46 us, with this 28
+            const bool many = hit && div_p2(ghi, g.tile) - div_p2(glo, g.tile) >= SKIP_TILES;
+            if (hit && !many) mark_track(g, d, glo, ghi, v, nxt, 0, 1);
+            for (uint64_t wm = (uint64_t)__ballot(many); wm; wm &= wm - 1) {
+                const int L = __builtin_ctzll(wm);
+                const uint32_t vl = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, L);
+                const uint32_t vh = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), L);
+                mark_track(g, d, __builtin_amdgcn_readlane(glo, L), __builtin_amdgcn_readlane(ghi, L),
+                           (int64_t)((uint64_t)vh << 32 | vl), nxt, lane, 64);
             }
         }
     }
