@@ -83,7 +83,6 @@ constexpr int MOM_MIN = 12;                   // fewer faint sources of a centre
 constexpr int MOM_COOP = 2048;                // more: all waves of the block share the centre
 constexpr int SNR_GRID = 2048;                // blocks of the SNR launch
 constexpr int GRP = 4;                        // consecutive candidates of a wave in it
-constexpr int PLAN_T = 1024;                  // threads of the one-block plan
 
 struct KArgs {
     Grid g;

@@ -18,7 +18,9 @@ constexpr int PREP_SRC = 4096;     // sources per block of the prep passes (coun
 constexpr int PREP_SRC_MIN = 1024; // and of catalogs up to PREP_SMALL sources
 constexpr uint64_t PREP_SMALL = 1u << 20;
 constexpr int SEG_BINS = 128;      // bins per segment of the 1/S_instr bounds of the candidate test
-constexpr int CS_WG = 1024;        // threads of a column-pass block (64 tiles, 16 waves over the blocks)
+constexpr int CS_WG = 1024;        // threads of a column-pass block
+constexpr int CS_COL = 32;         // tiles of a column-pass block
+constexpr int PLAN_T = 1024;       // threads of the one-block plans
 constexpr int ACC_T = 512;         // threads of an accumulation block
 constexpr int ACC_EV = 65536;      // binning events per accumulation block
 constexpr int RED_BINS = 256;      // bins per reduction block of the hot buckets

@@ -660,21 +660,21 @@ __global__ __launch_bounds__(WG) void k_prep_count(const Slot *S)
 
 // Column pass: for each tile, the exclusive prefix over the prep blocks of
 // its event counts (where each block's events start inside the tile's
-// segment) and the tile's total.  A block takes 64 tiles (one per lane; the
-// loads and stores of consecutive tiles are coalesced) and its 16 waves
-// split the prep blocks into ranges: each wave sums its range, a prefix
-// over the waves gives each range its start, and each wave walks its range
-// again writing the offsets.
+// segment) and the tile's total.  A block takes CS_COL tiles, its threads
+// NV ranges of the prep blocks: each sums its range, a prefix over the ranges
+// gives each its start, and each walks its range again writing the offsets.
+// (1e7 sources, 1843 tiles: 22 us; 64 tiles per block, 30 us; 16, 23 us, and 39
+// against 31 us at 3686 tiles, for the shorter rows.)
 __global__ __launch_bounds__(CS_WG) void k_prep_colscan(const Slot *S)
 {
-    constexpr int NV = CS_WG / 64;
-    __shared__ uint32_t part[NV][64];
+    constexpr int NV = CS_WG / CS_COL;
+    __shared__ uint32_t part[NV][CS_COL + 1];
     const Slot &sl = S[blockIdx.y];
     if (!sl.active) return;
     const Grid g = sl.g;
     const Dev d = sl.d;
-    const int lane = lane_id(), w = threadIdx.x >> 6;
-    const int tile = blockIdx.x * 64 + lane;
+    const int q0 = threadIdx.x % CS_COL, w = threadIdx.x / CS_COL;
+    const int tile = blockIdx.x * CS_COL + q0;
     const bool ok = tile < g.nt;
     const int col = ok ? tile : g.nt - 1;                      // a valid column; results dropped
     const int nb = (int)((sl.n + d.prep_src - 1) / d.prep_src);
@@ -691,16 +691,18 @@ __global__ __launch_bounds__(CS_WG) void k_prep_colscan(const Slot *S)
 #pragma unroll
         for (int q = 0; q < U; ++q) sum += bb + q < b1 ? c[q] : 0u;
     }
-    part[w][lane] = sum;
+    part[w][q0] = sum;
     __syncthreads();
-    uint32_t run = 0, tot = 0;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        const uint32_t x = part[v][lane];
-        run += v < w ? x : 0u;
-        tot += x;
+    // exclusive prefix over the ranges, one wave per column
+    for (int c = threadIdx.x >> 6; c < CS_COL; c += CS_WG / 64) {
+        const int l = lane_id();
+        const uint32_t x = l < NV ? part[l][c] : 0u;
+        const uint32_t inc = wave_scan_u32(x);
+        if (l < NV) part[l][c] = inc - x;
+        if (l == 63 && blockIdx.x * CS_COL + c < g.nt) d.btot[blockIdx.x * CS_COL + c] = inc;
     }
-    if (w == 0 && ok) d.btot[tile] = tot;
+    __syncthreads();
+    uint32_t run = part[w][q0];
     for (int bb = b0; bb < b1; bb += U) {
         uint32_t c[U];
 #pragma unroll
@@ -717,9 +719,9 @@ __global__ __launch_bounds__(CS_WG) void k_prep_colscan(const Slot *S)
 
 // Plan (one block): tile bases, accumulation blocks and partial-sum slots;
 // clears the tile sums of D.
-__global__ __launch_bounds__(WG) void k_prep_plan(const Slot *S)
+__global__ __launch_bounds__(PLAN_T) void k_prep_plan(const Slot *S)
 {
-    __shared__ uint32_t sh[WG / 64];
+    __shared__ uint32_t sh[PLAN_T / 64];
     const Slot &sl = S[blockIdx.y];
     if (!sl.active) return;
     const Grid g = sl.g;
@@ -730,30 +732,30 @@ __global__ __launch_bounds__(WG) void k_prep_plan(const Slot *S)
     {
         const int nb = (int)((sl.n + d.prep_src - 1) / d.prep_src);
         uint32_t am = 0;
-        for (int b = threadIdx.x; b < nb; b += WG) am = max(am, d.blk_amax[b]);
+        for (int b = threadIdx.x; b < nb; b += PLAN_T) am = max(am, d.blk_amax[b]);
         for (int s = 32; s >= 1; s >>= 1) am = max(am, (uint32_t)__shfl_xor((int)am, s, 64));
         if (lane_id() == 0) sh[threadIdx.x >> 6] = am;
         __syncthreads();
         if (threadIdx.x == 0) {
-            for (int w = 1; w < WG / 64; ++w) am = max(am, sh[w]);
+            for (int w = 1; w < PLAN_T / 64; ++w) am = max(am, sh[w]);
             d.ctl->amax_bits = am;
         }
         __syncthreads();
-        block_scan_array<uint32_t>(d.blk_cand, d.blk_cand, nb);   // in place: each thread rereads its own run
+        block_scan_array<uint32_t, PLAN_T>(d.blk_cand, d.blk_cand, nb);   // in place: each thread rereads its own run
         if (threadIdx.x == 0) d.ctl->n_cand = d.blk_cand[nb];
         __syncthreads();
     }
 
     uint32_t carry_e = 0, carry_c = 0, carry_s = 0;
-    for (int base = 0; base < g.nt; base += WG) {
+    for (int base = 0; base < g.nt; base += PLAN_T) {
         const int b = base + threadIdx.x;
         const uint32_t cnt = b < g.nt ? d.btot[b] : 0u;
         const uint32_t nc = b < g.nt ? max(1u, (cnt + ACC_EV - 1) / ACC_EV) : 0u;
         const uint32_t ns = nc > 1 ? nc : 0u;
         uint32_t te, tc, ts;
-        const uint32_t ee = block_excl_scan(cnt, sh, &te);
-        const uint32_t ec = block_excl_scan(nc, sh, &tc);
-        const uint32_t es = block_excl_scan(ns, sh, &ts);
+        const uint32_t ee = block_excl_scan<uint32_t, PLAN_T>(cnt, sh, &te);
+        const uint32_t ec = block_excl_scan<uint32_t, PLAN_T>(nc, sh, &tc);
+        const uint32_t es = block_excl_scan<uint32_t, PLAN_T>(ns, sh, &ts);
         if (b < g.nt) {
             d.bbase[b] = carry_e + ee;
             d.nch[b] = nc;
@@ -2773,8 +2775,8 @@ hipError_t launch_reset(Slot *ds, const Slot &slot, hipStream_t st)
 hipError_t launch_prep(const Slot *ds, const Dims &dm, hipStream_t st)
 {
     if (dm.prep_blocks > 0) k_prep_count<<<dim3(dm.prep_blocks, dm.ns), WG, 0, st>>>(ds);
-    k_prep_colscan<<<dim3((dm.maxnt + 63) / 64, dm.ns), CS_WG, 0, st>>>(ds);
-    k_prep_plan<<<dim3(1, dm.ns), WG, 0, st>>>(ds);
+    k_prep_colscan<<<dim3((dm.maxnt + CS_COL - 1) / CS_COL, dm.ns), CS_WG, 0, st>>>(ds);
+    k_prep_plan<<<dim3(1, dm.ns), PLAN_T, 0, st>>>(ds);
     if (dm.prep_blocks > 0) k_prep_scatter<<<dim3(dm.prep_blocks, dm.ns), WG, 0, st>>>(ds);
     k_accum<<<dim3(dm.accum_blocks, dm.ns), ACC_T, 0, st>>>(ds);
     // a tile is hot from more than ACC_EV events on; a source has two at most
