@@ -845,9 +845,10 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
     CxDev d;
     cx_carve(g, cat->n, (char *)ws, &d);
     CxIn in{cat->A, cat->f, cat->fdot, cat->phi_a, cat->phi_e, cat->id, (uint32_t)cat->n,
-            reinterpret_cast<uint32_t *>(&c->dev_out->prog), &c->dev_out->ctl};
-    volatile uint32_t *prog = reinterpret_cast<uint32_t *>(&c->host_out->prog);
+            &c->dev_out->prog, &c->dev_out->ctl};
+    volatile uint64_t *prog = &c->host_out->prog;
     *prog = 0;
+    bool two = (uint32_t)g.nt <= g.split_tiles;    // bodies of two launches, as in gbsub_run
     auto fail = [&](gbsub_status s) {
         (void)hipStreamSynchronize(st);
         return s;
@@ -857,10 +858,21 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
     hipError_t e = c->timed(K_PREP, -1, st, [&] { return cx_launch_prep(g, d, in, st); });
     if (e != hipSuccess) return fail(GBSUB_E_DEVICE);
     auto body = [&](int64_t ti) {
+        if (two) {
+            hipError_t r = c->timed_ext(K_MEDIAN, ti, [&](hipEvent_t a, hipEvent_t b) {
+                return cx_launch_next(g, d, st, a, b);
+            });
+            if (r == hipSuccess) r = c->timed(K_SNR, ti, st, [&] { return cx_launch_snr(g, d, in, st); });
+            return r;
+        }
         hipError_t r = c->timed(K_XUPDATE, ti, st, [&] { return cx_launch_power(g, d, in, st); });
         if (r == hipSuccess)
             r = c->timed_ext(K_MEDIAN, ti, [&](hipEvent_t a, hipEvent_t b) { return cx_launch_psd(g, d, st, a, b); });
-        if (r == hipSuccess) r = c->timed(K_SNR, ti, st, [&] { return cx_launch_snr(g, d, in, st); });
+        if (r == hipSuccess)
+            r = c->timed(K_SNR, ti, st, [&] {
+                const hipError_t q = cx_launch_snr(g, d, in, st);
+                return q == hipSuccess ? launch_cx_tail(d.slots, st) : q;
+            });
         return r;
     };
     // loop bodies paced by the progress word, as in gbsub_run
@@ -870,10 +882,11 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
     uint32_t seen_prev = 0;
     auto quiet_since = std::chrono::steady_clock::now();
     for (;;) {
-        const uint32_t w = *prog;
+        const uint64_t w = *prog;
         if (w & 1u) break;
-        const uint32_t seen = w >> 1;
+        const uint32_t seen = (uint32_t)w >> 1;
         if (t < (uint64_t)seen + AHEAD) {
+            two = two || (seen > 0 && (uint32_t)(w >> 32) <= g.split_tiles);
             if (t > guard) return fail(GBSUB_E_DEVICE);
             if (body((int64_t)t) != hipSuccess) return fail(GBSUB_E_DEVICE);
             ++t;

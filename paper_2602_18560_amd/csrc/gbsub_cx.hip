@@ -163,16 +163,6 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Fixed-point exponent E: every template component is at most A T / 2, so
-// with m = max(n, 4096) sources the sum of the n components of one word
-// stays below 2^62 and a single component below 2^50 (which the rounding
-// of fxm needs).
-__device__ __forceinline__ int cx_exp(uint32_t amax_bits, uint32_t n, double T)
-{
-    const double v = (double)max(n, 4096u) * (double)__uint_as_float(amax_bits) * (T * 0.5);
-    if (!(v > 0.0)) return 0;
-    return 61 - ilogb(v);
-}
 
 // v (already in units of 2^-E, |v| < 2^51) rounded to the nearest integer,
 // ties to even: v + 1.5 2^52 lies in [2^52, 2^53), where the spacing of
@@ -435,12 +425,27 @@ __device__ __forceinline__ int bin_tile(const Grid &g, int qb)
 
 // ------------------------------------------------------------------ prep
 
+// Clears the run's state and fills the grid tables: S_instr, 1/S_instr and its
+// maximum over each 128-bin segment (a wave per segment).  (One launch: the
+// tables in two of their own took 10 us more at 1e4 sources.)
 __global__ __launch_bounds__(WG) void k_cx_reset(KArgs a)
 {
     const Grid &g = a.g;
     const CxDev &d = a.d;
     const size_t stride = (size_t)gridDim.x * WG;
     const size_t i0 = (size_t)blockIdx.x * WG + threadIdx.x;
+    const int nseg = (g.B + NF - 1) / NF;
+    for (int seg = (int)(i0 >> 6); seg < nseg; seg += (int)(stride >> 6)) {
+        double m = 0.0;
+        for (int k = seg * NF + lane(); k < min((seg + 1) * NF, g.B); k += 64) {
+            const double v = sinstr_dev((double)(g.k0 + k) / g.T, g.oms_pm, g.tm_fm, g.arm_m), i = 1.0 / v;
+            d.sx[k] = v;
+            d.isx[k] = i;
+            m = fmax(m, i);
+        }
+        for (int o = 32; o >= 1; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
+        if (lane() == 0) d.isx_max[seg] = m;
+    }
     for (size_t k = i0; k < 4 * (size_t)g.B; k += stride) d.h[k] = 0;
     for (size_t k = i0; k <= (size_t)d.ntc; k += stride) {
         d.tcnt[k] = 0;
@@ -456,6 +461,7 @@ __global__ __launch_bounds__(WG) void k_cx_reset(KArgs a)
         sl.g = g;
         sl.d.sx = d.sx;
         sl.d.X = d.X + i0 * (size_t)g.B;
+        sl.d.h = d.h + 2 * i0 * (size_t)g.B;
         sl.d.S = d.S + i0 * (size_t)g.B;
         sl.d.is_pre = d.is_pre + i0 * (size_t)g.B;
         sl.d.is_psum = d.is_psum + i0 * (size_t)g.nparts;
@@ -465,6 +471,7 @@ __global__ __launch_bounds__(WG) void k_cx_reset(KArgs a)
         sl.d.ctl = d.ctl;
         sl.n = a.in.n;
         sl.active = 1;
+        sl.prog = a.in.prog;
         d.slots[i0] = sl;
     }
     if (i0 == 0) {
@@ -492,28 +499,6 @@ __global__ __launch_bounds__(WG) void k_cx_reset(KArgs a)
         c->n_new_body = 0;
         c->res_cursor = 0;
     }
-}
-
-__global__ __launch_bounds__(WG) void k_cx_sinstr(KArgs a)
-{
-    const int k = blockIdx.x * WG + threadIdx.x;
-    if (k >= a.g.B) return;
-    const double v = sinstr_dev((double)(a.g.k0 + k) / a.g.T, a.g.oms_pm, a.g.tm_fm, a.g.arm_m);
-    a.d.sx[k] = v;
-    a.d.isx[k] = 1.0 / v;
-}
-
-// Largest 1/S_instr of each 128-bin segment (one wave per segment).
-__global__ __launch_bounds__(WG) void k_cx_isxmax(KArgs a)
-{
-    const int seg = blockIdx.x * (WG / 64) + (threadIdx.x >> 6);
-    const int nseg = (a.g.B + NF - 1) / NF;
-    if (seg >= nseg) return;
-    const int k0 = seg * NF + lane(), k1 = k0 + 64;
-    double m = k0 < a.g.B ? a.d.isx[k0] : 0.0;
-    if (k1 < a.g.B) m = fmax(m, a.d.isx[k1]);
-    for (int o = 32; o >= 1; o >>= 1) m = fmax(m, __shfl_xor(m, o, 64));
-    if (lane() == 0) a.d.isx_max[seg] = m;
 }
 
 // Whether the moment path takes a source (the "faint" sources, see
@@ -1533,6 +1518,10 @@ __global__ __launch_bounds__(WG) void k_cx_snr(KArgs a)
             }
         }
     }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        c->xupd = nxt;
+        c->tail_due = 1;
+    }
     if (lane() == 0) {
         if (my_new) atomicAdd(&c->n_new_body, my_new);
         if (my_near) atomicAdd((unsigned long long *)&c->n_near, (unsigned long long)my_near);
@@ -1540,87 +1529,6 @@ __global__ __launch_bounds__(WG) void k_cx_snr(KArgs a)
         if (minm < INFINITY)
             atomicMin((unsigned long long *)&c->min_margin, (unsigned long long)__double_as_longlong(minm));
     }
-}
-
-// The body's end (one block): the stop decision, the split mode of the next
-// median launch, and the progress word for the host.
-__global__ __launch_bounds__(WG) void k_cx_tail(KArgs a)
-{
-    __shared__ uint32_t s_nds[WG / 64];
-    const Grid &g = a.g;
-    const CxDev &d = a.d;
-    Ctl *c = d.ctl;
-    if (c->done) return;
-    __shared__ uint32_t s_wl[WG / 64];
-    const uint32_t t = c->iter, nxt = t + 1;
-    uint32_t nds = 0;
-    uint64_t units = 0;
-    // the tiles the next PSD launch filters, listed in tile order
-    uint32_t listed = 0;
-    for (int base = 0; base < g.nt; base += WG) {
-        const int tl = base + (int)threadIdx.x;
-        bool sd = false;
-        if (tl < g.nt) {
-            sd = d.sstamp[tl] == nxt;
-            nds += sd;
-            if (d.xstamp[tl] == nxt) units += (uint64_t)min(g.tile, g.B - tl * g.tile);
-        }
-        const uint64_t m = (uint64_t)__ballot(sd);
-        if (lane() == 0) s_wl[threadIdx.x >> 6] = (uint32_t)__popcll(m);
-        __syncthreads();
-        uint32_t pre = 0, tot = 0;
-#pragma unroll
-        for (int v = 0; v < WG / 64; ++v) {
-            pre += v < (int)(threadIdx.x >> 6) ? s_wl[v] : 0u;
-            tot += s_wl[v];
-        }
-        if (sd) d.sdl[listed + pre + (uint32_t)__popcll(m & ((1ull << lane()) - 1ull))] = (uint32_t)tl;
-        listed += tot;
-        __syncthreads();
-    }
-    for (int o = 32; o >= 1; o >>= 1) {
-        nds += (uint32_t)__shfl_xor((int)nds, o, 64);
-        units += (uint64_t)__shfl_xor((long long)units, o, 64);
-    }
-    __shared__ uint64_t s_units[WG / 64];
-    if (lane() == 0) {
-        s_nds[threadIdx.x >> 6] = nds;
-        s_units[threadIdx.x >> 6] = units;
-    }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    uint32_t done = 0;
-    if (c->bad) {
-        done = 1;
-        c->n_iter = t;
-    } else {
-        for (int v = 1; v < WG / 64; ++v) {
-            s_nds[0] += s_nds[v];
-            s_units[0] += s_units[v];
-        }
-        const uint32_t n_new = c->n_new_body;
-        c->n_new_body = 0;
-        c->n_resolved += n_new;
-        const uint32_t mi = g.max_iter ? g.max_iter : c->cand_cursor + 1;
-        if (n_new == 0) {
-            done = 1;
-            c->n_iter = nxt;
-        } else if (nxt >= mi) {
-            done = 1;
-            c->status = 6;
-            c->n_iter = nxt;
-        } else {
-            c->iter = nxt;
-            c->med_split = s_nds[0] <= g.split_tiles;
-            c->n_sdl = s_nds[0];
-            c->units_x += s_units[0];
-            c->units_med += s_units[0];
-        }
-    }
-    c->n_cand = c->cand_cursor;
-    c->done = done;
-    if (a.in.prog)
-        __hip_atomic_store(a.in.prog, (nxt << 1) | done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ------------------------------------------------------------------ outputs
@@ -1735,9 +1643,6 @@ hipError_t cx_launch_prep(const Grid &g, const CxDev &d, const CxIn &in, hipStre
 {
     const KArgs a = args_of(g, d, in);
     k_cx_reset<<<1024, WG, 0, st>>>(a);
-    k_cx_sinstr<<<(g.B + WG - 1) / WG, WG, 0, st>>>(a);
-    const int nseg = (g.B + NF - 1) / NF;
-    k_cx_isxmax<<<(nseg + WG / 64 - 1) / (WG / 64), WG, 0, st>>>(a);
     const uint32_t nb = (in.n + SRC_PB - 1) / SRC_PB;
     if (nb) k_cx_count<<<nb, WG, 0, st>>>(a);
     k_cx_plan<<<1, PLAN_T, 0, st>>>(a);
@@ -1763,7 +1668,8 @@ hipError_t cx_launch_power(const Grid &g, const CxDev &d, const CxIn &in, hipStr
     return hipGetLastError();
 }
 
-hipError_t cx_launch_psd(const Grid &g, const CxDev &d, hipStream_t st, hipEvent_t ea, hipEvent_t eb)
+namespace {
+Dims channel_dims(const Grid &g)
 {
     Dims dm{};
     dm.ns = 2;
@@ -1773,14 +1679,23 @@ hipError_t cx_launch_psd(const Grid &g, const CxDev &d, hipStream_t st, hipEvent
     dm.maxparts = g.nparts;
     dm.maxlist = list_entries(g);
     dm.est_mask = 1u << g.est;
-    return launch_median(d.slots, dm, st, ea, eb);
+    return dm;
+}
+}  // namespace
+
+hipError_t cx_launch_psd(const Grid &g, const CxDev &d, hipStream_t st, hipEvent_t ea, hipEvent_t eb)
+{
+    return launch_median(d.slots, channel_dims(g), st, ea, eb);
+}
+
+hipError_t cx_launch_next(const Grid &g, const CxDev &d, hipStream_t st, hipEvent_t ea, hipEvent_t eb)
+{
+    return launch_next(d.slots, channel_dims(g), st, ea, eb);
 }
 
 hipError_t cx_launch_snr(const Grid &g, const CxDev &d, const CxIn &in, hipStream_t st)
 {
-    const KArgs a = args_of(g, d, in);
-    k_cx_snr<<<SNR_GRID, WG, 0, st>>>(a);
-    k_cx_tail<<<1, WG, 0, st>>>(a);
+    k_cx_snr<<<SNR_GRID, WG, 0, st>>>(args_of(g, d, in));
     return hipGetLastError();
 }
 

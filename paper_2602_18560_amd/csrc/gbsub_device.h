@@ -63,6 +63,17 @@ DEVI void window_reach(const Grid &g, int lo, int hi, int *a, int *b)
     *b = (whole || hi >= g.B - g.W) ? g.B - 1 : hi + g.h;
 }
 
+// Fixed-point exponent E of the template model's data: every template
+// component is at most A T / 2, so with m = max(n, 4096) sources the sum of the
+// n components of one word stays below 2^62 and a single component below 2^50
+// (which the rounding of fxm needs).
+DEVI int cx_exp(uint32_t amax_bits, uint32_t n, double T)
+{
+    const double v = (double)max(n, 4096u) * (double)__uint_as_float(amax_bits) * (T * 0.5);
+    if (!(v > 0.0)) return 0;
+    return 61 - ilogb(v);
+}
+
 // A record to host-mapped memory, in 8-byte words: lane w of the calling threads
 // stores word w (lane: 0, 1, .. at least the record's words).
 template <typename T> DEVI void put_host(T *dst, const T *src, int lane)

@@ -148,6 +148,7 @@ struct Dev {
     FF *Dc;                  // [B+1]  difference array of the wider tracks
     FF *Dtc;                 // [nt+1] per-tile sums of Dc (binning and subtractions)
     double *X;               // [B]    X^t
+    const int64_t *h;        // template model: re and im of the channel's data, [2][B] in units of 2^-E
     double *S;               // [B]    S^t
     double *is_pre;          // [B]    inclusive prefix of 1/S^t inside each part (an FF in the
                              //        compensated FP32 mode, a float in the naive one)
@@ -235,7 +236,10 @@ hipError_t launch_xupdate(const Slot *ds, const Dims &dm, hipStream_t st, hipEve
                           hipEvent_t eb = nullptr);
 hipError_t launch_median(const Slot *ds, const Dims &dm, hipStream_t st, hipEvent_t ea = nullptr,
                          hipEvent_t eb = nullptr);
-// X update, PSD and the previous body's tail in one launch (one FP64 slot).
+// Template model's tail (the two channels' slots).
+hipError_t launch_cx_tail(const Slot *ds, hipStream_t st);
+// X update, PSD and the previous body's tail in one launch: one FP64 slot, or
+// the two channels of the template model.
 hipError_t launch_next(const Slot *ds, const Dims &dm, hipStream_t st, hipEvent_t ea = nullptr,
                        hipEvent_t eb = nullptr);
 hipError_t launch_snr(const Slot *ds, const Dims &dm, hipStream_t st, hipEvent_t ea = nullptr,
@@ -308,16 +312,19 @@ struct CxIn {
     const float *A, *F, *FD, *PA, *PE;
     const uint32_t *ids;
     uint32_t n;
-    uint32_t *prog;
+    uint64_t *prog;          // Slot::prog
     Ctl *host_ctl;           // host-mapped copy of the control block, written by k_cx_ids
 };
 hipError_t cx_launch_prep(const Grid &g, const CxDev &d, const CxIn &in, hipStream_t st);
 // A loop body: X update, the PSD of both channels (the median or mean
 // kernels; optional events stamped by the dispatch), SNR + subtraction and
-// the tail.
+// the tail (launch_cx_tail); or, once few tiles are dirty, cx_launch_next (X
+// update, PSD and the tail of the body before) and the SNR.
 hipError_t cx_launch_power(const Grid &g, const CxDev &d, const CxIn &in, hipStream_t st);
 hipError_t cx_launch_psd(const Grid &g, const CxDev &d, hipStream_t st, hipEvent_t ea = nullptr,
                          hipEvent_t eb = nullptr);
+hipError_t cx_launch_next(const Grid &g, const CxDev &d, hipStream_t st, hipEvent_t ea = nullptr,
+                          hipEvent_t eb = nullptr);
 hipError_t cx_launch_snr(const Grid &g, const CxDev &d, const CxIn &in, hipStream_t st);
 hipError_t cx_launch_outputs(const Grid &g, const CxDev &d, const CxIn &in, hipStream_t st);
 // h_ch in fp64, re and im of bin k at out[2k], out[2k + 1].

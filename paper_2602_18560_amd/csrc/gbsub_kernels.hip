@@ -1609,10 +1609,37 @@ DEVI void fresh_union(const Grid &g, const Dev &d, int u0, int u1, I128 *st, dou
     __syncthreads();
 }
 
-// The work of one tile (or part) of a PSD launch.  FRESH: X comes from
-// the accumulators (fresh_union); the block stores the bins of its own outputs
-// where their tile's X has changed.
-template <bool FRESH>
+// X over the union from the template model's data, X = (2/T) |h|^2, as
+// fresh_union; the arithmetic is k_cx_power's.
+DEVI void fresh_union_cx(const Slot &sl, int u0, int u1, double (&xr)[MCH])
+{
+    const Grid &g = sl.g;
+    const int64_t *re = sl.d.h, *im = re + (size_t)g.B;
+    int64_t a[MCH], b[MCH];
+#pragma unroll
+    for (int i = 0; i < MCH; ++i) {
+        if (u0 + i * MWG > u1) continue;
+        const int k = min(u0 + (int)threadIdx.x + i * MWG, u1);
+        a[i] = re[k];
+        b[i] = im[k];
+    }
+    const int E = cx_exp(sl.d.ctl->amax_bits, (uint32_t)sl.n, g.T);
+    const double s2 = 2.0 / g.T;
+#pragma unroll
+    for (int i = 0; i < MCH; ++i) {
+        if (u0 + i * MWG > u1) continue;
+        const double x = ldexp((double)a[i], -E), y = ldexp((double)b[i], -E);
+        xr[i] = s2 * (x * x + y * y);
+    }
+}
+
+// Where a PSD launch takes X from: the array (converted by an earlier launch),
+// the accumulators, or the template model's data.
+enum XSource { X_ARRAY, X_ACCUM, X_CX };
+
+// The work of one tile (or part) of a PSD launch.  When X is converted here,
+// the block stores the bins of its own outputs where their tile's X has changed.
+template <XSource SRC>
 DEVI void median_work(MedianSmem &sm, const Slot *slp, int blk, int span)
 {
     const Grid g = slp->g;
@@ -1632,10 +1659,13 @@ DEVI void median_work(MedianSmem &sm, const Slot *slp, int blk, int span)
     double xr[MCH], sxr[RMAX];
 #pragma unroll
     for (int r = 0; r < RMAX; ++r) sxr[r] = d.sx[min(t0 + tid + r * MWG, t1 - 1)];
-    if constexpr (FRESH) {
+    if constexpr (SRC != X_ARRAY) {
         static_assert(FST * sizeof(I128) <= sizeof(MedianSmem), "fresh_union's LDS");
         const bool store = d.xstamp[div_p2(t0, g.tile)] == d.ctl->xupd;
-        fresh_union(g, d, u0, u1, reinterpret_cast<I128 *>(&sm), xr);
+        if constexpr (SRC == X_ACCUM)
+            fresh_union(g, d, u0, u1, reinterpret_cast<I128 *>(&sm), xr);
+        else
+            fresh_union_cx(*slp, u0, u1, xr);
 #pragma unroll
         for (int i = 0; i < MCH; ++i) {
             const int k = u0 + tid + i * MWG;
@@ -2058,11 +2088,11 @@ __global__ __launch_bounds__(MWG, 2) void k_median(const Slot *S)
     const int blk = blockIdx.x;
     const int tile = split ? blk / g.np : blk;
     if (tile >= g.nt || blk * span >= g.B || d.sstamp[tile] != d.ctl->iter) return;
-    median_work<false>(sm, &sl, blk, span);
+    median_work<X_ARRAY>(sm, &sl, blk, span);
 }
 
-// A body's X update, PSD and the previous body's tail in one launch (one
-// slot, FP64, few dirty tiles): block 0 is the tail of the k_snr before it,
+// A body's X update, PSD and the previous body's tail in one launch (one FP64
+// slot, or the template model's two channels; few dirty tiles): block 0 is the tail of the k_snr before it,
 // the others take a part each, convert its union from the accumulators and
 // filter it.  They touch disjoint data: the blocks read the accumulators, the
 // stamps and the control fields set before the launch (xupd, the stamp of this
@@ -2075,21 +2105,27 @@ __global__ __launch_bounds__(MWG, 2) void k_median(const Slot *S)
 // part reads 32 bytes of accumulators per bin, from its first tile's start,
 // where the two launches read 8 of X; taken while the dirty tiles fit the
 // split budget (at most one wave of part-sized blocks on the chip), where the
-// launch is latency, not traffic.
+// launch is latency, not traffic.  (Template model: X needs no prefix, and the
+// X update and tail launches it saves took 7.4 and 6.1 us a body.)
 template <int NT> DEVI void snr_tail(const Slot &sl);
-__global__ __launch_bounds__(MWG, 4) void k_median_next(const Slot *S)
+template <int NT> DEVI void cx_tail(const Slot &sl);
+template <XSource SRC> __global__ __launch_bounds__(MWG, 4) void k_median_next(const Slot *S)
 {
     __shared__ MedianSmem sm;
-    const Slot &sl = *S;
+    const Slot &sl = S[blockIdx.y];
     if (blockIdx.x == 0) {
-        snr_tail<MWG>(sl);
+        if constexpr (SRC == X_CX) {
+            if (blockIdx.y == 0) cx_tail<MWG>(sl);
+        } else {
+            snr_tail<MWG>(sl);
+        }
         return;
     }
     const Grid g = sl.g;
     const Dev d = sl.d;
     const int blk = blockIdx.x - 1;
     if (d.ctl->bad || d.sstamp[blk / g.np] != d.ctl->xupd) return;
-    median_work<true>(sm, &sl, blk, g.part);
+    median_work<SRC>(sm, &sl, blk, g.part);
 }
 
 // The launch of several slots (batches, the template model's two channels):
@@ -2114,7 +2150,7 @@ __global__ __launch_bounds__(MWG, 2) void k_median_listed(const Slot *S)
     if (e >= (int)d.ctl->n_sdl * (split ? g.np : 1)) return;
     const int tile = (int)d.sdl[split ? e / g.np : e];
     const int blk = split ? tile * g.np + e % g.np : tile;
-    if (blk * span < g.B) median_work<false>(sm, &sl, blk, span);
+    if (blk * span < g.B) median_work<X_ARRAY>(sm, &sl, blk, span);
 }
 
 // ------------------------------------------------------------------ running mean
@@ -2131,7 +2167,7 @@ struct MeanSmem {
 };
 
 // The work of one tile (or part) of a PSD launch.
-template <bool FRESH>
+template <XSource SRC>
 DEVI void mean_work(MeanSmem &sm, const Slot *slp, int blk, int span, I128 *st = nullptr)
 {
     const Grid g = slp->g;
@@ -2145,10 +2181,13 @@ DEVI void mean_work(MeanSmem &sm, const Slot *slp, int blk, int span, I128 *st =
     const int u1 = whole ? B - 1 : win_start(t1 - 1, B, W, h) + W - 1;
     const int M = u1 - u0 + 1;
 
-    if constexpr (FRESH) {
+    if constexpr (SRC != X_ARRAY) {
         const bool store = d.xstamp[div_p2(t0, g.tile)] == d.ctl->xupd;
         double xr[MCH];
-        fresh_union(g, d, u0, u1, st, xr);
+        if constexpr (SRC == X_ACCUM)
+            fresh_union(g, d, u0, u1, st, xr);
+        else
+            fresh_union_cx(*slp, u0, u1, xr);
 #pragma unroll
         for (int i = 0; i < MCH; ++i) {
             const int p = tid + i * MWG;
@@ -2216,26 +2255,30 @@ __global__ __launch_bounds__(MWG) void k_mean(const Slot *S)
     const int blk = blockIdx.x;
     const int tile = split ? blk / g.np : blk;
     if (tile >= g.nt || blk * span >= g.B || d.sstamp[tile] != d.ctl->iter) return;
-    mean_work<false>(sm, &sl, blk, span);
+    mean_work<X_ARRAY>(sm, &sl, blk, span);
 }
 
 // As k_median_next.
-__global__ __launch_bounds__(MWG) void k_mean_next(const Slot *S)
+template <XSource SRC> __global__ __launch_bounds__(MWG) void k_mean_next(const Slot *S)
 {
     __shared__ union {
         MeanSmem mean;
-        I128 st[FST];
+        I128 st[SRC == X_ACCUM ? FST : 1];
     } sm;
-    const Slot &sl = *S;
+    const Slot &sl = S[blockIdx.y];
     if (blockIdx.x == 0) {
-        snr_tail<MWG>(sl);
+        if constexpr (SRC == X_CX) {
+            if (blockIdx.y == 0) cx_tail<MWG>(sl);
+        } else {
+            snr_tail<MWG>(sl);
+        }
         return;
     }
     const Grid g = sl.g;
     const Dev d = sl.d;
     const int blk = blockIdx.x - 1;
     if (d.ctl->bad || d.sstamp[blk / g.np] != d.ctl->xupd) return;
-    mean_work<true>(sm.mean, &sl, blk, g.part, sm.st);
+    mean_work<SRC>(sm.mean, &sl, blk, g.part, sm.st);
 }
 
 // The launch of several slots, as k_median_listed.
@@ -2253,7 +2296,7 @@ __global__ __launch_bounds__(MWG) void k_mean_listed(const Slot *S)
     if (e >= (int)d.ctl->n_sdl * (split ? g.np : 1)) return;
     const int tile = (int)d.sdl[split ? e / g.np : e];
     const int blk = split ? tile * g.np + e % g.np : tile;
-    if (blk * span < g.B) mean_work<false>(sm, &sl, blk, span);
+    if (blk * span < g.B) mean_work<X_ARRAY>(sm, &sl, blk, span);
 }
 
 // ------------------------------------------------------------------ SNR, decisions, subtraction
@@ -2610,6 +2653,49 @@ __global__ __launch_bounds__(WG) void k_snr(const Slot *S)
     }
 }
 
+// Counts the tiles stamped for body nxt (the thread's share of the X stamps to
+// *nx) and lists those to filter in tile order; returns the list's length.
+// One block of NT threads: rounds of TW tiles per thread, all stamps of a round
+// loaded together.  One tile per thread and round, with two barriers each,
+// were 8 rounds of load latency for 1843 tiles and 15 for 3686: the launch
+// took 10.8 and 14 us a body instead of 9.9 and 11.3.
+template <int NT>
+DEVI uint32_t list_stamped(const Grid &g, const Dev &d, uint32_t nxt, uint32_t (&s_wl)[2][NT / 64], uint32_t *nx)
+{
+    constexpr int TW = 2048 / NT;
+    const int w = threadIdx.x >> 6;
+    uint32_t listed = 0;                  // block-uniform
+    for (int base = 0, rd = 0; base < g.nt; base += NT * TW, rd ^= 1) {
+        const int t0 = base + (int)threadIdx.x * TW;
+        uint32_t xs[TW], ss[TW];
+#pragma unroll
+        for (int q = 0; q < TW; ++q) {
+            const int tl = min(t0 + q, g.nt - 1);
+            xs[q] = d.xstamp[tl];
+            ss[q] = d.sstamp[tl];
+        }
+        uint32_t mask = 0;
+#pragma unroll
+        for (int q = 0; q < TW; ++q) {
+            if (t0 + q >= g.nt) continue;
+            *nx += xs[q] == nxt;
+            mask |= (ss[q] == nxt ? 1u : 0u) << q;
+        }
+        const uint32_t own = (uint32_t)__popc(mask), inc = wave_scan_u32(own);
+        if (lane_id() == 63) s_wl[rd][w] = inc;
+        __syncthreads();
+        uint32_t at = listed + inc - own;
+#pragma unroll
+        for (int v = 0; v < NT / 64; ++v) {
+            const uint32_t x = s_wl[rd][v];
+            at += v < w ? x : 0u;
+            listed += x;
+        }
+        for (; mask; mask &= mask - 1) d.sdl[at++] = (uint32_t)(t0 + __builtin_ctz(mask));
+    }
+    return listed;
+}
+
 // The tail of a loop body, run by one block of NT threads once k_snr has
 // ended: combines the per-block partials, counts the tiles stamped for the
 // next body, takes the stop decision (nothing new subtracted, or max_iter)
@@ -2635,41 +2721,8 @@ template <int NT> DEVI void snr_tail(const Slot &sl)
     SnrPart p[NP];
 #pragma unroll
     for (int i = 0; i < NP; ++i) p[i] = d.b_part[threadIdx.x + i * NT];
-    // stamped-tile counts, and the list of the tiles to filter in the next
-    // body in tile order: rounds of TW tiles per thread, all stamps of a round
-    // loaded together.  One tile per thread and round, with two barriers each,
-    // were 8 rounds of load latency for 1843 tiles and 15 for 3686: the launch
-    // took 10.8 and 14 us a body instead of 9.9 and 11.3
-    constexpr int TW = 2048 / NT;
-    uint32_t nx = 0, listed = 0;          // listed is block-uniform
-    for (int base = 0, rd = 0; base < g.nt; base += NT * TW, rd ^= 1) {
-        const int t0 = base + (int)threadIdx.x * TW;
-        uint32_t xs[TW], ss[TW];
-#pragma unroll
-        for (int q = 0; q < TW; ++q) {
-            const int tl = min(t0 + q, g.nt - 1);
-            xs[q] = d.xstamp[tl];
-            ss[q] = d.sstamp[tl];
-        }
-        uint32_t mask = 0;
-#pragma unroll
-        for (int q = 0; q < TW; ++q) {
-            if (t0 + q >= g.nt) continue;
-            nx += xs[q] == nxt;
-            mask |= (ss[q] == nxt ? 1u : 0u) << q;
-        }
-        const uint32_t own = (uint32_t)__popc(mask), inc = wave_scan_u32(own);
-        if (lane_id() == 63) s_wl[rd][w] = inc;
-        __syncthreads();
-        uint32_t at = listed + inc - own;
-#pragma unroll
-        for (int v = 0; v < NW; ++v) {
-            const uint32_t x = s_wl[rd][v];
-            at += v < w ? x : 0u;
-            listed += x;
-        }
-        for (; mask; mask &= mask - 1) d.sdl[at++] = (uint32_t)(t0 + __builtin_ctz(mask));
-    }
+    uint32_t nx = 0;
+    const uint32_t listed = list_stamped<NT>(g, d, nxt, s_wl, &nx);
     uint32_t red[NR] = {0, 0, 0, nx};
     double minm = INFINITY;
 #pragma unroll
@@ -2728,6 +2781,64 @@ template <int NT> DEVI void snr_tail(const Slot &sl)
         __hip_atomic_store(sl.prog, (uint64_t)listed << 32 | nxt << 1 | done, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
 }
+
+// The template model's tail, run by one block of NT threads once k_cx_snr has
+// ended: the stop decision, the split mode of the next PSD launch, the list of
+// its tiles, and the progress word for the host.  It runs at most once per
+// k_cx_snr (tail_due); an invalid catalog settles at once.
+template <int NT> DEVI void cx_tail(const Slot &sl)
+{
+    __shared__ uint32_t s_wl[2][NT / 64];
+    __shared__ uint32_t s_nx;
+    const Grid g = sl.g;
+    const Dev d = sl.d;
+    Ctl *c = d.ctl;
+    const Ctl k = *c;
+    if (k.done || !(k.tail_due || k.bad)) return;
+    const uint32_t nxt = k.iter + 1;
+    const uint32_t lx = d.xstamp[g.nt - 1];
+    if (threadIdx.x == 0) s_nx = 0;
+    __syncthreads();
+    uint32_t nx = 0;
+    const uint32_t listed = list_stamped<NT>(g, d, nxt, s_wl, &nx);
+    nx = wave_scan_u32(nx);
+    if (lane_id() == 63 && nx) atomicAdd(&s_nx, nx);
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    uint32_t done = 0;
+    c->tail_due = 0;
+    if (k.bad) {
+        done = 1;
+        c->n_iter = k.iter;
+    } else {
+        const uint64_t units = (uint64_t)s_nx * (uint32_t)g.tile - (lx == nxt ? (uint32_t)(g.nt * g.tile - g.B) : 0u);
+        const uint32_t n_new = k.n_new_body;
+        c->n_new_body = 0;
+        c->n_resolved = k.n_resolved + n_new;
+        const uint32_t mi = g.max_iter ? g.max_iter : k.cand_cursor + 1;
+        if (n_new == 0) {
+            done = 1;
+            c->n_iter = nxt;
+        } else if (nxt >= mi) {
+            done = 1;
+            c->status = 6;
+            c->n_iter = nxt;
+        } else {
+            c->iter = nxt;
+            c->med_split = listed <= g.split_tiles;
+            c->n_sdl = listed;
+            c->units_x = k.units_x + units;
+            c->units_med = k.units_med + units;
+        }
+    }
+    c->n_cand = k.cand_cursor;
+    c->done = done;
+    if (sl.prog)
+        __hip_atomic_store(sl.prog, (uint64_t)listed << 32 | nxt << 1 | done, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+__global__ __launch_bounds__(WG) void k_cx_tail(const Slot *S) { cx_tail<WG>(*S); }
 
 // The tail as a kernel of its own, ahead of k_xupdate: the naive FP32 mode
 // rescans the fp32 tile sums into the carries that k_xupdate reads.
@@ -2818,8 +2929,16 @@ hipError_t launch_median(const Slot *ds, const Dims &dm, hipStream_t st, hipEven
 
 hipError_t launch_next(const Slot *ds, const Dims &dm, hipStream_t st, hipEvent_t ea, hipEvent_t eb)
 {
-    const void *k = dm.est_mask & 2u ? (const void *)k_mean_next : (const void *)k_median_next;
-    return go(k, dim3(dm.maxparts + 1), dim3(MWG), st, ea, eb, ds);
+    const bool mean = dm.est_mask & 2u, cx = dm.ns == 2;
+    const void *k = mean ? (cx ? (const void *)k_mean_next<X_CX> : (const void *)k_mean_next<X_ACCUM>)
+                         : (cx ? (const void *)k_median_next<X_CX> : (const void *)k_median_next<X_ACCUM>);
+    return go(k, dim3(dm.maxparts + 1, dm.ns), dim3(MWG), st, ea, eb, ds);
+}
+
+hipError_t launch_cx_tail(const Slot *ds, hipStream_t st)
+{
+    k_cx_tail<<<1, WG, 0, st>>>(ds);
+    return hipGetLastError();
 }
 
 hipError_t launch_snr(const Slot *ds, const Dims &dm, hipStream_t st, hipEvent_t ea, hipEvent_t eb)
