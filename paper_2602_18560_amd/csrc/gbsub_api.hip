@@ -288,6 +288,7 @@ Dims dims_of(const Slot &sl)
     dm.maxtile = sl.g.tile;
     dm.maxparts = sl.g.nparts;
     dm.maxlist = list_entries(sl.g);
+    dm.split_parts = split_parts(sl.g);
     dm.est_mask = 1u << sl.g.est;
     dm.naive = sl.g.prec == PREC_NAIVE;
     dm.prep_blocks = (uint32_t)((sl.n + sl.d.prep_src - 1) / sl.d.prep_src);

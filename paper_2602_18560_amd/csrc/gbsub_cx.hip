@@ -1678,6 +1678,7 @@ Dims channel_dims(const Grid &g)
     dm.maxtile = g.tile;
     dm.maxparts = g.nparts;
     dm.maxlist = list_entries(g);
+    dm.split_parts = split_parts(g);
     dm.est_mask = 1u << g.est;
     return dm;
 }

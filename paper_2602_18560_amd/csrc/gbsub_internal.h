@@ -212,17 +212,18 @@ struct Dims {
     int ns;                  // slots (gridDim.y)
     int maxB, maxnt, maxtile, maxparts;
     int maxlist;             // entries of a listed median launch: every tile, or the split budget's parts
+    int split_parts;         // parts of the split budget
     uint32_t est_mask;       // bit e: some slot uses estimator e
     uint32_t naive;          // some slot runs in naive FP32
     uint32_t prep_blocks, accum_blocks;
     uint64_t max_n;
 };
 
-inline int list_entries(const Grid &g)
+inline int split_parts(const Grid &g)
 {
-    const int parts = (int64_t)g.split_blocks < (int64_t)g.nparts ? (int)g.split_blocks : g.nparts;
-    return g.nt > parts ? g.nt : parts;
+    return (int64_t)g.split_blocks < (int64_t)g.nparts ? (int)g.split_blocks : g.nparts;
 }
+inline int list_entries(const Grid &g) { return g.nt > split_parts(g) ? g.nt : split_parts(g); }
 
 // Kernel launchers (gbsub_kernels.hip); all enqueue on `st` and return the
 // launch status.  `ds` is the device array of `dm.ns` slot descriptors.

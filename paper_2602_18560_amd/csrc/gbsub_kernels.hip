@@ -2107,8 +2107,79 @@ __global__ __launch_bounds__(MWG, 2) void k_median(const Slot *S)
 // split budget (at most one wave of part-sized blocks on the chip), where the
 // launch is latency, not traffic.  (Template model: X needs no prefix, and the
 // X update and tail launches it saves took 7.4 and 6.1 us a body.)
+//
+// Blocks and parts.  One slot: a block per part of the grid, and those of clean
+// tiles exit (7372 blocks, 7.5 us when all do, 5 with the 512 of the split
+// budget).  Two channels: twice the blocks (14 us), so the blocks, one per part
+// of the budget, look their parts up among the stamps (the list is not made
+// yet); should a body have more entries than blocks, they stride over them.
+// The lookup takes 1.5 us of a block's chain: late launches of the 1e7 catalogs
+// 20 us with it instead of 24 for two channels, 21 instead of 20 for one slot
+// (running mean 13 instead of 11).
 template <int NT> DEVI void snr_tail(const Slot &sl);
 template <int NT> DEVI void cx_tail(const Slot &sl);
+
+// The n-th tile (from 0, in tile order) whose stamp is val (-1: there are not as
+// many), and the number of such tiles.  Blocks of MWG threads; contains barriers.
+DEVI int nth_stamped(const Grid &g, const uint32_t *stamp, uint32_t val, int n, int *total)
+{
+    constexpr int NV = MWG / 64, TW = 4;
+    __shared__ int s_cnt[2][NV];
+    __shared__ int s_tile;
+    const int tid = threadIdx.x, wave = tid >> 6;
+    int seen = 0;                                      // block-uniform
+    if (tid == 0) s_tile = -1;
+    for (int base = 0, rd = 0; base < g.nt; base += MWG * TW, rd ^= 1) {
+        const int t0 = base + tid * TW;
+        uint32_t st[TW];
+#pragma unroll
+        for (int q = 0; q < TW; ++q) st[q] = stamp[min(t0 + q, g.nt - 1)];
+        uint32_t mask = 0;
+#pragma unroll
+        for (int q = 0; q < TW; ++q) mask |= (t0 + q < g.nt && st[q] == val ? 1u : 0u) << q;
+        const int own = __popc(mask), inc = (int)wave_scan_u32((uint32_t)own);
+        if (lane_id() == 63) s_cnt[rd][wave] = inc;
+        __syncthreads();
+        int at = seen + inc - own;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const int x = s_cnt[rd][v];
+            at += v < wave ? x : 0;
+            seen += x;
+        }
+        if (n >= at && n < at + own) {
+            for (int q = at; q < n; ++q) mask &= mask - 1;
+            s_tile = t0 + __builtin_ctz(mask);
+        }
+    }
+    __syncthreads();
+    *total = seen;
+    return s_tile;
+}
+
+// The part of entry e of the body stamped xupd (-1: past its last), and the
+// number of its entries.
+DEVI int next_part(const Grid &g, const Dev &d, int e, int *n)
+{
+    int tiles;
+    const int tile = nth_stamped(g, d.sstamp, d.ctl->xupd, e / g.np, &tiles);
+    *n = tiles * g.np;
+    return tile < 0 ? -1 : tile * g.np + e % g.np;
+}
+
+// A block's entries beyond its first (rare: not inlined, so that the loop does
+// not cost the first one registers).
+template <typename M, typename W> __device__ __noinline__ void next_entries(M &sm, const Slot *slp, int e, W work)
+{
+    for (int n;;) {
+        e += (int)gridDim.x - 1;
+        __syncthreads();                               // LDS is reused by the next entry
+        const int blk = next_part(slp->g, slp->d, e, &n);
+        if (blk < 0) return;
+        if (blk * slp->g.part < slp->g.B) work(sm, slp, blk);
+    }
+}
+
 template <XSource SRC> __global__ __launch_bounds__(MWG, 4) void k_median_next(const Slot *S)
 {
     __shared__ MedianSmem sm;
@@ -2121,11 +2192,19 @@ template <XSource SRC> __global__ __launch_bounds__(MWG, 4) void k_median_next(c
         }
         return;
     }
+    if (sl.d.ctl->bad) return;
     const Grid g = sl.g;
-    const Dev d = sl.d;
-    const int blk = blockIdx.x - 1;
-    if (d.ctl->bad || d.sstamp[blk / g.np] != d.ctl->xupd) return;
-    median_work<SRC>(sm, &sl, blk, g.part);
+    const int e = (int)blockIdx.x - 1;
+    if constexpr (SRC == X_CX) {
+        int n;
+        const int blk = next_part(g, sl.d, e, &n);
+        if (blk < 0) return;
+        if (blk * g.part < g.B) median_work<SRC>(sm, &sl, blk, g.part);
+        if (e + (int)gridDim.x - 1 >= n) return;
+        next_entries(sm, &sl, e, [](MedianSmem &m, const Slot *p, int k) { median_work<SRC>(m, p, k, p->g.part); });
+    } else if (sl.d.sstamp[e / g.np] == sl.d.ctl->xupd) {
+        median_work<SRC>(sm, &sl, e, g.part);
+    }
 }
 
 // The launch of several slots (batches, the template model's two channels):
@@ -2259,7 +2338,7 @@ __global__ __launch_bounds__(MWG) void k_mean(const Slot *S)
 }
 
 // As k_median_next.
-template <XSource SRC> __global__ __launch_bounds__(MWG) void k_mean_next(const Slot *S)
+template <XSource SRC> __global__ __launch_bounds__(MWG, 4) void k_mean_next(const Slot *S)
 {
     __shared__ union {
         MeanSmem mean;
@@ -2274,11 +2353,19 @@ template <XSource SRC> __global__ __launch_bounds__(MWG) void k_mean_next(const 
         }
         return;
     }
+    if (sl.d.ctl->bad) return;
     const Grid g = sl.g;
-    const Dev d = sl.d;
-    const int blk = blockIdx.x - 1;
-    if (d.ctl->bad || d.sstamp[blk / g.np] != d.ctl->xupd) return;
-    mean_work<SRC>(sm.mean, &sl, blk, g.part, sm.st);
+    const int e = (int)blockIdx.x - 1;
+    if constexpr (SRC == X_CX) {
+        int n;
+        const int blk = next_part(g, sl.d, e, &n);
+        if (blk < 0) return;
+        if (blk * g.part < g.B) mean_work<SRC>(sm.mean, &sl, blk, g.part, sm.st);
+        if (e + (int)gridDim.x - 1 >= n) return;
+        next_entries(sm, &sl, e, [](auto &m, const Slot *p, int k) { mean_work<SRC>(m.mean, p, k, p->g.part, m.st); });
+    } else if (sl.d.sstamp[e / g.np] == sl.d.ctl->xupd) {
+        mean_work<SRC>(sm.mean, &sl, e, g.part, sm.st);
+    }
 }
 
 // The launch of several slots, as k_median_listed.
@@ -2932,7 +3019,7 @@ hipError_t launch_next(const Slot *ds, const Dims &dm, hipStream_t st, hipEvent_
     const bool mean = dm.est_mask & 2u, cx = dm.ns == 2;
     const void *k = mean ? (cx ? (const void *)k_mean_next<X_CX> : (const void *)k_mean_next<X_ACCUM>)
                          : (cx ? (const void *)k_median_next<X_CX> : (const void *)k_median_next<X_ACCUM>);
-    return go(k, dim3(dm.maxparts + 1, dm.ns), dim3(MWG), st, ea, eb, ds);
+    return go(k, dim3((cx ? dm.split_parts : dm.maxparts) + 1, dm.ns), dim3(MWG), st, ea, eb, ds);
 }
 
 hipError_t launch_cx_tail(const Slot *ds, hipStream_t st)
