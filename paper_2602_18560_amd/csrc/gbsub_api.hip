@@ -132,8 +132,7 @@ uint64_t carve(const Grid &g, uint64_t n, char *base, Dev *d)
     const uint64_t ev_chunks = (max_events + ACC_EV - 1) / ACC_EV;
     Dev t{};
     take(sizeof(Slot));                      // the one-slot table of gbsub_run
-    t.max_chunks = (uint32_t)(ev_chunks + nt);
-    t.max_slots = (uint32_t)(2 * ev_chunks + 2);
+    t.max_chunks = (uint32_t)(std::max<uint64_t>(ev_chunks, ACC_GRID) + nt);
     t.sx = (double *)take(B * 8);
     t.isx = (double *)take(B * 8);
     t.isx_pre = (double *)take(B * 8);
@@ -180,7 +179,13 @@ uint64_t carve(const Grid &g, uint64_t n, char *base, Dev *d)
     t.slot_base = (uint32_t *)take(nt * 4);
     t.ev_key = (uint32_t *)take((max_events ? max_events : 1) * 4);
     t.ev_val = (int64_t *)take((max_events ? max_events : 1) * 8);
-    t.partial = (I128 *)take((uint64_t)t.max_slots * 2 * (uint64_t)g.tile * 16);
+    // partial sums of the hot tiles: in X, S and the 1/S prefixes (free until
+    // the binning has ended) where those hold what the largest accumulation
+    // blocks can need (a tile of nc > 1 blocks has more than (nc - 1) ACC_EV
+    // events, so there are at most 2 ev_chunks)
+    const uint64_t slot_bytes = 2 * (uint64_t)g.tile * 16, least = 2 * ev_chunks + 2, room = 3 * B * 8 / slot_bytes;
+    t.max_slots = (uint32_t)std::max(least, room);
+    t.partial = room >= least ? (I128 *)t.X : (I128 *)take(least * slot_bytes);
     t.cbits = (uint64_t *)take(((nn + 63) / 64) * 8);
     t.rs_hist = (uint32_t *)take(resolved_scratch_words(nn) * 4);
     t.blk_cand = small ? (uint32_t *)t.is_pre : (uint32_t *)take((npb + 1) * 4);

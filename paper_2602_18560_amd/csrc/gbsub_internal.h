@@ -22,7 +22,9 @@ constexpr int CS_WG = 1024;        // threads of a column-pass block
 constexpr int CS_COL = 32;         // tiles of a column-pass block
 constexpr int PLAN_T = 1024;       // threads of the one-block plans
 constexpr int ACC_T = 512;         // threads of an accumulation block
-constexpr int ACC_EV = 65536;      // binning events per accumulation block
+constexpr int ACC_EV = 65536;      // binning events per accumulation block, at most
+constexpr int ACC_EV_MIN = 20480;  // and at least
+constexpr int ACC_GRID = 256;      // full accumulation blocks that fill the chip
 constexpr int RED_BINS = 256;      // bins per reduction block of the hot buckets
 constexpr int NEW_CAP = 1 << 16;   // per-iteration counters kept (iterations beyond: not recorded)
 constexpr int KEYBITS = 18;        // bits of the per-tile order key of the median sort
@@ -81,7 +83,7 @@ struct Ctl {
     uint32_t n_new_body;     // complex-template model: sources subtracted by the running body
     uint32_t n_sdl;          // tiles listed in sdl for the next median launch
     uint32_t res_cursor;     // entries of the resolved list handed out (list_resolved)
-    uint32_t pad;
+    uint32_t acc_ev;         // events per accumulation block
 };
 
 // Per-block partial results of k_snr (combined by the tail: the last block

@@ -205,6 +205,33 @@ template <> DEVI uint32_t zero_t<uint32_t>() { return 0u; }
 template <> DEVI I128 zero_t<I128>() { I128 z; z.lo = 0; z.hi = 0; return z; }
 template <> DEVI FF zero_t<FF>() { return ff_of(0.0f); }
 
+// Inclusive scan of a u32 across the 64 lanes of a wave (DPP row shifts and
+// row broadcasts; every lane must be active).
+DEVI uint32_t wave_scan_u32(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast:15
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast:31
+    return v;
+}
+
+// Smallest (largest) word of the wave, in lane 63.
+DEVI uint32_t wave_min_u32(uint32_t v)
+{
+    auto low = [&](int x) { v = min(v, (uint32_t)x); };
+    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x111, 0xF, 0xF, false));
+    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x112, 0xF, 0xF, false));
+    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x114, 0xF, 0xF, false));
+    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x118, 0xF, 0xF, false));
+    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xA, 0xF, false));
+    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xC, 0xF, false));
+    return v;
+}
+DEVI uint32_t wave_max_u32(uint32_t v) { return ~wave_min_u32(~v); }
+
 // Inclusive scan across the 64 lanes of a wave.
 template <typename T>
 DEVI T wave_incl_scan(T x)
@@ -217,6 +244,8 @@ DEVI T wave_incl_scan(T x)
     }
     return x;
 }
+
+template <> DEVI uint32_t wave_incl_scan<uint32_t>(uint32_t x) { return wave_scan_u32(x); }
 
 // Exclusive scan across the WG threads of a block; *total gets the block sum.
 // `sh` must hold WG/64 elements.  Contains __syncthreads().
@@ -238,19 +267,6 @@ DEVI T block_excl_scan(T x, T *sh, T *total)
     if (lane == 0) ex = zero_t<T>();
     *total = tot;
     return add_t(pre, ex);
-}
-
-// Inclusive scan of a u32 across the 64 lanes of a wave (DPP row shifts and
-// row broadcasts; every lane must be active).
-DEVI uint32_t wave_scan_u32(uint32_t v)
-{
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr:1
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);   // row_shr:2
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);   // row_shr:4
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);   // row_shr:8
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast:15
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast:31
-    return v;
 }
 
 DEVI double wave_sum(double x)
@@ -717,6 +733,8 @@ __global__ __launch_bounds__(CS_WG) void k_prep_colscan(const Slot *S)
     }
 }
 
+DEVI uint32_t acc_events(int k) { return k == 0 ? (uint32_t)ACC_EV_MIN : (uint32_t)ACC_EV / 4u * (uint32_t)(k + 1); }
+
 // Plan (one block): tile bases, accumulation blocks and partial-sum slots;
 // clears the tile sums of D.
 __global__ __launch_bounds__(PLAN_T) void k_prep_plan(const Slot *S)
@@ -727,56 +745,89 @@ __global__ __launch_bounds__(PLAN_T) void k_prep_plan(const Slot *S)
     const Grid g = sl.g;
     const Dev d = sl.d;
 
-    // largest A and the candidates of the count blocks: their exclusive
-    // prefix is each scatter block's first candidate slot
-    {
-        const int nb = (int)((sl.n + d.prep_src - 1) / d.prep_src);
-        uint32_t am = 0;
-        for (int b = threadIdx.x; b < nb; b += PLAN_T) am = max(am, d.blk_amax[b]);
-        for (int s = 32; s >= 1; s >>= 1) am = max(am, (uint32_t)__shfl_xor((int)am, s, 64));
-        if (lane_id() == 0) sh[threadIdx.x >> 6] = am;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            for (int w = 1; w < PLAN_T / 64; ++w) am = max(am, sh[w]);
-            d.ctl->amax_bits = am;
-        }
-        __syncthreads();
-        block_scan_array<uint32_t, PLAN_T>(d.blk_cand, d.blk_cand, nb);   // in place: each thread rereads its own run
-        if (threadIdx.x == 0) d.ctl->n_cand = d.blk_cand[nb];
-        __syncthreads();
-    }
+    // the candidates of the count blocks: their exclusive prefix is each
+    // scatter block's first candidate slot
+    const int nb = (int)((sl.n + d.prep_src - 1) / d.prep_src);
+    uint32_t am = 0;                                   // the largest A
+    for (int b = threadIdx.x; b < nb; b += PLAN_T) am = max(am, d.blk_amax[b]);
+    block_scan_array<uint32_t, PLAN_T>(d.blk_cand, d.blk_cand, nb);   // in place: each thread rereads its own run
 
-    uint32_t carry_e = 0, carry_c = 0, carry_s = 0;
-    for (int base = 0; base < g.nt; base += PLAN_T) {
-        const int b = base + threadIdx.x;
-        const uint32_t cnt = b < g.nt ? d.btot[b] : 0u;
-        const uint32_t nc = b < g.nt ? max(1u, (cnt + ACC_EV - 1) / ACC_EV) : 0u;
-        const uint32_t ns = nc > 1 ? nc : 0u;
-        uint32_t te, tc, ts;
-        const uint32_t ee = block_excl_scan<uint32_t, PLAN_T>(cnt, sh, &te);
-        const uint32_t ec = block_excl_scan<uint32_t, PLAN_T>(nc, sh, &tc);
-        const uint32_t es = block_excl_scan<uint32_t, PLAN_T>(ns, sh, &ts);
-        if (b < g.nt) {
-            d.bbase[b] = carry_e + ee;
-            d.nch[b] = nc;
-            d.chunk_base[b] = carry_c + ec;
-            d.slot_base[b] = carry_s + es;
-            d.Dtile[b].lo = 0;
-            d.Dtile[b].hi = 0;
-            if (g.prec == PREC_COMP) d.Dtc[b] = ff_of(0.0f);
-        }
-        carry_e += te;
-        carry_c += tc;
-        carry_s += ts;
+    // The events of an accumulation block (at most ACC_EV, acc_events' choices):
+    // the fewest that leave at most ACC_GRID full blocks, so that a hot tile
+    // spreads over the chip, and whose hot tiles' partial sums fit.  (2.3e5
+    // sources, whose hot tile has more than 65536 events: k_accum 18 us, 25 with
+    // blocks of 65536; 1e7 sources 53 us, as before; at most 1024 full blocks
+    // instead of 256 doubled their reduction to 30 us.)
+    constexpr int RUN = NBK_MAX / PLAN_T, NC = 4;
+    constexpr int NV = PLAN_T / 64;
+    __shared__ uint32_t s_need[NC + 2][NV];            // per wave: slots by choice, events, largest A
+    const int b0 = (int)threadIdx.x * RUN;
+    uint32_t cnt[RUN], need[NC + 1] = {};
+#pragma unroll
+    for (int r = 0; r < RUN; ++r) cnt[r] = d.btot[min(b0 + r, g.nt - 1)];
+#pragma unroll
+    for (int r = 0; r < RUN; ++r) {
+        cnt[r] = b0 + r < g.nt ? cnt[r] : 0u;
+        need[NC] += cnt[r];
+        if (cnt[r] <= (uint32_t)ACC_EV_MIN) continue;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) need[k] += cnt[r] > acc_events(k) ? (cnt[r] + acc_events(k) - 1) / acc_events(k) : 0u;
     }
+#pragma unroll
+    for (int k = 0; k <= NC; ++k) {
+        const uint32_t x = wave_scan_u32(need[k]);
+        if (lane_id() == 63) s_need[k][threadIdx.x >> 6] = x;
+    }
+    am = wave_max_u32(am);
+    if (lane_id() == 63) s_need[NC + 1][threadIdx.x >> 6] = am;
+    __syncthreads();
+    const int wl = lane_id() < NV ? lane_id() : 0;
+#pragma unroll
+    for (int k = 0; k <= NC; ++k) {
+        const uint32_t x = lane_id() < NV ? s_need[k][wl] : 0u;
+        need[k] = (uint32_t)__builtin_amdgcn_readlane((int)wave_scan_u32(x), 63);
+    }
+    am = wave_max_u32(s_need[NC + 1][wl]);             // in lane 63
+    int k = 0;
+    while (k < NC - 1 && (need[k] > d.max_slots || need[NC] / acc_events(k) > (uint32_t)ACC_GRID)) ++k;
+    const uint32_t ev = acc_events(k);
+    uint32_t sum[3] = {}, ex[3], tot[3], nch[RUN];     // events, blocks, partial-sum slots
+#pragma unroll
+    for (int r = 0; r < RUN; ++r) {
+        nch[r] = b0 + r < g.nt ? 1u : 0u;
+        if (cnt[r] > ev) nch[r] = (cnt[r] + ev - 1) / ev;
+        sum[0] += cnt[r];
+        sum[1] += nch[r];
+        sum[2] += nch[r] > 1 ? nch[r] : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) ex[q] = block_excl_scan<uint32_t, PLAN_T>(sum[q], sh, &tot[q]);
+#pragma unroll
+    for (int r = 0; r < RUN; ++r) {
+        const int b = b0 + r;
+        if (b >= g.nt) continue;
+        d.bbase[b] = ex[0];
+        d.nch[b] = nch[r];
+        d.chunk_base[b] = ex[1];
+        d.slot_base[b] = ex[2];
+        d.Dtile[b].lo = 0;
+        d.Dtile[b].hi = 0;
+        if (g.prec == PREC_COMP) d.Dtc[b] = ff_of(0.0f);
+        ex[0] += cnt[r];
+        ex[1] += nch[r];
+        ex[2] += nch[r] > 1 ? nch[r] : 0u;
+    }
+    if (threadIdx.x == 63) d.ctl->amax_bits = am;
     if (threadIdx.x == 0) {
-        d.bbase[g.nt] = carry_e;
-        d.chunk_base[g.nt] = carry_c;
+        d.ctl->n_cand = d.blk_cand[nb];
+        d.bbase[g.nt] = tot[0];
+        d.chunk_base[g.nt] = tot[1];
         d.Dtile[g.nt].lo = 0;
         d.Dtile[g.nt].hi = 0;
-        d.ctl->n_events = carry_e;
-        d.ctl->n_chunks = carry_c;
-        if (carry_s > d.max_slots || carry_c > d.max_chunks) d.ctl->bad |= 2u;   // cannot happen: sized for the worst case
+        d.ctl->n_events = tot[0];
+        d.ctl->n_chunks = tot[1];
+        d.ctl->acc_ev = ev;
+        if (tot[2] > d.max_slots || tot[1] > d.max_chunks) d.ctl->bad |= 2u;   // cannot happen: sized for the worst case
     }
 }
 
@@ -976,8 +1027,9 @@ __global__ __launch_bounds__(ACC_T) void k_accum(const Slot *S)
     }
     const int b = lo;
     const uint32_t ci = c - d.chunk_base[b];
-    const uint32_t e0 = d.bbase[b] + ci * ACC_EV;
-    const uint32_t e1 = min(e0 + (uint32_t)ACC_EV, d.bbase[b + 1]);
+    const uint32_t ev = d.ctl->acc_ev;
+    const uint32_t e0 = d.bbase[b] + ci * ev;
+    const uint32_t e1 = min(e0 + ev, d.bbase[b + 1]);
     const int k0 = b * g.tile;
     if (g.prec == PREC_COMP) {
         accum_comp(g, d, b, ci, e0, e1, reinterpret_cast<FF *>(xn.h), reinterpret_cast<FF *>(dd.h));
@@ -1076,9 +1128,21 @@ __global__ __launch_bounds__(RED_BINS) void k_accum_reduce(const Slot *S)
     }
     I128 x = zero_t<I128>(), y = zero_t<I128>();
     const I128 *slot = d.partial + (size_t)d.slot_base[b] * 2 * g.tile;
-    for (uint32_t s = 0; s < nc; ++s) {
-        x = i128_add(x, slot[(size_t)s * 2 * g.tile + k]);
-        y = i128_add(y, slot[(size_t)s * 2 * g.tile + g.tile + k]);
+    constexpr uint32_t U = 8;              // partial sums in flight
+    for (uint32_t s = 0; s < nc; s += U) {
+        I128 p[U], q[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const I128 *o = slot + (size_t)min(s + u, nc - 1) * 2 * g.tile + k;
+            p[u] = o[0];
+            q[u] = o[g.tile];
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            if (s + u >= nc) continue;
+            x = i128_add(x, p[u]);
+            y = i128_add(y, q[u]);
+        }
     }
     I128 dsum = zero_t<I128>();
     if (k < nbin) {
@@ -1328,20 +1392,6 @@ struct MedianSmem {
     double dsh[MWG / 64];
     int flag;
 };
-
-// Smallest (largest) word of the wave, in lane 63.
-DEVI uint32_t wave_min_u32(uint32_t v)
-{
-    auto low = [&](int x) { v = min(v, (uint32_t)x); };
-    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x111, 0xF, 0xF, false));
-    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x112, 0xF, 0xF, false));
-    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x114, 0xF, 0xF, false));
-    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x118, 0xF, 0xF, false));
-    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xA, 0xF, false));
-    low(__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xC, 0xF, false));
-    return v;
-}
-DEVI uint32_t wave_max_u32(uint32_t v) { return ~wave_min_u32(~v); }
 
 // Stable LSD radix sort of the M words in sm.kp[0] by bits [POSBITS, POSBITS +
 // DGB*passes), DGB bits per pass; returns the buffer holding the result.  A
@@ -2977,8 +3027,8 @@ hipError_t launch_prep(const Slot *ds, const Dims &dm, hipStream_t st)
     k_prep_plan<<<dim3(1, dm.ns), PLAN_T, 0, st>>>(ds);
     if (dm.prep_blocks > 0) k_prep_scatter<<<dim3(dm.prep_blocks, dm.ns), WG, 0, st>>>(ds);
     k_accum<<<dim3(dm.accum_blocks, dm.ns), ACC_T, 0, st>>>(ds);
-    // a tile is hot from more than ACC_EV events on; a source has two at most
-    if (2 * dm.max_n > (uint64_t)ACC_EV)
+    // a tile is hot from more than ACC_EV_MIN events on; a source has two at most
+    if (2 * dm.max_n > (uint64_t)ACC_EV_MIN)
         k_accum_reduce<<<dim3(dm.maxnt * (dm.maxtile / RED_BINS), dm.ns), RED_BINS, 0, st>>>(ds);
     if (dm.naive) k_accum_f32<<<dim3(2048, dm.ns), WG, 0, st>>>(ds);
     k_dscan<<<dim3(1, dm.ns), WG, 0, st>>>(ds);
