@@ -549,10 +549,13 @@ DEVI int tile_of(int bin, int tile) { return div_p2(bin, tile); }
 // counts are 16-bit halves of LDS words (at most 2 PREP_SRC < 2^16 events
 // of a block fall in one tile), which keeps the block's LDS at 16 KB; the
 // packed words are the block's row of bhist.
-template <int CB>                            // sources per thread in flight
 DEVI void k_prep_count_body(const Grid &g, const Dev &d, const float *A, const float *F, const float *FD, uint64_t n,
                             uint32_t *hist)
 {
+    // sources per thread in flight: four, with six waves per SIMD (eight, with
+    // three, took 93 us for 1e7 sources instead of 65)
+    constexpr int CB = 4;
+    static_assert(PREP_SRC % (CB * WG) == 0 && PREP_SRC_MIN % (CB * WG) == 0, "whole batches");
     __shared__ uint32_t scand, samax;
     auto hadd = [&](int b) { atomicAdd(&hist[b >> 1], 1u << (16 * (b & 1))); };
     for (int b = threadIdx.x; b < (g.nt + 1) / 2; b += WG) hist[b] = 0;
@@ -665,12 +668,8 @@ __global__ __launch_bounds__(WG) void k_prep_count(const Slot *S)
     if (!sl.active || (uint64_t)blockIdx.x * sl.d.prep_src >= sl.n) return;
     const Grid g = sl.g;
     const Dev d = sl.d;
-    static_assert(PREP_SRC % (8 * WG) == 0 && PREP_SRC_MIN % (4 * WG) == 0, "whole batches");
     __shared__ uint32_t hist[NBK_MAX / 2];
-    if (d.prep_src == PREP_SRC)
-        k_prep_count_body<8>(g, d, sl.A, sl.F, sl.FD, sl.n, hist);
-    else
-        k_prep_count_body<4>(g, d, sl.A, sl.F, sl.FD, sl.n, hist);
+    k_prep_count_body(g, d, sl.A, sl.F, sl.FD, sl.n, hist);
 }
 
 
@@ -836,17 +835,18 @@ __global__ __launch_bounds__(PLAN_T) void k_prep_plan(const Slot *S)
 // records.
 template <int SB>                            // sources per thread in flight
 DEVI void k_prep_scatter_body(const Grid &g, const Dev &d, const float *A, const float *F, const float *FD, uint64_t n,
-                              uint32_t *cur)
+                              uint32_t *cur, uint32_t row)
 {
+    static_assert(PREP_SRC % (SB * WG) == 0, "whole batches");
     __shared__ uint32_t scand, cbase;
-    for (int b = threadIdx.x; b < g.nt; b += WG) cur[b] = d.bbase[b] + d.boff[(size_t)blockIdx.x * g.nt + b];
+    for (int b = threadIdx.x; b < g.nt; b += WG) cur[b] = d.bbase[b] + d.boff[(size_t)row * g.nt + b];
     if (threadIdx.x == 0) {
-        cbase = d.blk_cand[blockIdx.x];
+        cbase = d.blk_cand[row];
         scand = 0;
     }
     __syncthreads();
     const int L = fx_exp(d.ctl->amax_bits, g.T);
-    const uint64_t base = (uint64_t)blockIdx.x * d.prep_src;
+    const uint64_t base = (uint64_t)row * d.prep_src;
     for (int r0 = 0; r0 < (int)d.prep_src / WG; r0 += SB) {
         float a[SB], f[SB], fd[SB];
         uint64_t cw[SB];                         // candidate-flag words of the sources
@@ -904,17 +904,25 @@ DEVI void k_prep_scatter_body(const Grid &g, const Dev &d, const float *A, const
     }
 }
 
+// Blocks go round-robin over the 8 XCDs, so XCD x takes the rows [x per,
+// (x + 1) per): the slots of neighbouring rows in a tile's segment are
+// neighbours, and a 128-byte line is then written by one XCD's L2, not in parts
+// by several (3e7 sources: 292 us, 307 with the rows dealt round-robin; more
+// waves, with LDS for the grid's own tiles only, 314).
 __global__ __launch_bounds__(WG) void k_prep_scatter(const Slot *S)
 {
     const Slot &sl = S[blockIdx.y];
-    if (!sl.active || (uint64_t)blockIdx.x * sl.d.prep_src >= sl.n) return;
+    if (!sl.active) return;
+    const uint32_t rows = (uint32_t)((sl.n + sl.d.prep_src - 1) / sl.d.prep_src), per = (rows + 7u) / 8u;
+    const uint32_t row = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+    if ((blockIdx.x >> 3) >= per || row >= rows) return;
     const Grid g = sl.g;
     const Dev d = sl.d;
     __shared__ uint32_t cur[NBK_MAX];
     if (d.prep_src == PREP_SRC)
-        k_prep_scatter_body<8>(g, d, sl.A, sl.F, sl.FD, sl.n, cur);
+        k_prep_scatter_body<8>(g, d, sl.A, sl.F, sl.FD, sl.n, cur, row);
     else
-        k_prep_scatter_body<4>(g, d, sl.A, sl.F, sl.FD, sl.n, cur);
+        k_prep_scatter_body<4>(g, d, sl.A, sl.F, sl.FD, sl.n, cur, row);
 }
 
 
@@ -3025,7 +3033,7 @@ hipError_t launch_prep(const Slot *ds, const Dims &dm, hipStream_t st)
     if (dm.prep_blocks > 0) k_prep_count<<<dim3(dm.prep_blocks, dm.ns), WG, 0, st>>>(ds);
     k_prep_colscan<<<dim3((dm.maxnt + CS_COL - 1) / CS_COL, dm.ns), CS_WG, 0, st>>>(ds);
     k_prep_plan<<<dim3(1, dm.ns), PLAN_T, 0, st>>>(ds);
-    if (dm.prep_blocks > 0) k_prep_scatter<<<dim3(dm.prep_blocks, dm.ns), WG, 0, st>>>(ds);
+    if (dm.prep_blocks > 0) k_prep_scatter<<<dim3((dm.prep_blocks + 7) / 8 * 8, dm.ns), WG, 0, st>>>(ds);
     k_accum<<<dim3(dm.accum_blocks, dm.ns), ACC_T, 0, st>>>(ds);
     // a tile is hot from more than ACC_EV_MIN events on; a source has two at most
     if (2 * dm.max_n > (uint64_t)ACC_EV_MIN)
