@@ -83,6 +83,7 @@ constexpr int MOM_MIN = 12;                   // fewer faint sources of a centre
 constexpr int MOM_COOP = 2048;                // more: all waves of the block share the centre
 constexpr int SNR_GRID = 2048;                // blocks of the SNR launch
 constexpr int GRP = 4;                        // consecutive candidates of a wave in it
+constexpr uint32_t BOUND_MIN_N = 1u << 14;    // smallest catalog whose candidates are tested by a bound first
 
 struct KArgs {
     Grid g;
@@ -465,6 +466,7 @@ __global__ __launch_bounds__(WG) void k_cx_reset(KArgs a)
         sl.d.S = d.S + i0 * (size_t)g.B;
         sl.d.is_pre = d.is_pre + i0 * (size_t)g.B;
         sl.d.is_psum = d.is_psum + i0 * (size_t)g.nparts;
+        sl.d.is_max = d.is_max + i0 * (size_t)((g.B + 63) / 64);
         sl.d.xstamp = d.xstamp;
         sl.d.sstamp = d.sstamp;
         sl.d.sdl = d.sdl;
@@ -1373,6 +1375,7 @@ __global__ __launch_bounds__(WG) void k_cx_inject(KArgs a)
                 d.c_iter[slot] = -1;
                 d.c_rho2[slot] = myr0;
                 d.c_qb[slot] = mine.qb;
+                d.c_amp[slot] = in.A[mine.i];
             }
         }
     }
@@ -1423,7 +1426,21 @@ __global__ __launch_bounds__(WG) void k_cx_power(KArgs a)
 // consecutive ones, a late body's few dirty tiles kept a few waves busy for
 // 64 evaluations in a row while the others had none (SNR of the 1e4 catalog
 // 30 us a run instead of 169, of the 1e7 catalog 1.68 ms instead of 2.13).
-__global__ __launch_bounds__(WG) void k_cx_snr(KArgs a)
+//
+// Most candidates cannot reach the threshold: by Parseval (sum_j |U_j|^2 = T^2
+// A^2 / 4) rho^2 <= T A^2 (max 1/S_A + max 1/S_E) over the template's bins, and
+// the PSD launches leave the maxima of every 64-bin segment.  From the second
+// body on, a candidate whose bound stays below the threshold by more than
+// the run's smallest margin so far (and the 1e-6 that counts as near) is not
+// evaluated: it is not resolved, and neither the margin nor the near count
+// would change.  Its rho^2 is marked stale (-1) and computed after the loop
+// (FINAL: S on its bins is still that of its last body).  SNR of the 1e7
+// catalog 1.01 ms a run, the last pass's 0.08 included, 1.66 with every candidate
+// evaluated; 4.1e5 sources (2 yr, mean) 102 and 123 us; at 1e4 sources the
+// evaluations fit one round of waves and the last pass would cost 9 us of 30
+// (BOUND_MIN_N).
+template <bool FINAL>
+__global__ __launch_bounds__(WG, 4) void k_cx_snr(KArgs a)
 {
     __shared__ double2 ex[NEX];
     const Grid &g = a.g;
@@ -1432,9 +1449,11 @@ __global__ __launch_bounds__(WG) void k_cx_snr(KArgs a)
     Ctl *c = d.ctl;
     set_cis_table(ex);
     __syncthreads();
-    if (c->done || c->bad) return;
+    if (c->bad || (!FINAL && c->done)) return;
     const uint32_t t = c->iter, nxt = t + 1;
     const uint32_t nc = c->cand_cursor;
+    const double margin = fmax(__longlong_as_double((long long)c->min_margin), 2e-6);
+    const double skip2 = margin < 1.0 ? g.rth2 * (1.0 - margin) * (1.0 - margin) * (1.0 - 1e-9) : 0.0;
     const int E = cx_exp(c->amax_bits, in.n, g.T);
     const double T = g.T;
     // rho^2 of the 2^E-scaled values: (4/T) 2^-2E sum
@@ -1450,12 +1469,28 @@ __global__ __launch_bounds__(WG) void k_cx_snr(KArgs a)
     for (uint32_t base = wave * GRP; base < nc; base += per) {
         const uint32_t j = base + (uint32_t)(lane() / GRP) * waves * GRP + (uint32_t)(lane() % GRP);
         bool need = j < nc && d.c_iter[j] < 0;
-        if (need && t > 0) {
+        if (FINAL) {
+            need = need && d.c_rho2[j] < 0.0;
+        } else if (need && t > 0) {
             const int qb = d.c_qb[j];
             const int lo = max(qb - HALO, 0), hi = min(qb + HALO - 1, g.B - 1);
             bool changed = false;
             for (int tl = div_p2(lo, g.tile); tl <= div_p2(hi, g.tile); ++tl) changed |= d.sstamp[tl] >= t;
             need = changed;
+            if (need && in.n >= BOUND_MIN_N) {
+                const uint32_t *ma = d.is_max, *me = d.is_max + (g.B + 63) / 64;
+                uint32_t xa = 0, xe = 0;
+                for (int sg = lo >> 6; sg <= hi >> 6; ++sg) {
+                    xa = max(xa, ma[sg]);
+                    xe = max(xe, me[sg]);
+                }
+                auto above = [](uint32_t x) { return __longlong_as_double((long long)(((uint64_t)x + 1) << 32)); };
+                const double A = (double)d.c_amp[j];
+                if (T * (A * A) * (above(xa) + above(xe)) < skip2) {
+                    need = false;
+                    d.c_rho2[j] = -1.0;
+                }
+            }
         }
         // the constants only of the candidates evaluated
         SrcConsts mine{};
@@ -1484,10 +1519,11 @@ __global__ __launch_bounds__(WG) void k_cx_snr(KArgs a)
             if (ine) r += pe * ((sAe + sEe) / (sAe * sEe));
             if (ino) r += po * ((sAo + sEo) / (sAo * sEo));
             const double r2 = rs * wave_sum(r);
+            if (lane() == 0) d.c_rho2[jk] = r2;
+            if (FINAL) continue;
             const double rel = fabs(sqrt(r2) / g.rth - 1.0);
             minm = fmin(minm, rel);
             my_near += rel <= 1e-6;
-            if (lane() == 0) d.c_rho2[jk] = r2;
             if (!(r2 > g.rth2)) continue;
             ++my_new;
             if (lane() == 0) d.c_iter[jk] = (int32_t)t;
@@ -1518,6 +1554,7 @@ __global__ __launch_bounds__(WG) void k_cx_snr(KArgs a)
             }
         }
     }
+    if (FINAL) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         c->xupd = nxt;
         c->tail_due = 1;
@@ -1621,6 +1658,8 @@ uint64_t cx_carve(const Grid &g, uint64_t n, char *base, CxDev *out)
     d.c_id = (uint32_t *)take(nn * 4);
     d.c_rho2 = (double *)take(nn * 8);
     d.c_qb = (int32_t *)take(nn * 4);
+    d.c_amp = (float *)take(nn * 4);
+    d.is_max = (uint32_t *)take(2 * ((B + 63) / 64) * 4);
     d.rs_hist = (uint32_t *)take(resolved_scratch_words(nn) * 4);
     d.rlist = (uint64_t *)take(nn * 16);
     const bool faint = n >= FAINT_MIN_N;
@@ -1696,12 +1735,13 @@ hipError_t cx_launch_next(const Grid &g, const CxDev &d, hipStream_t st, hipEven
 
 hipError_t cx_launch_snr(const Grid &g, const CxDev &d, const CxIn &in, hipStream_t st)
 {
-    k_cx_snr<<<SNR_GRID, WG, 0, st>>>(args_of(g, d, in));
+    k_cx_snr<false><<<SNR_GRID, WG, 0, st>>>(args_of(g, d, in));
     return hipGetLastError();
 }
 
 hipError_t cx_launch_outputs(const Grid &g, const CxDev &d, const CxIn &in, hipStream_t st)
 {
+    if (in.n >= BOUND_MIN_N) k_cx_snr<true><<<SNR_GRID, WG, 0, st>>>(args_of(g, d, in));
     k_cx_ids<<<256, WG, 0, st>>>(args_of(g, d, in));
     return hipGetLastError();
 }

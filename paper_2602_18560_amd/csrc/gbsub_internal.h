@@ -155,6 +155,7 @@ struct Dev {
     double *is_pre;          // [B]    inclusive prefix of 1/S^t inside each part (an FF in the
                              //        compensated FP32 mode, a float in the naive one)
     double *is_psum;         // [nparts] part sums of 1/S^t
+    uint32_t *is_max;        // template model: high word of the largest 1/S of each 64-bin segment (or null)
     // dirty tiles: a tile is converted (X) / filtered (S) in body t iff its
     // stamp equals t; k_snr stamps t + 1 where a subtraction changes them
     uint32_t *xstamp;        // [nt]
@@ -291,6 +292,8 @@ struct CxDev {
     uint32_t *c_id;          // [n] its id (written at the end of a run)
     double *c_rho2;          // [n] rho^2 at the last evaluation
     int32_t *c_qb;           // [n] its template's centre bin (the SNR pass's dirty-tile test)
+    float *c_amp;            // [n] its amplitude (the SNR pass's bound)
+    uint32_t *is_max;        // [2][ceil(B/64)] high word of the largest 1/S of each 64-bin segment
     uint32_t *rs_hist;       // resolved-list scratch
     uint64_t *rlist;         // [2n] the resolved list (list_resolved), then its sort's scratch
     // binning of the injection (catalogs of 2^16 sources or more: the faint

@@ -1691,6 +1691,15 @@ DEVI void fresh_union_cx(const Slot &sl, int u0, int u1, double (&xr)[MCH])
     }
 }
 
+// The largest 1/S of the wave's 64-bin segment, which starts at bin k0 < t1 (lanes
+// past the outputs bring 0): the bound that the template model's SNR pass uses.
+DEVI void segment_max(const Dev &d, double inv, int k0, int t1)
+{
+    if (!d.is_max || k0 >= t1) return;                 // wave-uniform
+    const uint32_t m = wave_max_u32((uint32_t)((uint64_t)__double_as_longlong(inv) >> 32));
+    if (lane_id() == 63) d.is_max[k0 >> 6] = m;
+}
+
 // Where a PSD launch takes X from: the array (converted by an earlier launch),
 // the accumulators, or the template model's data.
 enum XSource { X_ARRAY, X_ACCUM, X_CX };
@@ -2076,6 +2085,7 @@ DEVI void median_work(MedianSmem &sm, const Slot *slp, int blk, int span)
         const bool on = kb < ke;
         const double Sk = g.C * med[0] + sxr[0], inv = on ? 1.0 / Sk : 0.0;
         if (on) d.S[kb] = Sk;
+        segment_max(d, inv, t0 + wave * 64, t1);
         const double inc = wave_incl_scan(inv);
         double exw = __shfl_up(inc, 1, 64);
         if (lane == 0) exw = 0.0;
@@ -2104,18 +2114,21 @@ DEVI void median_work(MedianSmem &sm, const Slot *slp, int blk, int span)
 #pragma unroll
     for (int r = 0; r < RMAX; ++r) {
         const int i = tid + r * MWG;
-        if (i >= n) continue;
-        double Sk, inv;
-        if (g.prec == PREC_FP64) {
-            Sk = g.C * st[i] + sxr[r];
-            inv = 1.0 / Sk;
-        } else {                           // S and 1/S in fp32, scaled by 2^sc
-            const float sf = (float)g.C * (float)ldexp(st[i], sc) + (float)ldexp(sxr[r], sc);
-            Sk = ldexp((double)sf, -sc);
-            inv = (double)(1.0f / sf);
+        double inv = 0.0;
+        if (i < n) {
+            double Sk;
+            if (g.prec == PREC_FP64) {
+                Sk = g.C * st[i] + sxr[r];
+                inv = 1.0 / Sk;
+            } else {                       // S and 1/S in fp32, scaled by 2^sc
+                const float sf = (float)g.C * (float)ldexp(st[i], sc) + (float)ldexp(sxr[r], sc);
+                Sk = ldexp((double)sf, -sc);
+                inv = (double)(1.0f / sf);
+            }
+            d.S[t0 + i] = Sk;
+            st[i] = inv;
         }
-        d.S[t0 + i] = Sk;
-        st[i] = inv;
+        segment_max(d, inv, t0 + (i & ~63), t1);
     }
     __syncthreads();
     // prefix of 1/S restarted at every part: fp64 sums, double-fp32 sums in
@@ -2352,20 +2365,25 @@ DEVI void mean_work(MeanSmem &sm, const Slot *slp, int blk, int span, I128 *st =
         if (i < ch && pb + i < M) sm.v[pb + i] = ex + loc[i];
     __syncthreads();
     const int n = t1 - t0;
-    for (int i = tid; i < n; i += MWG) {
+    for (int i = tid; i - lane_id() < n; i += MWG) {   // whole waves
         const int k = t0 + i;
-        double sum, len;
-        if (whole) {
-            sum = sm.v[M - 1];
-            len = (double)B;
-        } else {
-            const int a = win_start(k, B, W, h) - u0;
-            sum = sm.v[a + W - 1] - (a > 0 ? sm.v[a - 1] : 0.0);
-            len = (double)W;
+        double inv = 0.0;
+        if (i < n) {
+            double sum, len;
+            if (whole) {
+                sum = sm.v[M - 1];
+                len = (double)B;
+            } else {
+                const int a = win_start(k, B, W, h) - u0;
+                sum = sm.v[a + W - 1] - (a > 0 ? sm.v[a - 1] : 0.0);
+                len = (double)W;
+            }
+            const double Sk = sum / len;
+            d.S[k] = Sk;
+            inv = 1.0 / Sk;
+            sm.stage[i] = inv;
         }
-        const double Sk = sum / len;
-        d.S[k] = Sk;
-        sm.stage[i] = 1.0 / Sk;
+        segment_max(d, inv, t0 + (i & ~63), t1);
     }
     __syncthreads();
     const int R = (span + MWG - 1) / MWG;
