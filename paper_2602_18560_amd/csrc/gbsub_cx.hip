@@ -1016,24 +1016,28 @@ __device__ __forceinline__ double2 phase_factor(float phi, const double2 *ex)
     return make_double2(cp, sp);
 }
 
-// Integer sums of the coefficients of channel ch over the sources order[o],
-// o = o0 + lane, o0 + lane + step, ... < o1: lane 2k gets Re G_k, lane 2k + 1
-// Im G_k (wrapping 64-bit sums; lanes past 2 NMOM get 0).  A value is rounded
-// to its unit by adding 1.5 2^52 and its bits are added as they are; the
-// constant part of the bits leaves at the end.
-__device__ __forceinline__ uint64_t moment_sums(const KArgs &a, uint32_t o0, uint32_t o1, uint32_t step, int ch,
-                                                int E7, const double2 *ex)
+// Integer sums of the coefficients over the sources order[o], o = o0 + l,
+// o0 + l + step, ... < o1, l = lane mod 32: each half of the wave sums one
+// channel, lane k of half ch gets Re G_k and Im G_k of channel ch (wrapping
+// 64-bit sums; lanes k >= NMOM get 0).  A value is rounded to its unit by
+// adding 1.5 2^52 and its bits are added as they are; the constant part of the
+// bits leaves at the end.
+// Channels by halves: one fold of 56 sums for both channels where a wave per
+// channel folded twice, and most centres have fewer than 32 sources, which
+// left half of such a wave idle.
+__device__ __forceinline__ void moment_sums(const KArgs &a, uint32_t o0, uint32_t o1, uint32_t step, int E7,
+                                            const double2 *ex, uint64_t *re, uint64_t *im)
 {
     const CxDev &d = a.d;
     const double T = a.g.T, scale = ldexp(T / NF * 0.5, E7);
-    const float *PH = reinterpret_cast<const float *>(d.fph) + ch;
+    const float *PH = reinterpret_cast<const float *>(d.fph) + (lane() >> 5);
     uint64_t sr[NMOM], si[NMOM];
 #pragma unroll
     for (int k = 0; k < NMOM; ++k) sr[k] = si[k] = 0;
     uint32_t turns = 0;
     // the next turn's record is loaded while this one's coefficients are
     // summed, and its place in the order one turn before that
-    const uint32_t last = o1 - 1u, l = (uint32_t)lane();
+    const uint32_t last = o1 - 1u, l = (uint32_t)lane() & 31u;
     uint32_t p = 0, pn = 0;
     float4 rec = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     float ph = 0.0f;
@@ -1074,25 +1078,26 @@ __device__ __forceinline__ uint64_t moment_sums(const KArgs &a, uint32_t o0, uin
             }
         }
     }
-    // lane l ends with the sum of value l: halves of the values change
-    // places with halves of the wave, then of the rows, and so on
+    // lane l of a half ends with the sums of values 2l and 2l + 1: halves of
+    // the values change places between the half's rows, then within the rows
     static_assert(NMOM == 28, "56 values: the folds below");
     uint64_t v[32];
 #pragma unroll
     for (int j = 0; j < 32; ++j) {
         const int m = j + 32;                                             // values 56 .. 63 are zero
-        v[j] = swap_add<32>(j & 1 ? si[j / 2] : sr[j / 2], m < 2 * NMOM ? (j & 1 ? si[m / 2] : sr[m / 2]) : 0ull);
+        v[j] = swap_add<16>(j & 1 ? si[j / 2] : sr[j / 2], m < 2 * NMOM ? (j & 1 ? si[m / 2] : sr[m / 2]) : 0ull);
     }
 #pragma unroll
-    for (int j = 0; j < 16; ++j) v[j] = swap_add<16>(v[j], v[j + 16]);
+    for (int j = 0; j < 16; ++j) v[j] = fold_add<8>(v[j], v[j + 16], lane() & 8);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = fold_add<8>(v[j], v[j + 8], l & 8);
+    for (int j = 0; j < 8; ++j) v[j] = fold_add<7>(v[j], v[j + 8], lane() & 4);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = fold_add<7>(v[j], v[j + 4], l & 4);
+    for (int j = 0; j < 4; ++j) v[j] = fold_add<2>(v[j], v[j + 4], lane() & 2);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) v[j] = fold_add<2>(v[j], v[j + 2], l & 2);
-    const uint64_t s = fold_add<1>(v[0], v[1], l & 1);
-    return l < 2u * NMOM ? s - (uint64_t)turns * 64ull * 0x4338000000000000ull : 0ull;
+    for (int j = 0; j < 2; ++j) v[j] = fold_add<1>(v[j], v[j + 2], lane() & 1);
+    const uint64_t base = (uint64_t)turns * 32ull * 0x4338000000000000ull;
+    *re = l < (uint32_t)NMOM ? v[0] - base : 0ull;
+    *im = l < (uint32_t)NMOM ? v[1] - base : 0ull;
 }
 
 // One block per bucket: the bucket's sources are ordered by centre (LDS
@@ -1103,11 +1108,13 @@ __device__ __forceinline__ uint64_t moment_sums(const KArgs &a, uint32_t o0, uin
 // window.  A centre of more than MOM_COOP sources is shared by the block's
 // waves.
 // Bound by VALU issue and the dependent steps of a task (two waves per SIMD:
-// 56 sums of 64 bits per lane).  1e7 sources on the 4-yr grid: 680 us for the
-// 9.4e6 faint ones, plus 380 us of grouping and 300 us for the others'
-// templates, against 6500 us (and 110 us of grouping) with one template per
-// source.  MOM_MIN: a centre's sums cost about 2600 wave instructions for both
-// channels (folds, Horner, FFT, rounding), a template 240.
+// 56 sums of 64 bits per lane).  1e7 sources on the 4-yr grid: 590 us for the
+// 9.4e6 faint ones (690 us with a wave per channel of a centre), plus 380 us of
+// grouping and 300 us for the others' templates, against 6500 us (and 110 us
+// of grouping) with one template per source.  MOM_MIN: a centre's sums cost
+// about 1800 wave instructions for both channels and up to 32 sources (turn
+// 450, folds 330, two times Horner, FFT and rounding 500), 2600 with a wave per
+// channel, a template 240.
 __global__ __launch_bounds__(WG, 2) void k_cx_faint(KArgs a)
 {
     constexpr int NW = WG / 64;
@@ -1186,15 +1193,15 @@ __global__ __launch_bounds__(WG, 2) void k_cx_faint(KArgs a)
     auto put = [&](int bin, int word, long long v) {
         atomicAdd((unsigned long long *)&acc[word][(bin - w0) & 1][(bin - w0) >> 1], (unsigned long long)v);
     };
-    // the transform of a centre's sums of channel ch (lane 2k: Re G_k, 2k + 1: Im G_k)
-    auto transform = [&](uint64_t sum, int c, int ch, int E7) {
-        const double v = ldexp((double)(long long)sum, E - E7);
+    auto unit = [&](uint64_t sum, int E7) { return ldexp((double)(long long)sum, E - E7); };
+    // the transform of a centre's sums of channel ch (lane k: Re G_k, Im G_k)
+    auto transform = [&](double vr, double vi, int c, int ch) {
         const LaneFft L = kept_fft(lf);
         const double z0 = 2.0 * L.x0 - 1.0, z1 = 2.0 * L.x1 - 1.0;
         double2 p0 = make_double2(0.0, 0.0), p1 = p0;
 #pragma unroll
         for (int k = NMOM - 1; k >= 0; --k) {
-            const double mr = rl(v, 2 * k), mi = rl(v, 2 * k + 1);
+            const double mr = rl(vr, k), mi = rl(vi, k);
             const double cx = k % 4 == 0 ? mr : k % 4 == 1 ? -mi : k % 4 == 2 ? -mr : mi;     // i^k G_k
             const double cy = k % 4 == 0 ? mi : k % 4 == 1 ? mr : k % 4 == 2 ? -mi : -mr;
             p0 = make_double2(fma(p0.x, z0, cx), fma(p0.y, z0, cy));
@@ -1207,26 +1214,38 @@ __global__ __launch_bounds__(WG, 2) void k_cx_faint(KArgs a)
         put(c0 + c + jo, 2 * ch, __double2ll_rn(uo.x));
         put(c0 + c + jo, 2 * ch + 1, __double2ll_rn(uo.y));
     };
-    for (int t = wave; t < 2 * width; t += NW) {
-        const int c = t >> 1, ch = t & 1;
+    for (int c = wave; c < width; c += NW) {
         const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)cnt[c]);
         if (n < (uint32_t)MOM_MIN || n > (uint32_t)MOM_COOP) continue;
         const uint32_t e = m0 + (uint32_t)__builtin_amdgcn_readfirstlane((int)beg[c]);
         const int E7 = moment_exp(amax, n, g.T);
-        transform(moment_sums(a, e - n, e, 64u, ch, E7, ex), c, ch, E7);
+        uint64_t re, im;
+        moment_sums(a, e - n, e, 32u, E7, ex, &re, &im);
+        double vr = unit(re, E7), vi = unit(im, E7);
+#pragma unroll 1
+        for (int ch = 0;; ++ch) {
+            transform(vr, vi, c, ch);
+            if (ch == 1) break;
+            double t = vr, u = vi;
+            row_swap<32>(&t, &vr);                    // both halves: the second channel
+            row_swap<32>(&u, &vi);
+        }
     }
     if (m1 - m0 > (uint32_t)MOM_COOP) {               // block-uniform
         for (int c = 0; c < width; ++c) {
             const uint32_t n = cnt[c];
             if (n <= (uint32_t)MOM_COOP) continue;
             const uint32_t e = m0 + beg[c];
-            const int ch = wave & 1, E7 = moment_exp(amax, n, g.T);
-            const uint64_t s = moment_sums(a, e - n + 64u * (uint32_t)(wave >> 1), e, 64u * (NW / 2), ch, E7, ex);
-            atomicAdd(&msum[ch][lane()], (unsigned long long)s);
+            const int E7 = moment_exp(amax, n, g.T);
+            uint64_t re, im;
+            moment_sums(a, e - n + 32u * (uint32_t)wave, e, 32u * NW, E7, ex, &re, &im);
+            atomicAdd(&msum[0][lane()], (unsigned long long)re);
+            atomicAdd(&msum[1][lane()], (unsigned long long)im);
             __syncthreads();
             if (wave < 2) {
-                transform(msum[wave][lane()], c, wave, E7);
-                msum[wave][lane()] = 0;
+                const int k = 32 * wave + (lane() & 31);
+                transform(unit(msum[0][k], E7), unit(msum[1][k], E7), c, wave);
+                msum[lane() >> 5][k] = 0;
             }
             __syncthreads();
         }
