@@ -268,6 +268,13 @@ constexpr int CX_NF = 128;          // samples per template
 constexpr int CX_TILE = 1024;       // bins per binning tile of the injection
 constexpr int CX_NTC_MAX = 8192;    // binning tiles at most (B <= CX_NTC_MAX * CX_TILE)
 
+// A faint source of the template model, by bucket.
+struct FaintRec {
+    float A, f, fd;
+    uint32_t centre;         // inside its tile
+    float ph[2];             // the channels' phases
+};
+
 // Pointers into the workspace of a complex-template run.
 struct CxDev {
     Slot *slots;             // [2] median descriptors of the A and E channels
@@ -303,8 +310,7 @@ struct CxDev {
     uint32_t *fbb;           // [ntc+1] first faint bucket of each tile
     uint32_t *ftot;          // [buckets+1] faint sources per bucket, then their exclusive prefix
     uint32_t *fmat;          // [blocks][buckets] faint sources per (block, bucket), then the blocks before
-    float4 *frec;            // [n] the faint sources' records by bucket: A, f, fdot, centre inside the tile
-    float2 *fph;             // [n] their phases
+    FaintRec *frec;          // [n] the faint sources' records by bucket
     uint32_t *forder;        // [n] their records by centre inside each bucket
     int32_t ntc;             // binning tiles
     int32_t pad;
