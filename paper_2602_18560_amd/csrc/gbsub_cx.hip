@@ -78,6 +78,8 @@ constexpr double FAINT_MAX_D = 0.25 * 4.0 / 3.141592653589793;   // its largest 
 constexpr int NMOM = 28;                      // moments per centre
 constexpr int FB_MAX = 16384;                 // faint buckets at most
 constexpr int FB_SRC = 16384;                 // sources per block of the faint passes
+constexpr int FB_SRC_MIN = 4096;              // and in catalogs of up to FB_SMALL sources
+constexpr uint64_t FB_SMALL = 1u << 20;
 constexpr int FB_T = 1024;                    // threads of those blocks
 constexpr int MOM_MIN = 12;                   // fewer faint sources of a centre: one template each
 constexpr int MOM_COOP = 2048;                // more: all waves of the block share the centre
@@ -735,8 +737,8 @@ __global__ __launch_bounds__(FB_T) void k_cx_scatter(KArgs a)
 // totals the scatter pass copies the records (amplitude, frequency,
 // derivative, centre in the tile; phases) to their buckets, so that the
 // moment blocks read contiguous memory instead of gathering five columns of
-// a catalog in random order (64 bytes of HBM per 4-byte value).  A record is
-// one 16-byte and one 8-byte store, and the blocks of one XCD take
+// a catalog in random order (64 bytes of HBM per 4-byte value).  A record has
+// 24 bytes in one place, and the blocks of one XCD take
 // neighbouring rows, whose slots of a bucket are neighbours: with a store per
 // column and the rows dealt round-robin, a 128-byte line was written in
 // parts by several XCDs' L2s (845 us for 1e7 sources).
@@ -765,7 +767,7 @@ __device__ __forceinline__ uint32_t bucket_of(const uint32_t *map, uint32_t key)
     return (w >> 4) + ((k % CX_TILE) >> (10u - (w & 15u)));
 }
 
-__global__ __launch_bounds__(FB_T) void k_cx_fcount(KArgs a)
+template <int SRC> __global__ __launch_bounds__(FB_T) void k_cx_fcount(KArgs a)
 {
     __shared__ uint32_t map[CX_NTC_MAX];
     __shared__ uint32_t hist[FB_MAX / 2];           // 16-bit counts
@@ -775,16 +777,16 @@ __global__ __launch_bounds__(FB_T) void k_cx_fcount(KArgs a)
     load_bucket_map(d, map);
     for (uint32_t b = threadIdx.x; b < (nbk + 1) / 2; b += FB_T) hist[b] = 0;
     __syncthreads();
-    const uint32_t b0 = blockIdx.x * (uint32_t)FB_SRC;
-    uint32_t key[FB_SRC / FB_T];
+    const uint32_t b0 = blockIdx.x * (uint32_t)SRC;
+    uint32_t key[SRC / FB_T];
 #pragma unroll
-    for (int r = 0; r < FB_SRC / FB_T; ++r) {
+    for (int r = 0; r < SRC / FB_T; ++r) {
         const uint32_t i = b0 + (uint32_t)(r * FB_T) + threadIdx.x;
         key[r] = d.key[min(i, a.in.n - 1u)];
         if (i >= a.in.n) key[r] = KEY_NONE;
     }
 #pragma unroll
-    for (int r = 0; r < FB_SRC / FB_T; ++r) {
+    for (int r = 0; r < SRC / FB_T; ++r) {
         if (key[r] == KEY_NONE || !(key[r] & KEY_FAINT)) continue;
         const uint32_t b = bucket_of(map, key[r]);
         atomicAdd(&hist[b >> 1], 1u << (16 * (b & 1u)));
@@ -797,7 +799,7 @@ __global__ __launch_bounds__(FB_T) void k_cx_fcount(KArgs a)
 // Column pass, in place: the sources of the blocks before, per bucket, and
 // the bucket totals.  64 buckets per block, one per lane; the waves split
 // the rows.
-__global__ __launch_bounds__(FB_T) void k_cx_fcols(KArgs a)
+template <int SRC> __global__ __launch_bounds__(FB_T) void k_cx_fcols(KArgs a)
 {
     constexpr int NV = FB_T / 64, U = 8;
     __shared__ uint32_t part[NV][64];
@@ -808,7 +810,7 @@ __global__ __launch_bounds__(FB_T) void k_cx_fcols(KArgs a)
     const uint32_t b = blockIdx.x * 64u + (uint32_t)l;
     const bool ok = b < nbk;
     const uint32_t col = ok ? b : nbk - 1u;
-    const uint32_t rows = (a.in.n + FB_SRC - 1) / FB_SRC, per = (rows + NV - 1) / NV;
+    const uint32_t rows = (a.in.n + SRC - 1) / SRC, per = (rows + NV - 1) / NV;
     const uint32_t r0 = min(w * per, rows), r1 = min(r0 + per, rows);
     uint32_t sum = 0;
     for (uint32_t r = r0; r < r1; r += U) {
@@ -870,21 +872,21 @@ __global__ __launch_bounds__(PLAN_T) void k_cx_fscan(KArgs a)
 // bucket, so the records go to scattered lines that leave the caches partly
 // filled: one record of 24 bytes per source, not two arrays.  9.4e6 sources:
 // 267 us (two arrays 332 us).
-__global__ __launch_bounds__(FB_T) void k_cx_fscatter(KArgs a)
+template <int SRC> __global__ __launch_bounds__(FB_T) void k_cx_fscatter(KArgs a)
 {
     __shared__ uint32_t map[CX_NTC_MAX];
     __shared__ uint32_t cur[FB_MAX];
     const CxDev &d = a.d;
     const CxIn &in = a.in;
     const uint32_t nbk = d.ctl->n_events;
-    const uint32_t rows = (in.n + FB_SRC - 1) / FB_SRC, row = faint_row(rows);
+    const uint32_t rows = (in.n + SRC - 1) / SRC, row = faint_row(rows);
     if (d.ctl->bad || row >= rows) return;
     load_bucket_map(d, map);
     for (uint32_t b = threadIdx.x; b < nbk; b += FB_T) cur[b] = d.ftot[b] + d.fmat[(size_t)row * nbk + b];
     __syncthreads();
-    const uint32_t b0 = row * (uint32_t)FB_SRC;
+    const uint32_t b0 = row * (uint32_t)SRC;
     constexpr int U = 4;
-    for (int r0 = 0; r0 < FB_SRC / FB_T; r0 += U) {
+    for (int r0 = 0; r0 < SRC / FB_T; r0 += U) {
         uint32_t key[U];
         float A[U], f[U], fd[U], pa[U], pe[U];
 #pragma unroll
@@ -1647,6 +1649,16 @@ __global__ __launch_bounds__(WG) void k_cx_templates(Grid g, const float *A, con
 
 KArgs args_of(const Grid &g, const CxDev &d, const CxIn &in) { return KArgs{g, d, in}; }
 
+// The faint sources' records by bucket, SRC sources per block.
+template <int SRC> void faint_group(const KArgs &a, hipStream_t st)
+{
+    const uint32_t rows = (a.in.n + SRC - 1) / SRC;
+    k_cx_fcount<SRC><<<rows, FB_T, 0, st>>>(a);
+    k_cx_fcols<SRC><<<FB_MAX / 64, FB_T, 0, st>>>(a);
+    k_cx_fscan<<<1, PLAN_T, 0, st>>>(a);
+    k_cx_fscatter<SRC><<<(rows + 7) / 8 * 8, FB_T, 0, st>>>(a);
+}
+
 }  // namespace
 
 uint64_t cx_carve(const Grid &g, uint64_t n, char *base, CxDev *out)
@@ -1665,9 +1677,11 @@ uint64_t cx_carve(const Grid &g, uint64_t n, char *base, CxDev *out)
     d.sx = (double *)take(B * 8);
     d.isx = (double *)take(B * 8);
     d.isx_max = (double *)take(((B + CX_NF - 1) / CX_NF) * 8);
+    const uint64_t x0 = off;
     d.X = (double *)take(2 * B * 8);
     d.S = (double *)take(2 * B * 8);
     d.is_pre = (double *)take(2 * B * 8);
+    const uint64_t spectra = off - x0;
     d.is_psum = (double *)take(2 * (uint64_t)g.nparts * 8);
     d.h = (int64_t *)take(4 * B * 8);
     d.xstamp = (uint32_t *)take(nt * 4);
@@ -1699,6 +1713,16 @@ uint64_t cx_carve(const Grid &g, uint64_t n, char *base, CxDev *out)
     d.key = d.c_src;
     d.frec = (FaintRec *)d.c_rho2;
     d.forder = d.c_id;
+    // blocks of the faint passes: 16384 sources leave most of the chip idle
+    // below ~4e6 sources; smaller ones make more rows of the matrix, which then
+    // lies in the spectra (first written by the first body) if these are large
+    // enough.  4.1e5 sources, count, columns and scatter: 22 us with 4096,
+    // 45 us with 16384.
+    d.fsrc = FB_SRC;
+    if (faint && n <= FB_SMALL && (n + FB_SRC_MIN - 1) / FB_SRC_MIN * (uint64_t)FB_MAX * 4 <= spectra) {
+        d.fsrc = FB_SRC_MIN;
+        d.fmat = (uint32_t *)d.X;
+    }
     if (out) *out = d;
     return off;
 }
@@ -1710,13 +1734,12 @@ hipError_t cx_launch_prep(const Grid &g, const CxDev &d, const CxIn &in, hipStre
     const uint32_t nb = (in.n + SRC_PB - 1) / SRC_PB;
     if (nb) k_cx_count<<<nb, WG, 0, st>>>(a);
     k_cx_plan<<<1, PLAN_T, 0, st>>>(a);
-    const uint32_t fb = (in.n + FB_SRC - 1) / FB_SRC;
-    if (nb) k_cx_scatter<<<fb, FB_T, 0, st>>>(a);
+    if (nb) k_cx_scatter<<<(in.n + FB_SRC - 1) / FB_SRC, FB_T, 0, st>>>(a);
     if (in.n >= FAINT_MIN_N) {
-        k_cx_fcount<<<fb, FB_T, 0, st>>>(a);
-        k_cx_fcols<<<FB_MAX / 64, FB_T, 0, st>>>(a);
-        k_cx_fscan<<<1, PLAN_T, 0, st>>>(a);
-        k_cx_fscatter<<<(fb + 7) / 8 * 8, FB_T, 0, st>>>(a);
+        if (d.fsrc == (uint32_t)FB_SRC_MIN)
+            faint_group<FB_SRC_MIN>(a, st);
+        else
+            faint_group<FB_SRC>(a, st);
         k_cx_faint<<<FB_MAX, WG, 0, st>>>(a);
     }
     // chunks: at most one partial chunk per tile beyond the full ones (the

@@ -310,6 +310,7 @@ struct CxDev {
     uint32_t *fbb;           // [ntc+1] first faint bucket of each tile
     uint32_t *ftot;          // [buckets+1] faint sources per bucket, then their exclusive prefix
     uint32_t *fmat;          // [blocks][buckets] faint sources per (block, bucket), then the blocks before
+    uint32_t fsrc;           // sources per row of it
     FaintRec *frec;          // [n] the faint sources' records by bucket
     uint32_t *forder;        // [n] their records by centre inside each bucket
     int32_t ntc;             // binning tiles

@@ -61,3 +61,17 @@ def test_smallest_catalog_without_the_path():
     cat = cat_of(10 ** rng.uniform(-26, -23, n), (k0 + rng.uniform(0, 2999, n)) / T, np.zeros(n))
     pa, pe = template_phases(n, 42)
     assert_cx_parity(cat, pa, pe, run, "2^16 - 1 sources")
+
+
+@pytest.mark.parametrize("n_bins,n", [(24000, N_MIN), (24000, 18 * 4096 + 1), (40000, 17 * 4096 + 1)],
+                         ids=["short rows", "matrix larger than the spectra", "one source in the last row"])
+def test_grouping_rows(n_bins, n):
+    """The faint sources' grouping in rows of 4096 sources (its matrix lies in
+    the spectra) or of 16384 (it does not fit there)."""
+    run, k0 = _grid(n_bins, 101)
+    rng = np.random.default_rng(43)
+    A = 10 ** rng.uniform(-26, -24, n)
+    A[::2000] = 10 ** rng.uniform(-22.5, -21, A[::2000].size)
+    cat = cat_of(A, (k0 + rng.uniform(0, n_bins - 1, n)) / T, np.zeros(n))
+    pa, pe = template_phases(n, 43)
+    assert_cx_parity(cat, pa, pe, run, f"{n_bins} bins {n} sources")
