@@ -534,7 +534,7 @@ def bench_precision(args):
 CX_ALGO = {
     "xupdate": ("hbm", 48.0),        # per bin: read 4 int64 of h, write X_A, X_E
     "median": ("hbm", 24.0),         # per output bin and channel: read X and S_instr, write S
-    "prep": ("alu", 6144.0),         # per source: one template (injection and candidate cut)
+    "prep": ("alu", 432.0),          # per source: 27 steps of its moments, 8 flops each, in two channels
     "snr": ("alu", 6144.0),          # per candidate evaluation: one template
 }
 FP64_VECTOR_PEAK_TFLOPS = 78.6

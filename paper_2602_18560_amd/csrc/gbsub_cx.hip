@@ -1110,10 +1110,10 @@ __device__ __forceinline__ void moment_sums(const KArgs &a, uint32_t o0, uint32_
 
 // One block per bucket: the bucket's sources are ordered by centre (LDS
 // counts; centres with fewer than MOM_MIN sources last, their sources take
-// one template each), then every (centre, channel) is a wave's task: moment
-// sums, the polynomial at the wave's 128 sample times (Horner, the
-// coefficients broadcast by readlane), one FFT, and the values into the
-// window.  A centre of more than MOM_COOP sources is shared by the block's
+// one template each), then every centre is a wave's task: the moment sums of
+// both channels, and per channel the polynomial at the wave's 128 sample times
+// (Horner, the coefficients broadcast by readlane), one FFT, and the values
+// into the window.  A centre of more than MOM_COOP sources is shared by the block's
 // waves.
 // Bound by VALU issue and the dependent steps of a task (two waves per SIMD:
 // 56 sums of 64 bits per lane).  1e7 sources on the 4-yr grid: 590 us for the

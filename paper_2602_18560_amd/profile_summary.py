@@ -46,7 +46,12 @@ def kernel_source_hash() -> str:
 
 def short(name: str) -> str:
     name = name.replace("(anonymous namespace)::", "")
-    return name.split("(")[0].replace("gbs::", "")
+    return name.split("(")[0].replace("gbs::", "").removeprefix("void ").split("<")[0]
+
+
+def is_body(name: str, kernel: str) -> bool:
+    """A launch of the kernel, or of its form in bodies of two launches."""
+    return name in (kernel, kernel + "_next")
 
 
 def stats(path: str, command: str) -> str:
@@ -66,7 +71,7 @@ def trace(path: str, kernel: str, n_iter: int) -> str:
         if name == "k_prep_count":
             cur = []
             runs.append(cur)
-        elif name == kernel and cur is not None:
+        elif is_body(name, kernel) and cur is not None:
             cur.append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
     runs = [r for r in runs if len(r) >= n_iter]
     work = [d for r in runs for d in r[:n_iter]]
@@ -97,7 +102,7 @@ def _run_dispatches(path: str, kernel: str, n_iter: int):
         if name == "k_prep_count":
             cur = []
             runs.append(cur)
-        elif name == kernel and cur is not None:
+        elif is_body(name, kernel) and cur is not None:
             cur.append(float(r["Counter_Value"]))
     return [v for run in runs if len(run) >= n_iter for v in run[:n_iter]]
 
@@ -118,7 +123,8 @@ def traffic(fetch, write, cfetch, cwrite, copy_bytes, kernel, commands, n_iter=0
         fv = sum(f[k]) / len(f[k])
         wv = sum(w.get(k, [0.0])) / max(len(w.get(k, [])), 1)
         rows.append(f"| {k} | {len(f[k])} | {fv:.1f} | {wv:.1f} | {(fv * ff + wv * fw) * 1024 / 1e6:.3f} |")
-    kf, kw = f[kernel], w[kernel]
+    kf = [v for k in sorted(f) if is_body(k, kernel) for v in f[k]]
+    kw = [v for k in sorted(w) if is_body(k, kernel) for v in w[k]]
     if n_iter:
         # the working dispatches of the runs that went all the way
         work = list(zip(_run_dispatches(fetch, kernel, n_iter), _run_dispatches(write, kernel, n_iter)))
