@@ -1704,7 +1704,14 @@ uint64_t cx_carve(const Grid &g, uint64_t n, char *base, CxDev *out)
     d.fcnt = (uint32_t *)take(((uint64_t)d.ntc + 1) * 4);
     d.fbb = (uint32_t *)take(((uint64_t)d.ntc + 1) * 4);
     d.ftot = (uint32_t *)take(faint ? (FB_MAX + 1) * 4 : 0);
-    d.fmat = (uint32_t *)take(faint ? ((n + FB_SRC - 1) / FB_SRC) * (uint64_t)FB_MAX * 4 : 0);
+    // blocks of the faint passes: 16384 sources leave most of the chip idle
+    // below ~4e6 sources; smaller ones make more rows of the matrix, which lies
+    // in the spectra (first written by the first body) if these are large
+    // enough, and otherwise has 16384 sources a row.  4.1e5 sources, count,
+    // columns and scatter: 22 us with 4096, 45 us with 16384.
+    auto matrix = [&](uint32_t src) { return (n + src - 1) / src * (uint64_t)FB_MAX * 4; };
+    d.fsrc = n <= FB_SMALL && matrix(FB_SRC_MIN) <= spectra ? FB_SRC_MIN : FB_SRC;
+    d.fmat = matrix(d.fsrc) <= spectra ? (uint32_t *)d.X : (uint32_t *)take(faint ? matrix(d.fsrc) : 0);
     // binning scratch in memory that is written only later: the candidate
     // records by the direct injection (after the moment path has ended), the
     // ids and the resolved-list buffers after the run; frec lies over c_rho2
@@ -1713,16 +1720,6 @@ uint64_t cx_carve(const Grid &g, uint64_t n, char *base, CxDev *out)
     d.key = d.c_src;
     d.frec = (FaintRec *)d.c_rho2;
     d.forder = d.c_id;
-    // blocks of the faint passes: 16384 sources leave most of the chip idle
-    // below ~4e6 sources; smaller ones make more rows of the matrix, which then
-    // lies in the spectra (first written by the first body) if these are large
-    // enough.  4.1e5 sources, count, columns and scatter: 22 us with 4096,
-    // 45 us with 16384.
-    d.fsrc = FB_SRC;
-    if (faint && n <= FB_SMALL && (n + FB_SRC_MIN - 1) / FB_SRC_MIN * (uint64_t)FB_MAX * 4 <= spectra) {
-        d.fsrc = FB_SRC_MIN;
-        d.fmat = (uint32_t *)d.X;
-    }
     if (out) *out = d;
     return off;
 }
