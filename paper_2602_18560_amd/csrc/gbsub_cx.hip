@@ -1122,7 +1122,8 @@ __device__ __forceinline__ void moment_sums(const KArgs &a, uint32_t o0, uint32_
 // of grouping) with one template per source.  MOM_MIN: a centre's sums cost
 // about 1800 wave instructions for both channels and up to 32 sources (turn
 // 450, folds 330, two times Horner, FFT and rounding 500), 2600 with a wave per
-// channel, a template 240.
+// channel, a template 240; 8 and 6 measure the same as 12 within 1 % (4.1e5
+// and 1e7 sources).
 __global__ __launch_bounds__(WG, 2) void k_cx_faint(KArgs a)
 {
     constexpr int NW = WG / 64;
