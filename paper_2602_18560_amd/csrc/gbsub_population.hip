@@ -91,15 +91,23 @@ __device__ double norm_quantile(double p)
     return z > -37.0 ? z - (norm_lower(z) - p) / norm_pdf(z) : z;
 }
 
-// The normal variate of y under Gamma(a, 1): z with Phi(z) = P(a, y), from the
-// series of P up to z ~ ZSPLIT and the continued fraction of Q beyond (each
-// tail keeps its relative precision).  lga = ln Gamma(a).
+// The normal variate of y = exp(w) under Gamma(a, 1): z with Phi(z) = P(a, y),
+// from the series of P up to zt <= ZSPLIT (zt: where the caller looks for it) and
+// the continued fraction of Q beyond, so that each tail keeps its relative
+// precision.  lga = ln Gamma(a).
+//   The fraction needs about 81/y terms below y ~ 1, and y is far below that
+// beyond ZSPLIT when a is small (6e-5 at z = 1.7 for a = 0.005), so the series also
+// takes y < a + 1: at most 210 terms a node for a from 1e-6 to 0.1, where
+// the fraction by z alone ended after GAMMA_TERMS without having converged, up
+// to 64 times a node, and left fdot off by up to 1.4e-5 for a below 0.01 (now
+// below 1e-12 from a = 1e-3 on; 6e-11 at 1e-4 and 4e-9 at 1e-6, by the rounding of
+// 1 - P).  For a >= 1 the two rules are the same beyond ZSPLIT.
 constexpr double ZSPLIT = 1.5;
 constexpr int GAMMA_TERMS = 1 << 15;
-__device__ double gamma_normal(double a, double lga, double w, bool lower)
+__device__ double gamma_normal(double a, double lga, double w, double zt)
 {
     const double y = exp(w);
-    if (lower) {
+    if (zt <= ZSPLIT || y < a + 1.0) {
         const double pre = exp(a * w - y - lga);
         double t = 1.0 / a, s = t;
         for (int k = 1; k < GAMMA_TERMS; ++k) {
@@ -150,7 +158,7 @@ __device__ void gamma_node(GenTables &t, int j, double a, double beta, double lg
     double z = zt;
     if (a <= 1e6)                       // beyond, Wilson-Hilferty is closer than the sums
         for (int it = 0; it < 64; ++it) {
-            z = gamma_normal(a, lga, w, zt <= ZSPLIT);
+            z = gamma_normal(a, lga, w, zt);
             if (fabs(z - zt) <= 0.25 * H) break;
             const double slope = exp(-0.5 * z * z - LOG_SQRT_2PI - a * w + exp(w) + lga);
             const double dw = fabs(z) < 37.0 ? (zt - z) * slope : zt - z;
