@@ -528,9 +528,9 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
     // synchronization once loop bodies are in flight)
     volatile uint64_t *prog = &c->host_out->prog;
     *prog = 0;
-    // bodies of two launches (k_median_next) from the first one whose dirty
-    // tiles fit the split budget
-    bool two = g.prec == PREC_FP64 && (uint32_t)g.nt <= g.split_tiles;
+    // the form of the body being queued: two launches (k_median_next) or three
+    const bool fits0 = (uint32_t)g.nt <= g.split_tiles;
+    bool two = false;
 
     c->ev_used = 0;
     c->recs.clear();
@@ -540,8 +540,6 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
         if (e == hipSuccess) c->tables_ws = ws;
     }
     if (e == hipSuccess) e = c->timed(K_PREP, -1, st, [&] { return launch_prep(ds, dm, st); });
-    if (e == hipSuccess && !two)
-        e = c->timed_ext(K_XUPDATE, -1, [&](hipEvent_t a, hipEvent_t b) { return launch_xupdate(ds, dm, st, a, b); });
     if (e != hipSuccess) {
         c->tables_ws = nullptr;
         return GBSUB_E_DEVICE;
@@ -552,26 +550,32 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
     // waits for the host and at most AHEAD bodies run past the settled one
     // (their kernels exit at once).  The device enforces max_iter.  A body is
     // median, SNR, then the X update of the next body, whose last block
-    // takes this body's stop decision; once few tiles are dirty (by the latest
-    // word), the X update and that decision are part of the next body's
-    // median launch.  Whenever the stream runs dry without
+    // takes this body's stop decision; while few tiles are dirty (pace_two), the
+    // X update and that decision are part of the next body's median launch,
+    // and a body of three launches after one of two starts with the X update.
+    // Whenever the stream runs dry without
     // a settled flag in sight, the control block in device memory decides.
-    constexpr uint64_t AHEAD = 2;
     const uint64_t guard = (uint64_t)cat->n + 2 + (c->cfg.max_iter ? c->cfg.max_iter : 0);
     auto fail = [&](gbsub_status s) {
         (void)hipStreamSynchronize(st);
         return s;
     };
+    bool owed = true;                // the next body's X update has not been queued
     auto body = [&](int64_t ti) {
-        hipError_t r = c->timed_ext(K_MEDIAN, ti, [&](hipEvent_t a, hipEvent_t b) {
-            return two ? launch_next(ds, dm, st, a, b) : launch_median(ds, dm, st, a, b);
-        });
-        if (r == hipSuccess)
-            r = c->timed_ext(K_SNR, ti, [&](hipEvent_t a, hipEvent_t b) { return launch_snr(ds, dm, st, a, b); });
-        if (r == hipSuccess && !two)
-            r = c->timed_ext(K_XUPDATE, ti, [&](hipEvent_t a, hipEvent_t b) {
+        auto xupdate = [&] {
+            return c->timed_ext(K_XUPDATE, ti, [&](hipEvent_t a, hipEvent_t b) {
                 return launch_xupdate(ds, dm, st, a, b);
             });
+        };
+        hipError_t r = owed && !two ? xupdate() : hipSuccess;
+        if (r == hipSuccess)
+            r = c->timed_ext(K_MEDIAN, ti, [&](hipEvent_t a, hipEvent_t b) {
+                return two ? launch_next(ds, dm, st, a, b) : launch_median(ds, dm, st, a, b);
+            });
+        if (r == hipSuccess)
+            r = c->timed_ext(K_SNR, ti, [&](hipEvent_t a, hipEvent_t b) { return launch_snr(ds, dm, st, a, b); });
+        if (r == hipSuccess && !two) r = xupdate();
+        owed = two;
         return r;
     };
     uint64_t t = 0;                  // bodies enqueued
@@ -579,10 +583,10 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
     auto quiet_since = std::chrono::steady_clock::now();
     for (;;) {
         const uint64_t w = *prog;
-        if (w & 1u) break;
-        const uint32_t seen = (uint32_t)w >> 1;
-        if (t < (uint64_t)seen + AHEAD) {
-            two = two || (g.prec == PREC_FP64 && seen > 0 && (uint32_t)(w >> 32) <= g.split_tiles);
+        if (pace_done(w)) break;
+        const uint32_t seen = pace_finished(w);
+        if (pace_room(w, t)) {
+            two = g.prec == PREC_FP64 && pace_two(w, t, fits0);
             if (t > guard) return fail(GBSUB_E_DEVICE);   // the loop must settle within n + 1 bodies
             if (body((int64_t)t) != hipSuccess) return fail(GBSUB_E_DEVICE);
             ++t;
@@ -609,6 +613,7 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
         if (c->host_ctl->bad) return GBSUB_E_INVALID;
         if (c->host_ctl->done) break;
         if (t > guard) return GBSUB_E_DEVICE;
+        if (pace_room(*prog, t)) continue;             // the word came in meanwhile
         if (body((int64_t)t) != hipSuccess) return fail(GBSUB_E_DEVICE);
         ++t;
     }
@@ -854,7 +859,9 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
             &c->dev_out->prog, &c->dev_out->ctl};
     volatile uint64_t *prog = &c->host_out->prog;
     *prog = 0;
-    bool two = (uint32_t)g.nt <= g.split_tiles;    // bodies of two launches, as in gbsub_run
+    // bodies of two or three launches, as in gbsub_run; here the third is the tail
+    const bool fits0 = (uint32_t)g.nt <= g.split_tiles;
+    bool two = false, owed = false;                // owed: the last body's tail has not been queued
     auto fail = [&](gbsub_status s) {
         (void)hipStreamSynchronize(st);
         return s;
@@ -864,6 +871,8 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
     hipError_t e = c->timed(K_PREP, -1, st, [&] { return cx_launch_prep(g, d, in, st); });
     if (e != hipSuccess) return fail(GBSUB_E_DEVICE);
     auto body = [&](int64_t ti) {
+        const bool late = owed && !two;
+        owed = two;
         if (two) {
             hipError_t r = c->timed_ext(K_MEDIAN, ti, [&](hipEvent_t a, hipEvent_t b) {
                 return cx_launch_next(g, d, st, a, b);
@@ -871,7 +880,8 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
             if (r == hipSuccess) r = c->timed(K_SNR, ti, st, [&] { return cx_launch_snr(g, d, in, st); });
             return r;
         }
-        hipError_t r = c->timed(K_XUPDATE, ti, st, [&] { return cx_launch_power(g, d, in, st); });
+        hipError_t r = late ? c->timed(K_SNR, ti - 1, st, [&] { return launch_cx_tail(d.slots, st); }) : hipSuccess;
+        if (r == hipSuccess) r = c->timed(K_XUPDATE, ti, st, [&] { return cx_launch_power(g, d, in, st); });
         if (r == hipSuccess)
             r = c->timed_ext(K_MEDIAN, ti, [&](hipEvent_t a, hipEvent_t b) { return cx_launch_psd(g, d, st, a, b); });
         if (r == hipSuccess)
@@ -882,17 +892,16 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
         return r;
     };
     // loop bodies paced by the progress word, as in gbsub_run
-    constexpr uint64_t AHEAD = 2;
     const uint64_t guard = (uint64_t)cat->n + 2 + (c->cfg.max_iter ? c->cfg.max_iter : 0);
     uint64_t t = 0;
     uint32_t seen_prev = 0;
     auto quiet_since = std::chrono::steady_clock::now();
     for (;;) {
         const uint64_t w = *prog;
-        if (w & 1u) break;
-        const uint32_t seen = (uint32_t)w >> 1;
-        if (t < (uint64_t)seen + AHEAD) {
-            two = two || (seen > 0 && (uint32_t)(w >> 32) <= g.split_tiles);
+        if (pace_done(w)) break;
+        const uint32_t seen = pace_finished(w);
+        if (pace_room(w, t)) {
+            two = pace_two(w, t, fits0);
             if (t > guard) return fail(GBSUB_E_DEVICE);
             if (body((int64_t)t) != hipSuccess) return fail(GBSUB_E_DEVICE);
             ++t;
@@ -917,6 +926,7 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
         if (e != hipSuccess) return fail(GBSUB_E_DEVICE);
         if (c->host_ctl->done) break;
         if (t > guard) return GBSUB_E_DEVICE;
+        if (pace_room(*prog, t)) continue;
         if (body((int64_t)t) != hipSuccess) return fail(GBSUB_E_DEVICE);
         ++t;
     }

@@ -2,6 +2,8 @@
 // runtime of libgbsub (not part of the public ABI).
 #pragma once
 
+#include "gbsub_pace.h"
+
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -205,8 +207,7 @@ struct Slot {
     uint64_t n;
     uint32_t active;
     uint32_t pad;
-    uint64_t *prog;          // host-mapped word of a single run: dirty tiles of the next body << 32 |
-                             // bodies finished << 1 | settled (null in batches)
+    uint64_t *prog;          // host-mapped progress word of a single run, pace_word (null in batches)
     Ctl *host_ctl;           // host-mapped copy of the control block, written by k_cand_ids (or null)
 };
 

@@ -2174,10 +2174,14 @@ __global__ __launch_bounds__(MWG, 2) void k_median(const Slot *S)
 // chain, so a late body of the 1e7 catalog takes 29 us instead of 35 (median
 // 17, SNR 8.5, X update 9.5), and one of the running mean 19 instead of 26.  A
 // part reads 32 bytes of accumulators per bin, from its first tile's start,
-// where the two launches read 8 of X; taken while the dirty tiles fit the
-// split budget (at most one wave of part-sized blocks on the chip), where the
-// launch is latency, not traffic.  (Template model: X needs no prefix, and the
-// X update and tail launches it saves took 7.4 and 6.1 us a body.)
+// where the two launches read 8 of X; taken while the dirty tiles of the body
+// before fit the split budget (pace_two; at most one wave of part-sized blocks on
+// the chip), where the launch is latency, not traffic.  Runs of the 1e7
+// catalog, 7 full and 15 late bodies: 1557 us by the rule, 1629 with three
+// launches always, 1840 with two always (40 us more a full body); running mean
+// 1218, 1340 and 1374; template model 3302, 3419 and 3908.  (Template model: X
+// needs no prefix, and the X update and tail launches it saves took 7.4 and 6.1
+// us a body.)
 //
 // Blocks and parts.  One slot: a block per part of the grid, and those of clean
 // tiles exit (7372 blocks, 7.5 us when all do, 5 with the 512 of the split
@@ -2937,11 +2941,9 @@ template <int NT> DEVI void snr_tail(const Slot &sl)
         c->units_med = k.units_med + us;
     }
     c->done = done;
-    // progress for the host that paces the launches: the next body's dirty
-    // tiles, the bodies finished and the settled flag in one word, so that the
-    // host never sees one without the others
+    // progress for the host that paces the launches
     if (sl.prog)
-        __hip_atomic_store(sl.prog, (uint64_t)listed << 32 | nxt << 1 | done, __ATOMIC_RELAXED,
+        __hip_atomic_store(sl.prog, pace_word(nxt, done, listed <= g.split_tiles, k.med_split), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
@@ -2997,7 +2999,7 @@ template <int NT> DEVI void cx_tail(const Slot &sl)
     c->n_cand = k.cand_cursor;
     c->done = done;
     if (sl.prog)
-        __hip_atomic_store(sl.prog, (uint64_t)listed << 32 | nxt << 1 | done, __ATOMIC_RELAXED,
+        __hip_atomic_store(sl.prog, pace_word(nxt, done, listed <= g.split_tiles, k.med_split), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
