@@ -144,7 +144,10 @@ gbsub_status gbsub_workspace_size(const gbsub_ctx *ctx, uint64_t n_sources, uint
  * 6-9)} until a body subtracts nothing (step 10; n_iter counts the bodies,
  * the last one included).  `workspace` is a DEVICE pointer to at least
  * gbsub_workspace_size() bytes, 256-byte aligned, owned by the caller and
- * holding the results until the next run or destroy.  All work is enqueued
+ * holding the results until the next run or destroy.  The context's grid
+ * tables stay in it for its next run there: several contexts may use one
+ * workspace in turn (each then loses the others' results), but other writes
+ * to it between two runs of a context are the caller's to avoid.  All work is enqueued
  * on `stream`; the call returns after it has completed.  While it runs, the
  * calling thread keeps a couple of loop bodies queued ahead of the GPU,
  * polling (and yielding) on a progress word that the loop writes to the

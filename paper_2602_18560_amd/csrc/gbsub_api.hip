@@ -45,8 +45,10 @@ struct gbsub_ctx {
     gbsub_summary summ;
     uint32_t n_cand;
     uint64_t res_n;    // its sources (the resolved list's capacity)
-    // the S_instr tables in `tables_ws` were computed for this grid
+    // the S_instr tables in `tables_ws` were computed for this grid and nothing
+    // the library runs has written there since (claim_workspace)
     void *tables_ws;
+    uint64_t tables_span;  // bytes of the smallest workspace: the tables lie inside
     Ctl *host_ctl;     // pinned
     HostOut *host_out;     // pinned, device-mapped, coherent: what kernels write for the host
     HostOut *dev_out;      // the same memory as the kernels address it
@@ -115,6 +117,15 @@ struct gbsub_ctx {
 namespace {
 
 constexpr double C_LIGHT = 299792458.0;
+
+// The live contexts: a run of one takes the tables away from the others whose
+// workspace it writes to.  Guards every context's tables_ws.
+std::mutex g_ctx_mu;
+std::vector<gbsub_ctx *> &live_contexts()
+{
+    static auto *v = new std::vector<gbsub_ctx *>;     // never freed: contexts may outlive static objects
+    return *v;
+}
 
 uint64_t align_up(uint64_t x) { return (x + 255) & ~uint64_t(255); }
 
@@ -206,6 +217,28 @@ uint64_t carve(const Grid &g, uint64_t n, char *base, Dev *d)
 }
 
 gbsub_status dev_err(hipError_t e) { return e == hipSuccess ? GBSUB_OK : GBSUB_E_DEVICE; }
+
+// Ends every context's hold on grid tables that lie in [ws, ws + bytes), except
+// c's own at ws, which a run of c in ws leaves as they are (own); returns
+// whether c has those.  (Several contexts may use one workspace in turn, and the
+// template model may use the power model's.)
+bool claim_workspace(gbsub_ctx *c, void *ws, uint64_t bytes, bool own)
+{
+    std::lock_guard<std::mutex> lk(g_ctx_mu);
+    const uintptr_t lo = (uintptr_t)ws, hi = lo + bytes;
+    for (gbsub_ctx *o : live_contexts()) {
+        const uintptr_t t = (uintptr_t)o->tables_ws;
+        if (!t || (o == c && own && t == lo)) continue;
+        if (t < hi && lo < t + o->tables_span) o->tables_ws = nullptr;
+    }
+    return own && c->tables_ws == ws;
+}
+
+void hold_tables(gbsub_ctx *c, void *ws)
+{
+    std::lock_guard<std::mutex> lk(g_ctx_mu);
+    c->tables_ws = ws;
+}
 
 gbsub_status validate(const gbsub_config *c, Grid *g)
 {
@@ -463,6 +496,7 @@ gbsub_status gbsub_create(const gbsub_config *cfg, gbsub_ctx **out)
     c->have_result = false;
     c->ws = nullptr;
     c->tables_ws = nullptr;
+    c->tables_span = carve(g, 0, nullptr, nullptr);
     c->host_ctl = nullptr;
     c->host_out = nullptr;
     c->dev_out = nullptr;
@@ -487,6 +521,13 @@ gbsub_status gbsub_create(const gbsub_config *cfg, gbsub_ctx **out)
         gbsub_destroy(c);
         return GBSUB_E_DEVICE;
     }
+    try {
+        std::lock_guard<std::mutex> lk(g_ctx_mu);
+        live_contexts().push_back(c);
+    } catch (const std::bad_alloc &) {
+        gbsub_destroy(c);
+        return GBSUB_E_NOMEM;
+    }
     *out = c;
     return GBSUB_OK;
 }
@@ -494,6 +535,11 @@ gbsub_status gbsub_create(const gbsub_config *cfg, gbsub_ctx **out)
 void gbsub_destroy(gbsub_ctx *c)
 {
     if (!c) return;
+    {
+        std::lock_guard<std::mutex> lk(g_ctx_mu);
+        std::vector<gbsub_ctx *> &v = live_contexts();
+        v.erase(std::remove(v.begin(), v.end(), c), v.end());
+    }
     if (c->host_ctl) (void)hipHostFree(c->host_ctl);
     if (c->host_out) (void)hipHostFree(c->host_out);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
@@ -517,7 +563,7 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
     if (use_device(c->device) != GBSUB_OK) return GBSUB_E_DEVICE;
     hipStream_t st = (hipStream_t)stream;
     Dev d;
-    carve(c->g, cat->n, (char *)ws, &d);
+    const bool tables = claim_workspace(c, ws, carve(c->g, cat->n, (char *)ws, &d), true);
     const Grid &g = c->g;
     Slot *ds = reinterpret_cast<Slot *>(ws);    // one-slot table at the start of the workspace
     Slot slot = make_slot(g, d, cat);
@@ -535,13 +581,13 @@ gbsub_status gbsub_run(gbsub_ctx *c, const gbsub_catalog *cat, void *ws, uint64_
     c->ev_used = 0;
     c->recs.clear();
     hipError_t e = c->timed(K_RESET, -1, st, [&] { return launch_reset(ds, slot, st); });
-    if (e == hipSuccess && c->tables_ws != ws) {
+    if (e == hipSuccess && !tables) {
         e = c->timed(K_TABLES, -1, st, [&] { return launch_grid_tables(ds, dm, st); });
-        if (e == hipSuccess) c->tables_ws = ws;
+        if (e == hipSuccess) hold_tables(c, ws);
     }
     if (e == hipSuccess) e = c->timed(K_PREP, -1, st, [&] { return launch_prep(ds, dm, st); });
     if (e != hipSuccess) {
-        c->tables_ws = nullptr;
+        hold_tables(c, nullptr);
         return GBSUB_E_DEVICE;
     }
     // Loop bodies, paced by the progress word the tail writes to host
@@ -671,9 +717,9 @@ gbsub_status gbsub_run_static(gbsub_ctx *c, const gbsub_catalog *cat, void *stre
     // grows host-side records.
     const uint32_t prof = c->profiling;
     c->profiling = 0;
-    c->tables_ws = nullptr;
+    hold_tables(c, nullptr);
     const gbsub_status st = gbsub_run(c, cat, ws, (uint64_t)GBSUB_STATIC_WORKSPACE_BYTES, stream, out);
-    c->tables_ws = nullptr;
+    hold_tables(c, nullptr);
     c->profiling = prof;
     return st;
 }
@@ -854,7 +900,7 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
     hipStream_t st = (hipStream_t)stream;
     const Grid &g = c->g;
     CxDev d;
-    cx_carve(g, cat->n, (char *)ws, &d);
+    (void)claim_workspace(c, ws, cx_carve(g, cat->n, (char *)ws, &d), false);
     CxIn in{cat->A, cat->f, cat->fdot, cat->phi_a, cat->phi_e, cat->id, (uint32_t)cat->n,
             &c->dev_out->prog, &c->dev_out->ctl};
     volatile uint64_t *prog = &c->host_out->prog;
@@ -1220,19 +1266,19 @@ gbsub_status gbsub_batch_admit(gbsub_batch *b, gbsub_ctx *c, const gbsub_catalog
     if (use_device(b->device) != GBSUB_OK) return GBSUB_E_DEVICE;
     hipStream_t st = (hipStream_t)stream;
     Dev d;
-    carve(c->g, cat->n, (char *)ws, &d);
+    const bool tables = claim_workspace(c, ws, carve(c->g, cat->n, (char *)ws, &d), true);
     b->host_table[k] = make_slot(c->g, d, cat);
     const Dims one = dims_of(b->host_table[k]);
     Slot *ds = b->table + k;
     hipError_t e = launch_reset(ds, b->host_table[k], st);
-    if (e == hipSuccess && c->tables_ws != ws) {
+    if (e == hipSuccess && !tables) {
         e = launch_grid_tables(ds, one, st);
-        if (e == hipSuccess) c->tables_ws = ws;
+        if (e == hipSuccess) hold_tables(c, ws);
     }
     if (e == hipSuccess) e = launch_prep(ds, one, st);
     if (e == hipSuccess) e = launch_xupdate(ds, one, st);
     if (e != hipSuccess) {
-        c->tables_ws = nullptr;
+        hold_tables(c, nullptr);
         return GBSUB_E_DEVICE;
     }
     c->have_result = false;
