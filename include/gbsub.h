@@ -260,8 +260,9 @@ enum {
     GBSUB_KF_TABLES = 0,         /* S_instr and its prefix tables (first run on a workspace) */
     GBSUB_KF_RESET = 1,          /* per-run state */
     GBSUB_KF_PREP = 2,           /* candidate cut, binning, fixed-point accumulation */
-    GBSUB_KF_XUPDATE = 3,        /* X from the fixed-point accumulators */
-    GBSUB_KF_MEDIAN = 4,         /* running median, S = C med + S_instr, in-part prefix of 1/S */
+    GBSUB_KF_XUPDATE = 3,        /* X from the fixed-point accumulators, as a launch of its own */
+    GBSUB_KF_MEDIAN = 4,         /* running median, S = C med + S_instr, in-part prefix of 1/S; in
+                                    late bodies the X update too (then not in XUPDATE's units) */
     GBSUB_KF_SNR = 5,            /* rho^2 (the part sums of 1/S under each track), decisions,
                                     subtraction, dirty tiles, settle test */
     GBSUB_KF_OUTPUT = 6,         /* candidate ids */

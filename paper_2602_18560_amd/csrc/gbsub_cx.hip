@@ -492,7 +492,8 @@ __global__ __launch_bounds__(WG) void k_cx_reset(KArgs a)
         c->iter = 0;
         c->n_near = 0;
         c->min_margin = 0x7FF0000000000000ull;   // +inf
-        c->units_x = (uint64_t)g.B;
+        c->units_x = 0;
+        c->x_next = (uint32_t)g.B;
         c->units_med = (uint64_t)g.B;
         c->units_snr = 0;
         c->status = 0;
@@ -1425,9 +1426,10 @@ __global__ __launch_bounds__(WG) void k_cx_power(KArgs a)
 {
     const Grid &g = a.g;
     const CxDev &d = a.d;
-    const Ctl *c = d.ctl;
+    Ctl *c = d.ctl;
     if (c->done || c->bad) return;
     const int tile = blockIdx.x;
+    if (tile == 0 && threadIdx.x == 0) c->units_x += c->x_next;
     if (tile >= g.nt || d.xstamp[tile] != c->iter) return;
     const int E = cx_exp(c->amax_bits, a.in.n, g.T);
     const double s2 = 2.0 / g.T;

@@ -75,7 +75,7 @@ struct Ctl {
     uint32_t iter;           // index t of the next loop body
     uint64_t n_near;         // evaluations within 1e-6 of the threshold
     uint64_t min_margin;     // bits of min |rho/rho_th - 1| (non-negative double)
-    uint64_t units_x;        // bins converted by k_xupdate
+    uint64_t units_x;        // bins converted by k_xupdate (k_cx_power)
     uint64_t units_med;      // median outputs computed by k_median
     uint64_t units_snr;      // candidate evaluations by k_snr
     uint32_t status;         // 0 running/settled, 6 = max_iter reached with sources still resolving
@@ -86,6 +86,8 @@ struct Ctl {
     uint32_t n_sdl;          // tiles listed in sdl for the next median launch
     uint32_t res_cursor;     // entries of the resolved list handed out (list_resolved)
     uint32_t acc_ev;         // events per accumulation block
+    uint32_t x_next;         // template model: bins whose X the next body converts
+    uint32_t pad;
 };
 
 // Per-block partial results of k_snr (combined by the tail: the last block

@@ -447,8 +447,8 @@ __global__ __launch_bounds__(WG) void k_reset(Slot sl, Slot *ds)
         c->iter = 0;
         c->n_near = 0;
         c->min_margin = 0x7FF0000000000000ull;   // +inf
-        c->units_x = (uint64_t)g.B;              // the first body converts and filters every bin
-        c->units_med = (uint64_t)g.B;
+        c->units_x = 0;
+        c->units_med = (uint64_t)g.B;            // the first body filters every bin
         c->units_snr = 0;
         c->status = 0;
         c->med_split = (uint32_t)g.nt <= g.split_tiles;   // every tile is dirty
@@ -1229,7 +1229,7 @@ __global__ __launch_bounds__(WG) void k_accum_f32(const Slot *S)
 // conflicts).
 DEVI int xpad(int i) { return i + (i >> 3); }
 
-template <int NT> DEVI void snr_tail(const Slot &sl);
+template <int NT> DEVI void snr_tail(const Slot &sl, bool converts);
 
 // The compensated FP32 mode's X of one tile: X = Xc + (carry + in-tile
 // prefix of Dc), every sum double-fp32, rounded once to fp32 at the end.
@@ -1282,7 +1282,9 @@ __global__ __launch_bounds__(WG) void k_xupdate(const Slot *S)
     const Slot &sl = S[blockIdx.y];
     if (!sl.active) return;
     if (blockIdx.x == gridDim.x - 1) {
-        snr_tail<WG>(sl);
+        // ahead of the first body: every tile, and no tail
+        if (threadIdx.x == 0 && sl.d.ctl->xupd == 0) sl.d.ctl->units_x = (uint64_t)sl.g.B;
+        snr_tail<WG>(sl, true);
         return;
     }
     const Grid g = sl.g;
@@ -2191,7 +2193,7 @@ __global__ __launch_bounds__(MWG, 2) void k_median(const Slot *S)
 // The lookup takes 1.5 us of a block's chain: late launches of the 1e7 catalogs
 // 20 us with it instead of 24 for two channels, 21 instead of 20 for one slot
 // (running mean 13 instead of 11).
-template <int NT> DEVI void snr_tail(const Slot &sl);
+template <int NT> DEVI void snr_tail(const Slot &sl, bool converts);
 template <int NT> DEVI void cx_tail(const Slot &sl);
 
 // The n-th tile (from 0, in tile order) whose stamp is val (-1: there are not as
@@ -2263,7 +2265,7 @@ template <XSource SRC> __global__ __launch_bounds__(MWG, 4) void k_median_next(c
         if constexpr (SRC == X_CX) {
             if (blockIdx.y == 0) cx_tail<MWG>(sl);
         } else {
-            snr_tail<MWG>(sl);
+            snr_tail<MWG>(sl, false);
         }
         return;
     }
@@ -2429,7 +2431,7 @@ template <XSource SRC> __global__ __launch_bounds__(MWG, 4) void k_mean_next(con
         if constexpr (SRC == X_CX) {
             if (blockIdx.y == 0) cx_tail<MWG>(sl);
         } else {
-            snr_tail<MWG>(sl);
+            snr_tail<MWG>(sl, false);
         }
         return;
     }
@@ -2867,8 +2869,8 @@ DEVI uint32_t list_stamped(const Grid &g, const Dev &d, uint32_t nxt, uint32_t (
 // ended: combines the per-block partials, counts the tiles stamped for the
 // next body, takes the stop decision (nothing new subtracted, or max_iter)
 // and whether the next median runs in split mode.  It runs at most once per
-// k_snr (tail_due).
-template <int NT> DEVI void snr_tail(const Slot &sl)
+// k_snr (tail_due).  converts: the next body's X is k_xupdate's to convert.
+template <int NT> DEVI void snr_tail(const Slot &sl, bool converts)
 {
     constexpr int NW = NT / 64;
     constexpr int NR = 4;                 // new, near, evals, X tiles
@@ -2937,7 +2939,7 @@ template <int NT> DEVI void snr_tail(const Slot &sl)
         c->n_iter = nxt;
     } else {
         c->iter = nxt;
-        c->units_x = k.units_x + ux;
+        if (converts) c->units_x = k.units_x + ux;
         c->units_med = k.units_med + us;
     }
     c->done = done;
@@ -2961,7 +2963,7 @@ template <int NT> DEVI void cx_tail(const Slot &sl)
     const Ctl k = *c;
     if (k.done || !(k.tail_due || k.bad)) return;
     const uint32_t nxt = k.iter + 1;
-    const uint32_t lx = d.xstamp[g.nt - 1];
+    const uint32_t lx = d.xstamp[g.nt - 1], ls = d.sstamp[g.nt - 1];
     if (threadIdx.x == 0) s_nx = 0;
     __syncthreads();
     uint32_t nx = 0;
@@ -2976,7 +2978,7 @@ template <int NT> DEVI void cx_tail(const Slot &sl)
         done = 1;
         c->n_iter = k.iter;
     } else {
-        const uint64_t units = (uint64_t)s_nx * (uint32_t)g.tile - (lx == nxt ? (uint32_t)(g.nt * g.tile - g.B) : 0u);
+        const uint32_t pad = (uint32_t)(g.nt * g.tile - g.B);      // the last tile may be short
         const uint32_t n_new = k.n_new_body;
         c->n_new_body = 0;
         c->n_resolved = k.n_resolved + n_new;
@@ -2992,8 +2994,8 @@ template <int NT> DEVI void cx_tail(const Slot &sl)
             c->iter = nxt;
             c->med_split = listed <= g.split_tiles;
             c->n_sdl = listed;
-            c->units_x = k.units_x + units;
-            c->units_med = k.units_med + units;
+            c->x_next = s_nx * (uint32_t)g.tile - (lx == nxt ? pad : 0u);
+            c->units_med = k.units_med + (uint64_t)listed * (uint32_t)g.tile - (ls == nxt ? pad : 0u);
         }
     }
     c->n_cand = k.cand_cursor;
@@ -3011,7 +3013,7 @@ __global__ __launch_bounds__(SNR_BLOCKS) void k_snr_tail(const Slot *S)
 {
     const Slot &sl = S[blockIdx.y];
     if (!sl.active) return;
-    snr_tail<SNR_BLOCKS>(sl);
+    snr_tail<SNR_BLOCKS>(sl, true);
 }
 
 // ------------------------------------------------------------------ outputs
