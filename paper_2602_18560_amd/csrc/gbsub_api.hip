@@ -976,7 +976,11 @@ gbsub_status gbsub_cx_run(gbsub_ctx *c, const gbsub_cx_catalog *cat, void *ws, u
         if (body((int64_t)t) != hipSuccess) return fail(GBSUB_E_DEVICE);
         ++t;
     }
-    e = cx_launch_outputs(g, d, in, st);
+    if (cx_bounded(in.n)) {
+        const bool count = c->profiling >> K_SNR & 1u;
+        e = c->timed(K_SNR, -1, st, [&] { return cx_launch_final(g, d, in, count, st); });
+    }
+    if (e == hipSuccess) e = cx_launch_outputs(g, d, in, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(GBSUB_E_DEVICE);
     const Ctl &h = c->host_out->ctl;

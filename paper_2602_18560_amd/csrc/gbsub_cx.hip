@@ -491,7 +491,7 @@ __global__ __launch_bounds__(WG) void k_cx_reset(KArgs a)
         c->n_events = 0;
         c->iter = 0;
         c->n_near = 0;
-        c->min_margin = 0x7FF0000000000000ull;   // +inf
+        c->min_margin = c->margin = 0x7FF0000000000000ull;   // +inf
         c->units_x = 0;
         c->x_next = (uint32_t)g.B;
         c->units_med = (uint64_t)g.B;
@@ -1460,15 +1460,18 @@ __global__ __launch_bounds__(WG) void k_cx_power(KArgs a)
 // A^2 / 4) rho^2 <= T A^2 (max 1/S_A + max 1/S_E) over the template's bins, and
 // the PSD launches leave the maxima of every 64-bin segment.  From the second
 // body on, a candidate whose bound stays below the threshold by more than
-// the run's smallest margin so far (and the 1e-6 that counts as near) is not
+// the smallest margin of the bodies before (and the 1e-6 that counts as near;
+// not the running body's, which its waves lower at their own times) is not
 // evaluated: it is not resolved, and neither the margin nor the near count
 // would change.  Its rho^2 is marked stale (-1) and computed after the loop
-// (FINAL: S on its bins is still that of its last body).  SNR of the 1e7
+// (FINAL: S on its bins is still that of its last body; its evaluations are
+// counted only for the kernel statistics, where one same-address atomic per
+// wave costs 50 us at 1e7 sources).  SNR of the 1e7
 // catalog 1.01 ms a run, the last pass's 0.08 included, 1.66 with every candidate
 // evaluated; 4.1e5 sources (2 yr, mean) 102 and 123 us; at 1e4 sources the
 // evaluations fit one round of waves and the last pass would cost 9 us of 30
 // (BOUND_MIN_N).
-template <bool FINAL>
+template <bool FINAL, bool COUNT>
 __global__ __launch_bounds__(WG, 4) void k_cx_snr(KArgs a)
 {
     __shared__ double2 ex[NEX];
@@ -1481,7 +1484,7 @@ __global__ __launch_bounds__(WG, 4) void k_cx_snr(KArgs a)
     if (c->bad || (!FINAL && c->done)) return;
     const uint32_t t = c->iter, nxt = t + 1;
     const uint32_t nc = c->cand_cursor;
-    const double margin = fmax(__longlong_as_double((long long)c->min_margin), 2e-6);
+    const double margin = fmax(__longlong_as_double((long long)c->margin), 2e-6);
     const double skip2 = margin < 1.0 ? g.rth2 * (1.0 - margin) * (1.0 - margin) * (1.0 - 1e-9) : 0.0;
     const int E = cx_exp(c->amax_bits, in.n, g.T);
     const double T = g.T;
@@ -1583,7 +1586,10 @@ __global__ __launch_bounds__(WG, 4) void k_cx_snr(KArgs a)
             }
         }
     }
-    if (FINAL) return;
+    if (FINAL) {
+        if (COUNT && lane() == 0 && evals) atomicAdd((unsigned long long *)&c->units_snr, (unsigned long long)evals);
+        return;
+    }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         c->xupd = nxt;
         c->tail_due = 1;
@@ -1783,13 +1789,23 @@ hipError_t cx_launch_next(const Grid &g, const CxDev &d, hipStream_t st, hipEven
 
 hipError_t cx_launch_snr(const Grid &g, const CxDev &d, const CxIn &in, hipStream_t st)
 {
-    k_cx_snr<false><<<SNR_GRID, WG, 0, st>>>(args_of(g, d, in));
+    k_cx_snr<false, true><<<SNR_GRID, WG, 0, st>>>(args_of(g, d, in));
+    return hipGetLastError();
+}
+
+bool cx_bounded(uint32_t n) { return n >= BOUND_MIN_N; }
+
+hipError_t cx_launch_final(const Grid &g, const CxDev &d, const CxIn &in, bool count, hipStream_t st)
+{
+    if (count)
+        k_cx_snr<true, true><<<SNR_GRID, WG, 0, st>>>(args_of(g, d, in));
+    else
+        k_cx_snr<true, false><<<SNR_GRID, WG, 0, st>>>(args_of(g, d, in));
     return hipGetLastError();
 }
 
 hipError_t cx_launch_outputs(const Grid &g, const CxDev &d, const CxIn &in, hipStream_t st)
 {
-    if (in.n >= BOUND_MIN_N) k_cx_snr<true><<<SNR_GRID, WG, 0, st>>>(args_of(g, d, in));
     k_cx_ids<<<256, WG, 0, st>>>(args_of(g, d, in));
     return hipGetLastError();
 }

@@ -75,6 +75,7 @@ struct Ctl {
     uint32_t iter;           // index t of the next loop body
     uint64_t n_near;         // evaluations within 1e-6 of the threshold
     uint64_t min_margin;     // bits of min |rho/rho_th - 1| (non-negative double)
+    uint64_t margin;         // template model: min_margin of the bodies that have ended
     uint64_t units_x;        // bins converted by k_xupdate (k_cx_power)
     uint64_t units_med;      // median outputs computed by k_median
     uint64_t units_snr;      // candidate evaluations by k_snr
@@ -342,6 +343,10 @@ hipError_t cx_launch_psd(const Grid &g, const CxDev &d, hipStream_t st, hipEvent
 hipError_t cx_launch_next(const Grid &g, const CxDev &d, hipStream_t st, hipEvent_t ea = nullptr,
                           hipEvent_t eb = nullptr);
 hipError_t cx_launch_snr(const Grid &g, const CxDev &d, const CxIn &in, hipStream_t st);
+// The evaluations that the bound put off until the loop has ended (catalogs
+// for which cx_bounded); count: into units_snr.
+bool cx_bounded(uint32_t n);
+hipError_t cx_launch_final(const Grid &g, const CxDev &d, const CxIn &in, bool count, hipStream_t st);
 hipError_t cx_launch_outputs(const Grid &g, const CxDev &d, const CxIn &in, hipStream_t st);
 // h_ch in fp64, re and im of bin k at out[2k], out[2k + 1].
 hipError_t cx_launch_h(const Grid &g, const CxDev &d, uint32_t n, int ch, double *out, hipStream_t st);

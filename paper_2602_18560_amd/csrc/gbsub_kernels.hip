@@ -2974,6 +2974,7 @@ template <int NT> DEVI void cx_tail(const Slot &sl)
     if (threadIdx.x != 0) return;
     uint32_t done = 0;
     c->tail_due = 0;
+    c->margin = k.min_margin;
     if (k.bad) {
         done = 1;
         c->n_iter = k.iter;
