@@ -52,7 +52,9 @@
 //    synthesises one template after the other.
 //  * The per-channel PSD is the power model's median (or mean) kernel, run
 //    over a two-slot descriptor table (A and E), with the same dirty-tile
-//    stamps; a body is X update, PSD, SNR + subtraction, and a one-block tail.
+//    stamps; a body is X update, PSD, SNR + subtraction, and a one-block tail, or,
+//    while few tiles are dirty, PSD (with the X update and the tail of the body
+//    before) and SNR.
 
 #include "gbsub_internal.h"
 #include "gbsub_device.h"
@@ -978,9 +980,13 @@ __device__ __forceinline__ SrcConsts bcast(const SrcConsts &c, int k)
 // amplitude: every coefficient stays below 2^50, and centres with more than
 // 4096 sources take a coarser unit so that no sum leaves 64 bits): the sum
 // does not depend on the order of a centre's sources, which the grouping
-// leaves open.  With catalogs of at least 2^16 sources the unit is finer than
-// h's own rounding of every single template was (2^-E with E <= 45 - ilogb(A
-// T/2); here 2^-48), and h is rounded once per centre.
+// leaves open.  A coefficient's unit reaches a value of the template 2^7 times
+// (the DFT's 128 samples): with v = A T/2 of the loudest source it is 2^-48 v
+// there, and 2^-(59 - k) v for a centre of more than 4096 sources, at least 2^k of
+// them; h, and a template rounded on its own, has 2^-(61 - log2 n) v, 2^-45 v or
+// more.  So the unit is the finer one unless a centre holds more than a quarter
+// of the catalog, and at most four times the other then.  h is rounded once per
+// centre.
 //
 // Only sources that can never be candidates are taken, so none is ever
 // subtracted: h stays the same integer whatever subset of the candidates is
@@ -1445,7 +1451,8 @@ __global__ __launch_bounds__(WG) void k_cx_power(KArgs a)
 
 // rho^2 of every unsubtracted candidate whose template meets a tile
 // refiltered in this body (or stamped for the next one by a subtraction of
-// this launch: re-evaluating against an unchanged S gives the same value);
+// this launch: re-evaluating against an unchanged S gives the same value, so
+// only the count of evaluations may differ between two runs);
 // rho^2 > rho_th^2 subtracts its templates from h at once and stamps the
 // tiles whose X and S change.  Each wave takes 64 candidates at a time: the
 // lanes find which need an evaluation and their constants, then the wave
@@ -1466,11 +1473,13 @@ __global__ __launch_bounds__(WG) void k_cx_power(KArgs a)
 // would change.  Its rho^2 is marked stale (-1) and computed after the loop
 // (FINAL: S on its bins is still that of its last body; its evaluations are
 // counted only for the kernel statistics, where one same-address atomic per
-// wave costs 50 us at 1e7 sources).  SNR of the 1e7
-// catalog 1.01 ms a run, the last pass's 0.08 included, 1.66 with every candidate
-// evaluated; 4.1e5 sources (2 yr, mean) 102 and 123 us; at 1e4 sources the
-// evaluations fit one round of waves and the last pass would cost 9 us of 30
-// (BOUND_MIN_N).
+// wave costs 50 us at 1e7 sources).  SNR of the 1e7 catalog 1.01 ms a run, the
+// last pass's 0.08 included, 1.66 with every candidate evaluated; 4.1e5 sources (2
+// yr, mean) 102 and 123 us.  Whole runs of small catalogs (1 yr), with and without
+// the bound: 2e3 sources 250 and 236 us, 8e3 268 and 261, 1.6e4 292 and 287,
+// 2.4e4 346 and 340, 3.2e4 361 and 363, 6.5e4 441 and 463.  Below BOUND_MIN_N
+// the evaluations fit one round of waves and the last pass's 5 to 14 us is all it
+// changes; from there to 3e4 the two are within 2 %.
 template <bool FINAL, bool COUNT>
 __global__ __launch_bounds__(WG, 4) void k_cx_snr(KArgs a)
 {
@@ -1713,11 +1722,14 @@ uint64_t cx_carve(const Grid &g, uint64_t n, char *base, CxDev *out)
     d.fcnt = (uint32_t *)take(((uint64_t)d.ntc + 1) * 4);
     d.fbb = (uint32_t *)take(((uint64_t)d.ntc + 1) * 4);
     d.ftot = (uint32_t *)take(faint ? (FB_MAX + 1) * 4 : 0);
-    // blocks of the faint passes: 16384 sources leave most of the chip idle
-    // below ~4e6 sources; smaller ones make more rows of the matrix, which lies
+    // blocks of the faint passes: 16384 sources leave most of the chip idle in
+    // small catalogs; smaller ones make more rows of the matrix, which lies
     // in the spectra (first written by the first body) if these are large
     // enough, and otherwise has 16384 sources a row.  4.1e5 sources, count,
-    // columns and scatter: 22 us with 4096, 45 us with 16384.
+    // columns and scatter: 22 us with 4096, 45 us with 16384.  Whole runs (4 yr)
+    // with rows of 4096 and 16384: 2e5 sources 778 and 802 us, 1e6 1171 and 1190,
+    // 1.5e6 1403 and 1416, 2e6 1525 and 1532, 4e6 2011 and 2004, 8e6 2901 and 2915:
+    // from FB_SMALL on the two are within 1 %, and the longer rows write less.
     auto matrix = [&](uint32_t src) { return (n + src - 1) / src * (uint64_t)FB_MAX * 4; };
     d.fsrc = n <= FB_SMALL && matrix(FB_SRC_MIN) <= spectra ? FB_SRC_MIN : FB_SRC;
     d.fmat = matrix(d.fsrc) <= spectra ? (uint32_t *)d.X : (uint32_t *)take(faint ? matrix(d.fsrc) : 0);

@@ -1351,7 +1351,7 @@ __global__ __launch_bounds__(WG) void k_xupdate(const Slot *S)
 //
 // One block per tile of `tile` outputs.  The union of the tile's windows
 // (tile + W - 1 bins) is loaded once into LDS and sorted there: a stable LSD
-// radix sort on a per-tile 16-bit order key (the fp64 bit pattern minus the
+// radix sort on a per-tile 18-bit order key (the fp64 bit pattern minus the
 // tile minimum, shifted), then an exact repair that orders equal keys by
 // the full fp64 value.  The sorted order is cut into buckets of 32 or 64
 // consecutive ranks, and a bit matrix in LDS holds, for every bucket b and
@@ -1360,7 +1360,9 @@ __global__ __launch_bounds__(WG) void k_xupdate(const Slot *S)
 // is the h-th smallest rank among its W positions: a binary search over the
 // buckets (two counts per step) gives its bucket and its index there, and
 // the bucket's sorted elements are tested against the window.  Each of the
-// 512 threads answers its R = tile/512 (at most 4) windows independently.
+// 512 threads answers its first window so, and its other R - 1 (R = tile/512, at
+// most 4) by sliding: one element leaves, one enters, and the median stays or
+// moves to a neighbour in the sorted order.
 // Selection is exact: no arithmetic touches X.
 //
 // The kernel is bound by the latency of its LDS phases (two blocks per CU in
@@ -2596,11 +2598,6 @@ DEVI void subtract_track_comp(const Grid &g, const Dev &d, int glo, int ghi, flo
         ff_atomic_add(&d.Dtc[div_p2(ghi + 1, g.tile)], vf);
     }
 }
-
-// Stamps tiles lo/tile .. hi/tile for body `nxt` (every writer stores the
-// same value, read after the launch ends; the tail counts the stamped
-// tiles).
-
 
 // True when S^t may differ from S^{t-1} somewhere on tiles lo/tile ..
 // hi/tile: one of them was refiltered in body t (stamp t), or was stamped

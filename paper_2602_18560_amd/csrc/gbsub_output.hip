@@ -17,8 +17,9 @@
 //    the (id, body) pairs by id, 8 bits per pass (per-block digit histograms,
 //    one scan over (digit, block), a stable scatter ranked by ballots inside
 //    each wave), whose cost is linear in the entries while the searches'
-//    grows with their square.
-//
+//    grows with their square.  Both ways, whole calls: 2^16 entries 61 us by
+//    searches and 141 by passes, 2^17 162 and 157, 3 2^16 331 and 172, 2^18 567
+//    and 188.
 #include "gbsub_internal.h"
 
 namespace gbs {

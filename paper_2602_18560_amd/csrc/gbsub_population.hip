@@ -56,8 +56,9 @@ __device__ __forceinline__ double unit53(uint32_t hi, uint32_t lo)
 // sqrt(2 * 54 ln 2) = 8.652 of zero.  A block lays NODE expansion points over
 // that range (spacing H) in LDS and each source evaluates one polynomial per
 // marginal, instead of inverting the incomplete gamma function on its own: a
-// node needs P(a, y) about once (the node is put at the z that belongs to
-// its y, so no root finding), and its coefficients follow from the
+// node needs P(a, y) one to three times in the prior's range (up to 7 for
+// shapes of 1e-3; the node is put at the z that belongs to its y, so Newton steps
+// need only come within H/4 of its place), and its coefficients follow from the
 // differential equations of the two maps.
 //   Truncation: log f(z) has its nearest singularities where the power-law
 // argument vanishes, at a distance of at least about 0.87 from the real axis
