@@ -306,7 +306,8 @@ gbsub_status gbsub_kernel_stats(const gbsub_ctx *ctx, gbsub_kernel_stat *out, ui
  * between steps (continuous batching).  Each admitted slot uses its own
  * context (configuration, results) and its own workspace; the results of a
  * retired slot are read with gbsub_spectrum / gbsub_resolved on that context.
- * Results are identical to gbsub_run on the same context and catalog. */
+ * Results are those of gbsub_run on the same context and catalog, up to the
+ * association of the fp64 sums (the split budget is shared, see split_blocks). */
 typedef struct gbsub_batch gbsub_batch;
 
 enum {                                   /* slot states reported by gbsub_batch_poll */
