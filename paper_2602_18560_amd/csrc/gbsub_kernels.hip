@@ -970,12 +970,12 @@ DEVI I128 split_total(const SplitAcc &a, int k)
     return i128_add(x, y);
 }
 
-// The compensated FP32 mode's binning of events e0 .. e1 of tile b (chunk
-// ci): every event's power rounded to fp32 (scaled by 2^sc), summed per bin
+// The compensated FP32 mode's binning of the ne events from e0 on of tile b
+// (chunk ci): every event's power rounded to fp32 (scaled by 2^sc), summed per bin
 // in LDS by compensated atomics (xc: one-bin tracks, dc: difference array;
 // TILE_MAX entries each); written to Xc, Dc and the tile sum of Dc, or to
 // the chunk's partial-sum slot of a hot tile.
-DEVI void accum_comp(const Grid &g, const Dev &d, int b, uint32_t ci, uint32_t e0, uint32_t e1, FF *xc, FF *dc)
+DEVI void accum_comp(const Grid &g, const Dev &d, int b, uint32_t ci, uint32_t e0, uint32_t ne, FF *xc, FF *dc)
 {
     __shared__ FF shf[ACC_T / 64];
     const int k0 = b * g.tile;
@@ -986,9 +986,9 @@ DEVI void accum_comp(const Grid &g, const Dev &d, int b, uint32_t ci, uint32_t e
         dc[k] = ff_of(0.0f);
     }
     __syncthreads();
-    for (uint32_t e = e0 + threadIdx.x; e < e1; e += ACC_T) {
-        const uint32_t key = d.ev_key[e];
-        const float v = (float)ldexp((double)d.ev_val[e], L + sc);
+    for (uint32_t e = threadIdx.x; e < ne; e += ACC_T) {
+        const uint32_t key = d.ev_key[e0 + e];
+        const float v = (float)ldexp((double)d.ev_val[e0 + e], L + sc);
         const int k = (int)(key & 0x7FFFFFFFu) - k0;
         ff_atomic_add((key >> 31) ? &dc[k] : &xc[k], v);
     }
@@ -1036,11 +1036,13 @@ __global__ __launch_bounds__(ACC_T) void k_accum(const Slot *S)
     const int b = lo;
     const uint32_t ci = c - d.chunk_base[b];
     const uint32_t ev = d.ctl->acc_ev;
+    // this block's events, by their offset: a catalog's event numbers reach 2^32 - 2,
+    // and a step past the last one would wrap
     const uint32_t e0 = d.bbase[b] + ci * ev;
-    const uint32_t e1 = min(e0 + ev, d.bbase[b + 1]);
+    const uint32_t ne = min(ev, d.bbase[b + 1] - e0);
     const int k0 = b * g.tile;
     if (g.prec == PREC_COMP) {
-        accum_comp(g, d, b, ci, e0, e1, reinterpret_cast<FF *>(xn.h), reinterpret_cast<FF *>(dd.h));
+        accum_comp(g, d, b, ci, e0, ne, reinterpret_cast<FF *>(xn.h), reinterpret_cast<FF *>(dd.h));
         return;
     }
     for (int k = threadIdx.x; k < g.tile; k += ACC_T) {
@@ -1053,18 +1055,18 @@ __global__ __launch_bounds__(ACC_T) void k_accum(const Slot *S)
     // flight, 51 with 256 and 4 (1e7 sources 57 and 91); 1024 threads leave one
     // block per CU, 27 and 69 us
     constexpr int AU = 8;
-    for (uint32_t e = e0 + threadIdx.x; e < e1; e += AU * ACC_T) {
+    for (uint32_t e = threadIdx.x; e < ne; e += AU * ACC_T) {
         uint32_t key[AU];
         int64_t v[AU];
 #pragma unroll
         for (int q = 0; q < AU; ++q) {
-            const uint32_t ee = min(e + (uint32_t)(q * ACC_T), e1 - 1u);
+            const uint32_t ee = e0 + min(e + (uint32_t)(q * ACC_T), ne - 1u);
             key[q] = d.ev_key[ee];
             v[q] = d.ev_val[ee];
         }
 #pragma unroll
         for (int q = 0; q < AU; ++q) {
-            if (e + (uint32_t)(q * ACC_T) >= e1) continue;
+            if (e + (uint32_t)(q * ACC_T) >= ne) continue;
             const int k = (int)(key[q] & 0x7FFFFFFFu) - k0;
             split_add((key[q] >> 31) ? dd : xn, k, v[q]);
         }
@@ -1208,7 +1210,7 @@ __global__ __launch_bounds__(WG) void k_accum_f32(const Slot *S)
     const int L = fx_exp(d.ctl->amax_bits, g.T);
     const int sc = f32_scale(d.ctl->amax_bits, g.T);
     const uint32_t ne = d.ctl->n_events;
-    for (uint32_t e = blockIdx.x * WG + threadIdx.x; e < ne; e += gridDim.x * WG) {
+    for (uint64_t e = blockIdx.x * WG + threadIdx.x; e < ne; e += gridDim.x * WG) {
         const uint32_t key = d.ev_key[e];
         const float v = (float)ldexp((double)d.ev_val[e], L + sc);
         const int k = (int)(key & 0x7FFFFFFFu);
